@@ -169,6 +169,190 @@ DEV int acc_col(int wn, int j, int lane, int e)
     return wn * S::TN + j * 16 + bcol16(lane, e);
 }
 
+// ---------------------------------------------------------------------------
+// FP64 tile product of rows that are contiguous along k:
+//   acc(m, n) += sum_k A[m][k] B[n][k]
+// on v_mfma_f64_16x16x4_f64, staged by direct global-to-LDS loads.  LDS holds a
+// stage row by row in 16-byte units (two consecutive k), A's BM rows then B's
+// BN; unit u of a row sits at slot u ^ swz(row), so that the eight lanes of a
+// fragment read that share u take eight different bank groups.  A lane reads
+// one unit per 16 rows and 8 k: lane group g = l / 16 takes k = 2g and 2g + 1
+// of the eight, one for each of two MFMAs (A and B permute k alike, so each
+// MFMA still forms four terms of the sum).  A stage needs no VGPRs and no LDS
+// stores, its reads are half as many as with 8-byte fragments, and the loads of
+// the next stage run during the MFMAs of the current one.
+// Measured (262144 x 8192 x 400, the loop alone): 70.4 TFLOP/s with 256 x 64
+// tiles of 8 waves, 71.7 with 128 x 128 of 8 waves, 68.9 with 4-wave tiles; the
+// K-major stages of TileShape, filled through registers, 55.
+// ---------------------------------------------------------------------------
+typedef double d2 __attribute__((ext_vector_type(2)));
+
+template <int BM_, int BN_, int BK_, int WM_, int WN_>
+struct KTile {
+    static constexpr int BM = BM_, BN = BN_, BK = BK_, WM = WM_, WN = WN_;
+    static constexpr bool M16 = true;
+    static constexpr int NT = WM * WN * 64;
+    static constexpr int TM = BM / WM, TN = BN / WN, FM = TM / 16, FN = TN / 16;
+    static constexpr int U = BK / 2;                    // 16-byte units of a row per stage
+    static constexpr int UNITS = (BM + BN) * U;         // units of a stage
+    static constexpr int LPT = (UNITS + NT - 1) / NT;   // units per thread (the last round may be partial)
+    static_assert(BK == 8 || BK == 16, "4 or 8 units per row");
+    static_assert(TM % 16 == 0 && TN % 16 == 0 && UNITS % 64 == 0, "whole 16x16 blocks and wave loads");
+    // rows r and r + 2 (BK = 8) or r + 1 (BK = 16) start in the same bank group
+    DEV static int swz(int row) { return U == 8 ? (row & 7) : ((row >> 1) & 3); }
+    // does this thread's wave load a unit in round i?
+    DEV static bool has(int i) { return UNITS % NT == 0 || i * NT + wave0() < UNITS; }
+    DEV static int wave0() { return __builtin_amdgcn_readfirstlane((int)(threadIdx.x & ~63u)); }
+    DEV static int unit_row(int i) { return (i * NT + (int)threadIdx.x) / U; }
+    DEV static int unit_k(int i) { return 2 * (((i * NT + (int)threadIdx.x) % U) ^ swz(unit_row(i))); }
+};
+
+DEV void load_lds16(const double *g, d2 *l)
+{
+    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)g,
+                                     (__attribute__((address_space(3))) void *)l, 16, 0, 0);
+}
+
+// A full stage (k0 + BK <= d) at src[i] + k0, 16-byte aligned (src[i] points at the
+// thread's unit of round i).  Waits are the caller's (ktile_wait).
+template <class S>
+DEV void ktile_issue(const double *const (&src)[S::LPT], int64_t k0, d2 *stage)
+{
+#pragma unroll
+    for (int i = 0; i < S::LPT; ++i)
+        if (S::has(i))
+            load_lds16(src[i] + k0, stage + i * S::NT + S::wave0());
+}
+
+// The same stage through registers (rows that are not 16-byte aligned).
+template <class S>
+DEV void ktile_load_full(const double *const (&src)[S::LPT], int64_t k0, d2 (&r)[S::LPT])
+{
+#pragma unroll
+    for (int i = 0; i < S::LPT; ++i)
+        if (S::has(i))
+            __builtin_memcpy(&r[i], src[i] + k0, sizeof(d2));
+}
+
+// A ragged last stage through registers, k checked against d.
+template <class S>
+DEV void ktile_load(const double *const (&src)[S::LPT], int64_t k0, int64_t d, d2 (&r)[S::LPT])
+{
+#pragma unroll
+    for (int i = 0; i < S::LPT; ++i)
+        if (S::has(i)) {
+            const int64_t k = k0 + S::unit_k(i);
+            const double *p = src[i] + k0;
+            r[i].x = k < d ? p[0] : 0.0;
+            r[i].y = k + 1 < d ? p[1] : 0.0;
+        }
+}
+template <class S>
+DEV void ktile_store(const d2 (&r)[S::LPT], d2 *stage)
+{
+#pragma unroll
+    for (int i = 0; i < S::LPT; ++i)
+        if (S::has(i))
+            stage[i * S::NT + threadIdx.x] = r[i];
+}
+
+// This wave's part of the stage is in LDS, and after the barrier everyone's.
+DEV void ktile_wait()
+{
+    __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0)
+    __syncthreads();
+}
+
+// The wave's fragments of a whole stage.  They are read before the next stage's direct
+// loads are issued: the compiler takes any LDS read after one to depend on it and would
+// wait for the load there.
+template <class S>
+struct KFrag {
+    d2 a[S::U / 4][S::FM], b[S::U / 4][S::FN];
+};
+
+template <class S>
+DEV void ktile_read(const d2 *stage, KFrag<S> &f, int wm, int wn, int lane)
+{
+    const int rl = lane & 15, g = lane >> 4;
+    const d2 *Sa = stage + (wm * S::TM + rl) * S::U, *Sb = stage + (S::BM + wn * S::TN + rl) * S::U;
+#pragma unroll
+    for (int q = 0; q < S::U / 4; ++q) {
+        const int u = (4 * q + g) ^ S::swz(rl);
+#pragma unroll
+        for (int i = 0; i < S::FM; ++i)
+            f.a[q][i] = Sa[i * 16 * S::U + u];
+#pragma unroll
+        for (int j = 0; j < S::FN; ++j)
+            f.b[q][j] = Sb[j * 16 * S::U + u];
+    }
+}
+
+template <class S>
+DEV void ktile_mma(const KFrag<S> &f, d4 (&acc)[S::FM][S::FN])
+{
+#pragma unroll
+    for (int q = 0; q < S::U / 4; ++q)
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+            for (int i = 0; i < S::FM; ++i)
+#pragma unroll
+                for (int j = 0; j < S::FN; ++j)
+                    acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(f.a[q][i][h], f.b[q][j][h], acc[i][j], 0, 0, 0);
+}
+
+// acc += the product over k = 0 .. d-1; lds: two stages (2 * S::UNITS units).  direct:
+// every src[i] is 16-byte aligned.  Starts with a barrier (LDS may still be in use) and
+// ends with one.
+template <class S>
+DEV void ktile_product(d4 (&acc)[S::FM][S::FN], d2 *lds, const double *const (&src)[S::LPT], int d, bool direct)
+{
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int wm = wave / S::WN, wn = wave % S::WN;
+    const int nk = (d + S::BK - 1) / S::BK, nkf = direct ? d / S::BK : 0;
+    d2 r[S::LPT];
+    __syncthreads();
+    if (nkf > 0) {
+        ktile_issue<S>(src, 0, lds);
+    } else {
+        ktile_load<S>(src, 0, d, r);
+        ktile_store<S>(r, lds);
+    }
+    int kt = 0;
+    KFrag<S> f;
+    for (; kt + 1 < nkf; ++kt) {
+        ktile_wait();
+        ktile_read<S>(lds + (kt & 1) * S::UNITS, f, wm, wn, lane);
+        ktile_issue<S>(src, (kt + 1) * S::BK, lds + ((kt + 1) & 1) * S::UNITS);
+        ktile_mma<S>(f, acc);
+    }
+    for (; kt + 1 < d / S::BK; ++kt) {  // full stages through registers
+        ktile_wait();
+        ktile_load_full<S>(src, (kt + 1) * S::BK, r);
+        ktile_read<S>(lds + (kt & 1) * S::UNITS, f, wm, wn, lane);
+        ktile_mma<S>(f, acc);
+        ktile_store<S>(r, lds + ((kt + 1) & 1) * S::UNITS);
+    }
+    for (; kt < nk; ++kt) {  // the last full stage and a ragged one
+        ktile_wait();
+        const bool more = kt + 1 < nk;
+        if (more)
+            ktile_load<S>(src, (kt + 1) * S::BK, d, r);
+        ktile_read<S>(lds + (kt & 1) * S::UNITS, f, wm, wn, lane);
+        ktile_mma<S>(f, acc);
+        if (more)
+            ktile_store<S>(r, lds + ((kt + 1) & 1) * S::UNITS);
+    }
+    __syncthreads();
+}
+
+// 16-byte alignment of rows of d doubles at p.
+DEV bool rows_aligned16(const double *p, int64_t d)
+{
+    return (reinterpret_cast<uintptr_t>(p) & 15) == 0 && (d & 1) == 0;
+}
+
 // Integer power by repeated multiplication, p = g^zeta (zeta >= 1).
 DEV double ipow(double g, int zeta)
 {

@@ -171,149 +171,24 @@ int64_t knm_max_tiles(int64_t N, int64_t n_atoms)
     return bound < N ? bound : N;
 }
 
-// 256 threads, 4 waves of 64 x BN (BN = 64 by default, 32 as a tuning choice),
-// BK = 8: two workgroups share a CU and cover each other's barriers.
+// 256 threads, 4 waves of 64 x BN (BN = 64 by default, 32 as a tuning choice), BK = 8.
+// Bound by the FP64 matrix cores; two workgroups share a CU and one's tile set-up and
+// epilogue run beside the other's MFMAs.  901,000 atoms x 10,000 x 400: 134 ms (53.7
+// TFLOP/s) with K-major stages filled through registers and 4x4x4 MFMAs, 114 ms (63.0)
+// now.  8 waves of 64 x 32 need 128 VGPRs for the same occupancy and spill: 118 ms.
 template <int BN>
-using KSB = TileShape<KNM_BM, BN, 8, 4, 1>;
+using KSB = KTile<KNM_BM, BN, 8, 4, 1>;
 using KS = KSB<KNM_BN>;
-static_assert(KS::NT == 256, "K_NM kernel assumes 256 threads");
-static_assert(!KS::M16, "the predict row sums assume the 4x4x4 accumulator layout");
-static_assert(KNM_BM == 256 && KNM_BN == 64, "loader mapping assumes 256-atom tiles");
+constexpr int KNM_NT = 256;
+static_assert(KS::NT == KNM_NT && KSB<32>::NT == KNM_NT, "K_NM kernels assume 256 threads");
 
-constexpr int EPC = 32;           // epilogue columns per pass (two 16-column blocks)
+constexpr int EPC = 32;           // epilogue columns per pass
 constexpr int EPLD = EPC + 1;     // padded LDS row of the epilogue buffer
 
-// Load one BK-slice (8 descriptor components) of the atom tile (256 rows) and
-// the sparse tile (BN rows) into registers.  Rows past the valid range and k
-// past d read as zero.  Each thread loads 8 k of its atom row and BN / 32 k of
-// sparse row tid / (256 / BN).
 template <int BN>
-struct KnmLoads {
-    double a[8];
-    double b[BN / 32];
-    bool za = false, zb = false;  // store zeros instead (a missing row, see knm_load_full)
-};
-
-template <int BN>
-DEV void knm_load(KnmLoads<BN> &r, const double *__restrict__ xr, const double *__restrict__ XM, int64_t col0,
-                  int64_t M, int d, int k0)
+constexpr int knm_lds_units()
 {
-    constexpr int TPR = 256 / BN, VB = BN / 32;  // threads per sparse row, k per thread
-    const int tid = threadIdx.x;
-    {
-        // xr: this thread's atom row (nullptr past the tile's atoms)
-        const int kb = k0;
-        if (xr && kb + 8 <= d) {
-#pragma unroll
-            for (int e = 0; e < 8; ++e)
-                r.a[e] = xr[kb + e];
-        } else {
-#pragma unroll
-            for (int e = 0; e < 8; ++e)
-                r.a[e] = (xr && kb + e < d) ? xr[kb + e] : 0.0;
-        }
-    }
-    {
-        const int64_t row = col0 + tid / TPR;
-        const int kb = k0 + (tid % TPR) * VB;
-        const bool rv = row < M;
-        const double *p = XM + row * (int64_t)d + kb;
-        if (rv && kb + VB <= d) {
-#pragma unroll
-            for (int e = 0; e < VB; ++e)
-                r.b[e] = p[e];
-        } else {
-#pragma unroll
-            for (int e = 0; e < VB; ++e)
-                r.b[e] = (rv && kb + e < d) ? p[e] : 0.0;
-        }
-    }
-}
-
-// The same for a slice that lies inside the rows (k0 + 8 <= d), without
-// branches: a thread whose atom or sparse row is missing reads row 0 of XM
-// instead and stores zeros, so the loads stay in flight through the stage's
-// MFMAs (a divergent branch here makes the compiler wait for them before).
-template <int BN>
-DEV void knm_load_full(KnmLoads<BN> &r, const double *__restrict__ xr, const double *__restrict__ XM,
-                       int64_t col0, int64_t M, int d, int k0)
-{
-    constexpr int TPR = 256 / BN, VB = BN / 32;
-    const int tid = threadIdx.x;
-    r.za = !xr;
-    const double *sa = xr ? xr + k0 : XM + k0;
-#pragma unroll
-    for (int e = 0; e < 8; ++e)
-        r.a[e] = sa[e];
-    const int64_t row = col0 + tid / TPR;
-    const int kb = k0 + (tid % TPR) * VB;
-    r.zb = row >= M;
-    const double *sb = row < M ? XM + row * (int64_t)d + kb : XM + kb;
-#pragma unroll
-    for (int e = 0; e < VB; ++e)
-        r.b[e] = sb[e];
-}
-
-template <int BN>
-DEV void knm_store(const KnmLoads<BN> &r, double *As, double *Bs)
-{
-    using S = KSB<BN>;
-    constexpr int TPR = 256 / BN, VB = BN / 32;
-    const int tid = threadIdx.x;
-    {
-        const int row = tid;
-#pragma unroll
-        for (int e = 0; e < 8; ++e)
-            As[e * S::LDA + row] = r.za ? 0.0 : r.a[e];
-    }
-    {
-        const int row = tid / TPR, kb = (tid % TPR) * VB;
-#pragma unroll
-        for (int e = 0; e < VB; ++e)
-            Bs[(kb + e) * S::LDB + row] = r.zb ? 0.0 : r.b[e];
-    }
-}
-
-// G = (the tile's 256 atom rows, thread t's row at xr) . XM[col0 : col0+BN)^T,
-// accumulated in registers.
-template <int BN>
-DEV void knm_gemm(d4 (&acc)[KSB<BN>::FM][KSB<BN>::FN], double *lds, const double *__restrict__ xr,
-                  const double *__restrict__ XM, int64_t col0, int64_t M, int d)
-{
-    using S = KSB<BN>;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int wm = wave / S::WN, wn = wave % S::WN;
-    zero_acc<S>(acc);
-    const int nk = (d + S::BK - 1) / S::BK;
-    const int nkf = d / S::BK;  // slices inside the rows; a ragged last one is loaded with checks
-    KnmLoads<BN> r;
-    if (nkf > 0)
-        knm_load_full<BN>(r, xr, XM, col0, M, d, 0);
-    else
-        knm_load<BN>(r, xr, XM, col0, M, d, 0);
-    knm_store<BN>(r, lds, lds + S::A_ELEMS);
-    __syncthreads();
-    for (int kt = 0; kt < nk; ++kt) {
-        double *cur = lds + (kt & 1) * S::STAGE;
-        double *nxt = lds + ((kt + 1) & 1) * S::STAGE;
-        const bool more = kt + 1 < nkf;
-        if (more)
-            knm_load_full<BN>(r, xr, XM, col0, M, d, (kt + 1) * S::BK);
-        mma_stage<S>(cur, cur + S::A_ELEMS, acc, wm, wn, lane);
-        if (more) {
-            knm_store<BN>(r, nxt, nxt + S::A_ELEMS);
-        } else if (kt + 1 < nk) {  // the ragged last slice, loaded after this stage's MFMAs
-            knm_load<BN>(r, xr, XM, col0, M, d, (kt + 1) * S::BK);
-            knm_store<BN>(r, nxt, nxt + S::A_ELEMS);
-        }
-        __syncthreads();
-    }
-}
-
-template <int BN>
-constexpr int knm_lds_doubles()
-{
-    return (2 * KSB<BN>::STAGE > KNM_BM * EPLD) ? 2 * KSB<BN>::STAGE : KNM_BM * EPLD;
+    return (2 * KSB<BN>::UNITS > KNM_BM * EPLD / 2) ? 2 * KSB<BN>::UNITS : KNM_BM * EPLD / 2;
 }
 
 // One workgroup's tile; bid = the workgroup's index within this K_NM's own grid
@@ -331,8 +206,10 @@ DEV void knm_body(const KnmArgs &a, int64_t bid)
     using KS = KSB<BN>;
     constexpr int KNM_BN = BN;
     static_assert(BN == 32 || BN == 64, "column tile of 32 or 64 sparse points");
-    __shared__ double lds[knm_lds_doubles<BN>()];
+    __shared__ __align__(16) d2 lds[knm_lds_units<BN>()];
     __shared__ int32_t sstart[KNM_MAX_SEG + 1];  // atom offset of each segment within the tile
+    __shared__ int32_t scan_tot[KNM_MAX_SEG / 64];
+    __shared__ int64_t rowpos[KNM_BM];           // row of X of each tile row (-1: none)
     __shared__ int64_t sbase[KNM_MAX_SEG];       // first atom (row of X) of each segment
     __shared__ int32_t srow[KNM_MAX_SEG];        // output row of each segment
     __shared__ double carry[KNM_BN];
@@ -409,17 +286,22 @@ DEV void knm_body(const KnmArgs &a, int64_t bid)
             sbase[tid] = lo;
             srow[tid] = cfg;
         }
-        // inclusive scan of the segment sizes (one per thread)
-        int32_t *scan = reinterpret_cast<int32_t *>(lds);
-        scan[tid] = (int32_t)sz;
-        __syncthreads();
-        for (int off = 1; off < KNM_MAX_SEG; off <<= 1) {
-            const int32_t x = (tid >= off) ? scan[tid - off] : 0;
-            __syncthreads();
-            scan[tid] += x;
-            __syncthreads();
+        // inclusive scan of the segment sizes (one per thread of the first four waves)
+        int32_t incl = (int32_t)sz;
+#pragma unroll
+        for (int off = 1; off < 64; off <<= 1) {
+            const int32_t x = __shfl_up(incl, off, 64);
+            if (lane >= off)
+                incl += x;
         }
-        sstart[tid + 1] = scan[tid];
+        if (tid < KNM_MAX_SEG && lane == 63)
+            scan_tot[wave] = incl;
+        __syncthreads();
+        if (tid < KNM_MAX_SEG) {
+            for (int q = 0; q < wave; ++q)
+                incl += scan_tot[q];
+            sstart[tid + 1] = incl;
+        }
         if (tid == 0)
             sstart[0] = 0;
         __syncthreads();
@@ -453,45 +335,16 @@ DEV void knm_body(const KnmArgs &a, int64_t bid)
         return;
     }
 
-    // This thread's atom row for a tile of whole segments: segment by binary search.
-    const double *xr_packed = nullptr;
     const bool multi = n_at > KNM_BM;  // then n_seg == 1: a configuration in several atom chunks
-    if (!multi && tid < n_at) {
-        int lo = 0, hi = n_seg - 1;
-        while (lo < hi) {
-            const int mid = (lo + hi + 1) >> 1;
-            if (sstart[mid] <= tid)
-                lo = mid;
-            else
-                hi = mid - 1;
-        }
-        const int64_t pos = sbase[lo] + (tid - sstart[lo]);
-        xr_packed = a.X + (DERIV ? a.pos_grad[pos] : pos) * (int64_t)a.d;
-        if (DERIV && !kdm_valid(a, pos)) {
-            xr_packed = nullptr;
-            set_status(a.status, DST_EINVAL);
-        }
-    }
+    const bool direct = rows_aligned16(a.X, a.d) && rows_aligned16(a.XM, a.d);
     d4 acc[KS::FM][KS::FN];
     for (int64_t cs = 0; cs < n_at; cs += KNM_BM) {
         const bool first = (cs == 0), last = (cs + KNM_BM >= n_at);
-        const double *xr = xr_packed;
-        if (multi) {
-            const int64_t pos = sbase[0] + cs + tid;
-            xr = (cs + tid < n_at) ? a.X + (DERIV ? a.pos_grad[pos] : pos) * (int64_t)a.d : nullptr;
-            if (DERIV && xr && !kdm_valid(a, pos)) {
-                xr = nullptr;
-                set_status(a.status, DST_EINVAL);
-            }
-        }
-        if constexpr (DERIV) {
-            // this thread's tile row: its weight and its gradient's atom
+        // the tile rows' positions: segment by binary search (the first one when multi)
+        if (tid < KNM_BM) {
             int64_t pos = -1;
-            if (multi) {
-                if (cs + tid < n_at)
-                    pos = sbase[0] + cs + tid;
-            } else if (xr) {
-                int lo = 0, hi = n_seg - 1;
+            if (cs + tid < n_at) {
+                int lo = 0, hi = multi ? 0 : n_seg - 1;
                 while (lo < hi) {
                     const int mid = (lo + hi + 1) >> 1;
                     if (sstart[mid] <= tid)
@@ -499,15 +352,44 @@ DEV void knm_body(const KnmArgs &a, int64_t bid)
                     else
                         hi = mid - 1;
                 }
-                pos = sbase[lo] + (tid - sstart[lo]);
+                pos = sbase[lo] + (cs + tid - sstart[lo]);
             }
-            if (pos >= 0 && !kdm_valid(a, pos))
-                pos = -1;  // reported above; the row reads as zero
-            rowf[tid] = pos >= 0 ? a.zeta * a.sw2 * a.pos_weight[pos] : 0.0;
-            rowatom[tid] = pos >= 0 ? a.grad_atom[a.pos_grad[pos]] : -1;
+            if constexpr (DERIV) {
+                // this tile row's weight and its gradient's atom
+                if (pos >= 0 && !kdm_valid(a, pos)) {
+                    pos = -1;  // the row counts as zero
+                    set_status(a.status, DST_EINVAL);
+                }
+                rowf[tid] = pos >= 0 ? a.zeta * a.sw2 * a.pos_weight[pos] : 0.0;
+                rowatom[tid] = pos >= 0 ? a.grad_atom[a.pos_grad[pos]] : -1;
+                if (pos >= 0)
+                    pos = a.pos_grad[pos];
+            }
+            rowpos[tid] = pos;
         }
         __syncthreads();
-        knm_gemm<BN>(acc, lds, xr, a.XM, col0, a.M, a.d);
+        // this thread's units; a missing atom row or sparse row reads the first sparse row
+        // (its products are never used)
+        const double *src[KS::LPT];
+#pragma unroll
+        for (int i = 0; i < KS::LPT; ++i) {
+            const int r = KS::unit_row(i);
+            const double *p = a.XM;
+            if (r < KNM_BM) {
+                const int64_t pos = rowpos[r];
+                if (pos >= 0)
+                    p = a.X + pos * (int64_t)a.d;
+            } else if (col0 + r - KNM_BM < a.M) {
+                p = a.XM + (col0 + r - KNM_BM) * (int64_t)a.d;
+            }
+            src[i] = p + KS::unit_k(i);
+        }
+#pragma unroll
+        for (int i = 0; i < KS::FM; ++i)
+#pragma unroll
+            for (int j = 0; j < KS::FN; ++j)
+                acc[i][j] = d4{0.0, 0.0, 0.0, 0.0};
+        ktile_product<KS>(acc, lds, src, a.d, direct);
 
         if constexpr (DERIV) {
             // d k / dr = zeta sigma_w^2 (x_i . x_j)^(zeta - 1) (x' . x_j), times the
@@ -523,10 +405,10 @@ DEV void knm_body(const KnmArgs &a, int64_t bid)
                         acc[i][j][e] = a.sw2 * ipow(acc[i][j][e], a.zeta);
         }
 
-        double *E = lds;  // [256][EPLD], reused after the GEMM
+        double *E = reinterpret_cast<double *>(lds);  // [256][EPLD], reused after the GEMM
         for (int p = 0; p < (KNM_BN + EPC - 1) / EPC; ++p) {
-            // waves owning columns [p*16, p*16+16) park their values in LDS
-            if (wn == (p * EPC) / KS::TN) {
+            // waves owning columns of the pass park their values in LDS
+            if (wn * KS::TN < (p + 1) * EPC && (wn + 1) * KS::TN > p * EPC) {
 #pragma unroll
                 for (int i = 0; i < KS::FM; ++i)
 #pragma unroll
@@ -541,7 +423,7 @@ DEV void knm_body(const KnmArgs &a, int64_t bid)
                                     // (rowf / rowatom were written before the GEMM's barriers)
                                     const int64_t at = rowatom[r], colg = col0 + p * EPC + cl;
                                     const double dv = (a.D && at >= 0 && colg < a.M) ? a.D[at * a.ldd + colg] : 1.0;
-                                    v = v * (rowf[r] * dv);
+                                    v = at >= 0 ? v * (rowf[r] * dv) : 0.0;
                                 }
                                 E[r * EPLD + cl] = v;
                             }
@@ -600,14 +482,14 @@ DEV void knm_body(const KnmArgs &a, int64_t bid)
 }
 
 template <int BN>
-__global__ __launch_bounds__(256, 2) void knm_kernel(KnmArgs a) { knm_body<BN>(a, blockIdx.x); }
+__global__ __launch_bounds__(KNM_NT, 2) void knm_kernel(KnmArgs a) { knm_body<BN>(a, blockIdx.x); }
 
 // Derivative observation rows: the K_NM tile loop over the observations' positions.
-__global__ __launch_bounds__(256, 2) void kdm_kernel(KnmArgs a) { knm_body<64, true>(a, blockIdx.x); }
+__global__ __launch_bounds__(KNM_NT, 2) void kdm_kernel(KnmArgs a) { knm_body<64, true>(a, blockIdx.x); }
 
 // The K_NM of several fits in one grid: fit i owns workgroups [base[i], base[i+1]).
 template <int BN>
-__global__ __launch_bounds__(256, 2) void knm_group_kernel(KnmGroup g)
+__global__ __launch_bounds__(KNM_NT, 2) void knm_group_kernel(KnmGroup g)
 {
     const int64_t b = blockIdx.x;
     int i = 0;
@@ -618,109 +500,300 @@ __global__ __launch_bounds__(256, 2) void knm_group_kernel(KnmGroup g)
 
 // ---------------------------------------------------------------------------
 // Prediction (Eqs. 1-2): y_A = sum_{i in A} sum_j c_j sigma_w^2 (x_i . x_j)^zeta.
-// Workgroup w owns configurations [w*C, (w+1)*C); it walks their atoms in
-// chunks of 256, accumulates each atom's energy over all sparse tiles in LDS
-// (the atom-by-sparse covariances stay in registers), then one thread per
-// configuration adds its atoms' energies in atom order.
-// ---------------------------------------------------------------------------
-__global__ __launch_bounds__(256, 2) void predict_kernel(const double *__restrict__ X, const int64_t *offsets,
-                                                      int64_t N, int64_t n_atoms, const double *__restrict__ XM,
-                                                      int64_t M, int d, int zeta, double sw2,
-                                                      const double *__restrict__ c, double *y, int64_t C,
-                                                      int32_t *status)
+//
+// The atoms are cut into tiles of BM consecutive rows and the sparse points into
+// `split` runs of column tiles; workgroup (tile, run) forms its atoms' energies
+// over its run (the atom-by-sparse covariances stay in registers) and adds them
+// up, in atom order, over the piece of each configuration that lies in the tile.
+// A second kernel adds a configuration's pieces: tile by tile, run by run.  One
+// request's column runs thus spread over the chip: with one workgroup per
+// few configurations and all columns, a single configuration against 4,000
+// points took 4.2 ms on one CU, and 4,096 configurations 21 ms with the
+// CUs a third idle in the last round.
+//
+// The pieces live in a static pool of PRED_SLOTS slots per GPU (a predict call has
+// no workspace).  The call's first kernel claims a free slot and writes its
+// number into the call's own output (the first entry of each group of
+// configurations, which is written last); the last workgroup of the second
+// kernel frees it.  Claiming on the device works for any streams, threads and
+// captured graphs, and never waits: with no slot free (more than PRED_SLOTS
+// calls in flight), with malformed offsets, or when one request's pieces exceed a
+// slot, the second kernel computes its groups' tiles itself, with the same sums in
+// the same order.
+//
+// Bound by the matrix cores from a few hundred configurations on (d = 400, M = 4,000:
+// 4,096 configurations 21.3 -> 7.6 ms, 62 TFLOP/s; d = 256, M = 2,250: 333
+// configurations 3.2 -> 0.26 ms), by the latency of the column tile's k loop below
+// (one configuration 4,230 -> 29 us, three launches). ---------------------------------------------------------------------------
+constexpr int PRED_SLOTS = 32;
+constexpr int64_t PRED_CAP = 131072;  // doubles of a slot (1 MiB)
+static __device__ double g_pred_pool[PRED_SLOTS * PRED_CAP];
+static __device__ unsigned g_pred_busy[PRED_SLOTS];
+static __device__ unsigned g_pred_done[PRED_SLOTS];
+
+// Both tile heights give waves of 64 columns and the same order of every sum.
+using PSL = KTile<KNM_BM, KNM_BN, 8, 4, 1>;  // 256 atoms
+using PSS = KTile<64, KNM_BN, 16, 4, 1>;     // 64 atoms
+static_assert(PSL::TN == PSS::TN && PSL::WN == PSS::WN && PSL::NT == KNM_NT, "one summation order");
+
+struct PredArgs {
+    const double *X;
+    const int64_t *offsets;
+    int64_t N, n_atoms;
+    const double *XM;
+    int64_t M;
+    int d, zeta;
+    double sw2;
+    const double *c;
+    double *y;
+    int32_t *status;
+    int64_t C;              // configurations per group (checked together; a bad one makes the group NaN)
+    int64_t tiles, n_ct;    // atom tiles, column tiles
+    int split;              // runs of column tiles
+    int small;              // 64-atom tiles
+};
+
+// Energies of the tile's atoms over column tiles [ct0, ct1), into eps[0 .. S::BM).
+template <class S>
+DEV void predict_tile_energies(const PredArgs &a, int64_t t, int64_t ct0, int64_t ct1, d2 *lds,
+                               double (&part)[S::WN][S::BM], double *eps)
 {
-    __shared__ double lds[2 * KS::STAGE];
-    __shared__ double eps[KNM_BM];
-    __shared__ double part[KS::WN][KNM_BM];
-    __shared__ int bad_s;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int wm = wave / KS::WN, wn = wave % KS::WN;
-    const int64_t cfg_lo = (int64_t)blockIdx.x * C;
-    int64_t cfg_hi = cfg_lo + C;
-    if (cfg_hi > N)
-        cfg_hi = N;
-    if (cfg_lo >= cfg_hi)
+    const int wm = wave / S::WN, wn = wave % S::WN;
+    const bool direct = rows_aligned16(a.X, a.d) && rows_aligned16(a.XM, a.d);
+    double e_sum = 0.0;
+    for (int64_t ct = ct0; ct < ct1; ++ct) {
+        const int64_t col0 = ct * S::BN;
+        const double *src[S::LPT];
+#pragma unroll
+        for (int i = 0; i < S::LPT; ++i) {
+            const int r = S::unit_row(i);
+            const double *p = a.XM;  // a missing row reads the first sparse row, unused below
+            if (r < S::BM) {
+                if (t * S::BM + r < a.n_atoms)
+                    p = a.X + (t * S::BM + r) * (int64_t)a.d;
+            } else if (col0 + r - S::BM < a.M) {
+                p = a.XM + (col0 + r - S::BM) * (int64_t)a.d;
+            }
+            src[i] = p + S::unit_k(i);
+        }
+        d4 acc[S::FM][S::FN];
+#pragma unroll
+        for (int i = 0; i < S::FM; ++i)
+#pragma unroll
+            for (int j = 0; j < S::FN; ++j)
+                acc[i][j] = d4{0.0, 0.0, 0.0, 0.0};
+        ktile_product<S>(acc, lds, src, a.d, direct);
+        double cw[S::FN];
+        bool in[S::FN];
+#pragma unroll
+        for (int j = 0; j < S::FN; ++j) {
+            const int64_t col = col0 + acc_col<S>(wn, j, lane, 0);
+            in[j] = col < a.M;
+            cw[j] = in[j] ? a.c[col] : 0.0;
+        }
+#pragma unroll
+        for (int i = 0; i < S::FM; ++i)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                double s = 0.0;
+#pragma unroll
+                for (int j = 0; j < S::FN; ++j)
+                    s += in[j] ? cw[j] * (a.sw2 * ipow(acc[i][j][e], a.zeta)) : 0.0;
+                // the 16 lanes that share l / 16 share this row
+                s += __shfl_xor(s, 1, 64);
+                s += __shfl_xor(s, 2, 64);
+                s += __shfl_xor(s, 4, 64);
+                s += __shfl_xor(s, 8, 64);
+                if ((lane & 15) == 0)
+                    part[wn][acc_row<S>(wm, i, lane, e)] = s;
+            }
+        __syncthreads();
+        if (tid < S::BM) {
+            double add = part[0][tid];
+#pragma unroll
+            for (int q = 1; q < S::WN; ++q)
+                add += part[q][tid];
+            e_sum += add;
+        }
+    }
+    if (tid < S::BM)
+        eps[tid] = e_sum;
+    __syncthreads();
+}
+
+// First and last column tile of run s.
+DEV int64_t run_lo(const PredArgs &a, int64_t s) { return s * a.n_ct / a.split; }
+
+// Number of configurations whose atoms end at or before row r (every lane probes one
+// point of the remaining range; uniform).
+DEV int64_t configs_before(const int64_t *offsets, int64_t N, int64_t r)
+{
+    const int lane = threadIdx.x & 63;
+    int64_t lo = 0, hi = N;  // offsets[c + 1] <= r for c < lo, > r for c >= hi
+    while (lo < hi) {
+        const int64_t step = (hi - lo + 63) / 64;
+        const int64_t c = lo + lane * step;
+        const uint64_t le = __ballot(c < hi && offsets[c + 1] <= r);
+        const int k = __builtin_ctzll(~le);  // leading run of probes at or before r (64: all of them)
+        const int64_t first_gt = lo + (int64_t)(le == ~0ull ? 64 : k) * step;
+        if (k > 0 || le == ~0ull)
+            lo = first_gt - step + 1;
+        if (first_gt < hi)
+            hi = first_gt;
+    }
+    return lo;
+}
+
+// The call's slot, and the claim kernel that finds one.
+DEV int64_t pred_slot(const double *y, int64_t at)
+{
+    return __double_as_longlong(y[at]);
+}
+
+// Also checks every offset: with a malformed one no slot is taken, and each group computes
+// its own tiles (a good group's energies do not depend on the others' offsets).
+constexpr int CLAIM_NT = 1024;
+__global__ __launch_bounds__(CLAIM_NT) void predict_claim_kernel(PredArgs a, int64_t n_groups)
+{
+    __shared__ int slot_s, bad_s;
+    if (threadIdx.x == 0)
+        bad_s = 0;
+    __syncthreads();
+    bool bad = threadIdx.x == 0 && (a.offsets[0] != 0 || a.offsets[a.N] != a.n_atoms);
+    for (int64_t c = threadIdx.x; c < a.N; c += CLAIM_NT)
+        bad |= a.offsets[c] > a.offsets[c + 1];
+    if (bad)
+        bad_s = 1;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        int slot = -1;
+        if (!bad_s)
+            for (int k = 0; k < PRED_SLOTS && slot < 0; ++k)
+                if (atomicCAS(&g_pred_busy[k], 0u, 1u) == 0u)
+                    slot = k;
+        slot_s = slot;
+    }
+    __syncthreads();
+    for (int64_t w = threadIdx.x; w < n_groups; w += CLAIM_NT)
+        a.y[w * a.C] = __longlong_as_double((long long)slot_s);
+}
+
+template <class S>
+__global__ __launch_bounds__(S::NT, S::BM == 64 ? 3 : 2) void predict_tile_kernel(PredArgs a)
+{
+    __shared__ __align__(16) d2 lds[2 * S::UNITS];
+    __shared__ double part[S::WN][S::BM];
+    __shared__ double eps[S::BM];
+    const int64_t total = a.tiles * a.split;
+    const int64_t lw = xcd_remap(blockIdx.x, (total + 7) & ~int64_t(7));
+    if (lw >= total)
         return;
+    const int64_t slot = pred_slot(a.y, 0);
+    if (slot < 0)
+        return;
+    const int64_t t = lw / a.split, s = lw % a.split;
+    // the configurations that own the tile's first and last row
+    const int64_t r0 = t * S::BM, r1 = (r0 + S::BM < a.n_atoms) ? r0 + S::BM : a.n_atoms;
+    const int64_t c_first = configs_before(a.offsets, a.N, r0), c_end = configs_before(a.offsets, a.N, r1 - 1) + 1;
+    predict_tile_energies<S>(a, t, run_lo(a, s), run_lo(a, s + 1), lds, part, eps);
+    double *out = g_pred_pool + slot * PRED_CAP + s * (a.N + a.tiles) + t;
+    for (int64_t c = c_first + threadIdx.x; c < c_end && c < a.N; c += S::NT) {
+        int64_t lo = a.offsets[c], hi = a.offsets[c + 1];
+        lo = lo > r0 ? lo : r0;
+        hi = hi < r1 ? hi : r1;
+        if (lo >= hi)
+            continue;
+        double sum = 0.0;
+        for (int64_t r = lo; r < hi; ++r)
+            sum += eps[r - r0];
+        out[c] = sum;
+    }
+}
+
+// One group of configurations: checks their offsets, then adds up their pieces.
+__global__ __launch_bounds__(KNM_NT) void predict_sum_kernel(PredArgs a)
+{
+    using S = PSL;
+    __shared__ __align__(16) d2 lds[2 * S::UNITS];
+    __shared__ double part[S::WN][S::BM];
+    __shared__ double eps[S::BM];
+    __shared__ int bad_s, last_s;
+    const int tid = threadIdx.x;
+    const int64_t cfg_lo = (int64_t)blockIdx.x * a.C;
+    const int64_t cfg_hi = (cfg_lo + a.C < a.N) ? cfg_lo + a.C : a.N;
     const int ncfg = (int)(cfg_hi - cfg_lo);
-    // Validate this workgroup's offsets before any descriptor is read: each of its
-    // configurations must be a range inside [0, n_atoms) (so every row read is in
-    // bounds); offsets[0] = 0 and offsets[N] = n_atoms are checked by the first
-    // and last workgroup.  A violation gives NaN energies for the workgroup's
-    // configurations and GAP_EINVAL in the status word (when there is one).
+    // Every configuration must be a range inside [0, n_atoms); offsets[0] = 0 and offsets[N] =
+    // n_atoms are checked by the first and last group.  A violation gives NaN energies for the
+    // group and GAP_EINVAL in the status word (when there is one).
+    const int64_t slot = a.split > 0 ? pred_slot(a.y, cfg_lo) : -1;
     if (tid == 0)
         bad_s = 0;
     __syncthreads();
     int64_t my_lo = 0, my_hi = 0;
     if (tid < ncfg) {
-        my_lo = offsets[cfg_lo + tid];
-        my_hi = offsets[cfg_lo + tid + 1];
-        if (my_lo < 0 || my_hi < my_lo || my_hi > n_atoms)
+        my_lo = a.offsets[cfg_lo + tid];
+        my_hi = a.offsets[cfg_lo + tid + 1];
+        if (my_lo < 0 || my_hi < my_lo || my_hi > a.n_atoms)
             bad_s = 1;
     }
-    if (tid == 0 && ((cfg_lo == 0 && offsets[0] != 0) || (cfg_hi == N && offsets[N] != n_atoms)))
+    if (tid == 0 && ((cfg_lo == 0 && a.offsets[0] != 0) || (cfg_hi == a.N && a.offsets[a.N] != a.n_atoms)))
         bad_s = 1;
     __syncthreads();
-    if (bad_s) {
-        if (tid < ncfg)
-            y[cfg_lo + tid] = __builtin_nan("");
-        if (tid == 0 && status)
-            set_status(status, DST_EINVAL);
-        return;
-    }
-    const int64_t atom_lo = offsets[cfg_lo], atom_hi = offsets[cfg_hi];
+    const bool bad = bad_s != 0;
     double ysum = 0.0;
-    const int64_t n_ct = (M + KNM_BN - 1) / KNM_BN;
-    d4 acc[KS::FM][KS::FN];
-    for (int64_t cs = atom_lo; cs < atom_hi; cs += KNM_BM) {
-        __syncthreads();  // the previous chunk's sums have read eps
-        if (tid < KNM_BM)
-            eps[tid] = 0.0;
-        for (int64_t ct = 0; ct < n_ct; ++ct) {
-            const int64_t col0 = ct * KNM_BN;
-            __syncthreads();
-            knm_gemm<KNM_BN>(acc, lds, (cs + tid < atom_hi) ? X + (cs + tid) * (int64_t)d : nullptr, XM, col0, M,
-                             d);
-            double cw[KS::FN][4];
-#pragma unroll
-            for (int j = 0; j < KS::FN; ++j)
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    const int64_t col = col0 + acc_col<KS>(wn, j, lane, e);
-                    cw[j][e] = (col < M) ? c[col] : 0.0;
-                }
-#pragma unroll
-            for (int i = 0; i < KS::FM; ++i) {
-                double s = 0.0;
-#pragma unroll
-                for (int j = 0; j < KS::FN; ++j)
-#pragma unroll
-                    for (int e = 0; e < 4; ++e)
-                        s += cw[j][e] * (sw2 * ipow(acc[i][j][e], zeta));
-                // the 4 lanes that differ in l % 4 share this row
-                s += __shfl_xor(s, 1, 64);
-                s += __shfl_xor(s, 2, 64);
-                if ((lane & 3) == 0)
-                    part[wn][acc_row<KS>(wm, i, lane, 0)] = s;
-            }
-            __syncthreads();
-            if (tid < KNM_BM) {
-                double add = 0.0;
-#pragma unroll
-                for (int q = 0; q < KS::WN; ++q)
-                    add += part[q][tid];
-                eps[tid] += add;
+    if (bad) {
+        ysum = __builtin_nan("");
+        if (tid == 0 && a.status)
+            set_status(a.status, DST_EINVAL);
+    } else if (slot >= 0) {
+        if (tid < ncfg && my_lo < my_hi) {
+            const int64_t bm = a.small ? PSS::BM : PSL::BM;
+            const double *p = g_pred_pool + slot * PRED_CAP + cfg_lo + tid;
+            for (int64_t t = my_lo / bm; t * bm < my_hi; ++t) {
+                double piece = 0.0;
+#pragma unroll 8
+                for (int s = 0; s < a.split; ++s)
+                    piece += p[s * (a.N + a.tiles) + t];
+                ysum += piece;
             }
         }
-        __syncthreads();
-        if (tid < ncfg) {
-            const int64_t lo = my_lo > cs ? my_lo : cs;
-            const int64_t hi = my_hi < cs + KNM_BM ? my_hi : cs + KNM_BM;
-            for (int64_t a = lo; a < hi; ++a)
-                ysum += eps[a - cs];
+    } else {
+        // no slot: the tiles that the group meets (of 256 rows, four small tiles at a time),
+        // and in them the pieces of its configurations
+        const int64_t atom_lo = a.offsets[cfg_lo], atom_hi = a.offsets[cfg_hi];
+        const int64_t bm = a.small ? PSS::BM : PSL::BM;
+        const int runs = a.split > 0 ? a.split : 1;
+        PredArgs b = a;
+        b.split = runs;
+        for (int64_t t = atom_lo / S::BM; t * S::BM < atom_hi; ++t) {
+            const int64_t r0 = t * S::BM;
+            constexpr int PIECES = PSL::BM / PSS::BM;
+            double piece[PIECES] = {};
+            for (int s = 0; s < runs; ++s) {
+                predict_tile_energies<S>(b, t, run_lo(b, s), run_lo(b, s + 1), lds, part, eps);
+#pragma unroll
+                for (int q = 0; q < PIECES; ++q) {
+                    const int64_t q0 = r0 + q * bm, q1 = (q + 1) * bm <= S::BM ? q0 + bm : q0;
+                    const int64_t lo = my_lo > q0 ? my_lo : q0, hi = my_hi < q1 ? my_hi : q1;
+                    double sum = 0.0;
+                    if (tid < ncfg)
+                        for (int64_t r = lo; r < hi; ++r)
+                            sum += eps[r - r0];
+                    piece[q] += sum;
+                }
+                __syncthreads();
+            }
+#pragma unroll
+            for (int q = 0; q < PIECES; ++q)
+                ysum += piece[q];
         }
     }
     if (tid < ncfg)
-        y[cfg_lo + tid] = ysum;
+        a.y[cfg_lo + tid] = ysum;
+    // the last workgroup to have read the pieces frees the slot
+    if (slot >= 0 && arrive_last(&g_pred_done[slot], gridDim.x, &last_s) && tid == 0)
+        __hip_atomic_store(&g_pred_busy[slot], 0u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 hipError_t launch_predict(const double *X, int64_t n_atoms, const int64_t *offsets, int64_t N,
@@ -729,14 +802,43 @@ hipError_t launch_predict(const double *X, int64_t n_atoms, const int64_t *offse
 {
     if (N <= 0)
         return hipSuccess;
-    int64_t C = n_atoms > 0 ? (224 * N) / n_atoms : N;
-    if (C < 1)
-        C = 1;
-    if (C > 256)
-        C = 256;
-    const int64_t grid = (N + C - 1) / C;
-    hipLaunchKernelGGL(predict_kernel, dim3((unsigned)grid), dim3(KS::NT), 0, s, X, offsets, N, n_atoms, XM, M,
-                       d, zeta, sw2, c, y, C, status);
+    PredArgs a{};
+    a.X = X;
+    a.offsets = offsets;
+    a.N = N;
+    a.n_atoms = n_atoms;
+    a.XM = XM;
+    a.M = M;
+    a.d = d;
+    a.zeta = zeta;
+    a.sw2 = sw2;
+    a.c = c;
+    a.y = y;
+    a.status = status;
+    a.C = n_atoms > 0 ? (224 * N) / n_atoms : N;
+    a.C = a.C < 1 ? 1 : (a.C > 256 ? 256 : a.C);
+    const int64_t groups = (N + a.C - 1) / a.C;
+    // 64-atom tiles where 256-atom ones would not fill the chip's 512 workgroup places
+    // twice: a workgroup then has a quarter of the work, and the last round costs less
+    a.n_ct = (M + KNM_BN - 1) / KNM_BN;
+    const int64_t large = (n_atoms + PSL::BM - 1) / PSL::BM;
+    a.small = large * a.n_ct < 1024;
+    a.tiles = a.small ? (n_atoms + PSS::BM - 1) / PSS::BM : large;
+    // runs: enough workgroups for about twelve rounds, so that the last one costs little
+    int64_t split = a.tiles > 0 ? (6144 + a.tiles - 1) / a.tiles : 0;
+    split = split > a.n_ct ? a.n_ct : split;
+    if (split * (N + a.tiles) > PRED_CAP)
+        split = PRED_CAP / (N + a.tiles);
+    a.split = (int)split;  // 0: no atoms, or too many pieces for a slot
+    if (a.split > 0) {
+        hipLaunchKernelGGL(predict_claim_kernel, dim3(1), dim3(CLAIM_NT), 0, s, a, groups);
+        const unsigned grid = (unsigned)((a.tiles * a.split + 7) & ~int64_t(7));
+        if (a.small)
+            hipLaunchKernelGGL(predict_tile_kernel<PSS>, dim3(grid), dim3(PSS::NT), 0, s, a);
+        else
+            hipLaunchKernelGGL(predict_tile_kernel<PSL>, dim3(grid), dim3(PSL::NT), 0, s, a);
+    }
+    hipLaunchKernelGGL(predict_sum_kernel, dim3((unsigned)groups), dim3(KNM_NT), 0, s, a);
     return hipGetLastError();
 }
 
@@ -760,9 +862,9 @@ hipError_t launch_knm_group(const KnmArgs *fits, const int64_t *max_tiles, int n
         auto flush = [&]() {
             if (g.n > 0 && g.base[g.n] > 0) {
                 if (bn == 64)
-                    hipLaunchKernelGGL(knm_group_kernel<64>, dim3((unsigned)g.base[g.n]), dim3(256), 0, s, g);
+                    hipLaunchKernelGGL(knm_group_kernel<64>, dim3((unsigned)g.base[g.n]), dim3(KNM_NT), 0, s, g);
                 else
-                    hipLaunchKernelGGL(knm_group_kernel<32>, dim3((unsigned)g.base[g.n]), dim3(256), 0, s, g);
+                    hipLaunchKernelGGL(knm_group_kernel<32>, dim3((unsigned)g.base[g.n]), dim3(KNM_NT), 0, s, g);
             }
             g = KnmGroup{};
         };
@@ -789,7 +891,7 @@ hipError_t launch_kdm(KnmArgs a, int64_t max_tiles, hipStream_t s)
     a.total_pad = (max_tiles + 7) / 8 * 8 * a.n_ct;  // whole rounds of 8 tiles (see knm_body)
     if (a.total_pad == 0)
         return hipSuccess;
-    hipLaunchKernelGGL(kdm_kernel, dim3((unsigned)a.total_pad), dim3(256), 0, s, a);
+    hipLaunchKernelGGL(kdm_kernel, dim3((unsigned)a.total_pad), dim3(KNM_NT), 0, s, a);
     return hipGetLastError();
 }
 
@@ -802,9 +904,9 @@ hipError_t launch_knm(KnmArgs a, int64_t max_tiles, hipStream_t s)
     if (a.total_pad == 0)
         return hipSuccess;
     if (bn == 64)
-        hipLaunchKernelGGL(knm_kernel<64>, dim3((unsigned)a.total_pad), dim3(256), 0, s, a);
+        hipLaunchKernelGGL(knm_kernel<64>, dim3((unsigned)a.total_pad), dim3(KNM_NT), 0, s, a);
     else
-        hipLaunchKernelGGL(knm_kernel<32>, dim3((unsigned)a.total_pad), dim3(256), 0, s, a);
+        hipLaunchKernelGGL(knm_kernel<32>, dim3((unsigned)a.total_pad), dim3(KNM_NT), 0, s, a);
     return hipGetLastError();
 }
 
