@@ -14,6 +14,7 @@ using namespace gap;
 namespace {
 
 constexpr int N_STAGES = 10;
+constexpr int N_COUNTERS = 16;  // arrival counters
 
 enum State { ST_CREATED = 0, ST_BOUND = 1, ST_KNM = 2, ST_BUILT = 3, ST_SOLVED = 4 };
 
@@ -97,15 +98,15 @@ Layout make_layout(int64_t NE, int64_t n_atoms, int64_t M, int32_t precision, in
     L.off_rhs = takep(sizeof(double) * (size_t)M);
     L.off_misc = takep(sizeof(double) * 512);
     L.off_tiles = take(sizeof(int32_t) * (size_t)(L.max_tiles + 2));
-    L.off_plan = take(sizeof(int32_t) * (size_t)(NE + knm_plan_chunks(NE) * (2049 + 1)));
+    L.off_plan = take(sizeof(int32_t) * (size_t)knm_plan_ints(NE));
     if (n_obs > 0) {
         // derivative observations: their tile plan over the positions, and D = (X X_M^T)^(zeta - 1)
         L.max_tiles_d = knm_max_tiles(n_obs, n_pos);
         L.off_tiles_d = take(sizeof(int32_t) * (size_t)(L.max_tiles_d + 2));
-        L.off_plan_d = take(sizeof(int32_t) * (size_t)(n_obs + knm_plan_chunks(n_obs) * (2049 + 1)));
+        L.off_plan_d = take(sizeof(int32_t) * (size_t)knm_plan_ints(n_obs));
         L.off_D = takep(sizeof(double) * (size_t)n_atoms * (size_t)M);
     }
-    L.off_counters = take(sizeof(unsigned) * 16);
+    L.off_counters = take(sizeof(unsigned) * N_COUNTERS);
     L.off_status = take(sizeof(int32_t) * 4);
     L.n_tflags = trsv_sync_ints(M);
     L.off_tflags = take(sizeof(int32_t) * (size_t)L.n_tflags);
@@ -228,10 +229,17 @@ __global__ void zero_u32_kernel(unsigned *p, int n)
         p[threadIdx.x] = 0u;
 }
 
-__global__ void zero_i32_kernel(int32_t *p, int64_t n)
+// The build's counters [N_COUNTERS], status words [4] and triangular-solve flags [n].
+__global__ __launch_bounds__(256) void build_clear_kernel(unsigned *counters, int32_t *status, int32_t *flags,
+                                                          int64_t n)
 {
-    for (int64_t i = threadIdx.x; i < n; i += blockDim.x)
-        p[i] = 0;
+    const int t = threadIdx.x;
+    if (t < N_COUNTERS)
+        counters[t] = 0u;
+    else if (t < N_COUNTERS + 4)
+        status[t - N_COUNTERS] = 0;
+    for (int64_t i = t; i < n; i += 256)
+        flags[i] = 0;
 }
 
 // All-ones words over n 4-byte words (GAP_FLAG_POISON_WORKSPACE).
@@ -500,8 +508,7 @@ static KnmPlan plan_of(gap_handle h)
     kp.tile_start = tiles;
     kp.n_tiles = tiles + L.max_tiles + 1;
     kp.cfg_list = plan;
-    kp.lstart = plan + L.NE;
-    kp.lcount = kp.lstart + knm_plan_chunks(L.NE) * 2049;
+    kp.lists = reinterpret_cast<uint16_t *>(plan + L.NE);
     return kp;
 }
 
@@ -515,8 +522,7 @@ static KnmPlan plan_of_d(gap_handle h)
     kp.tile_start = tiles;
     kp.n_tiles = tiles + L.max_tiles_d + 1;
     kp.cfg_list = plan;
-    kp.lstart = plan + L.n_obs;
-    kp.lcount = kp.lstart + knm_plan_chunks(L.n_obs) * 2049;
+    kp.lists = reinterpret_cast<uint16_t *>(plan + L.n_obs);
     return kp;
 }
 
@@ -534,9 +540,8 @@ static gap_status build_setup(gap_handle h, hipStream_t s, KnmArgs *a)
             const unsigned blocks = (unsigned)std::min<int64_t>((words + 255) / 256, 4096);
             hipLaunchKernelGGL(poison_kernel, dim3(blocks), dim3(256), 0, s, h->at<uint32_t>(L.poison_off[i]), words);
         }
-    hipLaunchKernelGGL(zero_u32_kernel, dim3(1), dim3(64), 0, s, h->counters(), 16);
-    hipLaunchKernelGGL(zero_u32_kernel, dim3(1), dim3(64), 0, s, reinterpret_cast<unsigned *>(h->status()), 4);
-    hipLaunchKernelGGL(zero_i32_kernel, dim3(1), dim3(256), 0, s, h->at<int32_t>(L.off_tflags), L.n_tflags);
+    hipLaunchKernelGGL(build_clear_kernel, dim3(1), dim3(256), 0, s, h->counters(), h->status(),
+                       h->at<int32_t>(L.off_tflags), (int64_t)L.n_tflags);
     const KnmPlan kp = plan_of(h);
     GAP_TRY(dev(launch_plan_tiles(h->offsets, L.NE, L.n_atoms, kp, L.max_tiles, h->status(), s)));
     *a = KnmArgs{};

@@ -44,11 +44,12 @@ struct KnmArgs {
 };
 
 int64_t knm_max_tiles(int64_t N, int64_t n_atoms);
-int64_t knm_plan_chunks(int64_t N);
-// Plan arrays (device): tile_start [max_tiles + 1], n_tiles [1], cfg_list [N],
-// lstart [n_chunks * 2049], lcount [n_chunks] (n_chunks = knm_plan_chunks(N)).
+// Plan arrays (device): tile_start [max_tiles + 1], n_tiles [1], cfg_list [N] followed by
+// the chunks' tile lists (knm_plan_ints(N) int32 together).
+int64_t knm_plan_ints(int64_t N);
 struct KnmPlan {
-    int32_t *tile_start, *n_tiles, *cfg_list, *lstart, *lcount;
+    int32_t *tile_start, *n_tiles, *cfg_list;
+    uint16_t *lists;
 };
 hipError_t launch_plan_tiles(const int64_t *offsets, int64_t N, int64_t n_atoms, const KnmPlan &p, int64_t max_tiles,
                              int32_t *status, hipStream_t s);
