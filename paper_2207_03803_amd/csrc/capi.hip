@@ -14,7 +14,8 @@ using namespace gap;
 namespace {
 
 constexpr int N_STAGES = 10;
-constexpr int N_COUNTERS = 16;  // arrival counters
+constexpr int N_COUNTERS = 64;  // arrival counters: 8 .. 15 single ones, 16 .. the QR panel's
+static_assert(16 + CQ_COUNTERS <= N_COUNTERS, "room for the panel's counters");
 
 enum State { ST_CREATED = 0, ST_BOUND = 1, ST_KNM = 2, ST_BUILT = 3, ST_SOLVED = 4 };
 
@@ -930,6 +931,7 @@ gap_status gap_solve(gap_handle h, const double *y, double *c_out, gap_solve_inf
     w.cq_part = h->at<double>(L.off_cq_part);
     w.cq_G = h->at<double>(L.off_cq_G);
     w.cq_R = h->at<double>(L.off_cq_R);
+    w.cq_counters = h->counters() + 16;
     w.status = h->status();
     double *rhs = h->at<double>(L.off_rhs);
     if (!L.mixed) {

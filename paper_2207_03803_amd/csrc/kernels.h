@@ -84,11 +84,13 @@ struct QrWork {
     double *cq_S;       // CholeskyQR: FP64 scratch panel [QR_NB x cq_ld] (column-major)
     int64_t cq_ld;      // >= m
     double *cq_part;    // [CQ_MAX_CHUNKS * QR_NB * QR_NB] partial Gram matrices
-    double *cq_G;       // [4 * QR_NB * QR_NB] four partial sums of the Gram matrix
-    double *cq_R;       // [4 * QR_NB * QR_NB] R1, R2, R2 R1, U R3 (row-major)
+    double *cq_G;       // [4 * QR_NB * QR_NB] Y_a^T Y_b of a panel pair
+    double *cq_R;       // [4 * QR_NB * QR_NB] R1, R2, R2 R1, U R3 (packed upper triangles)
+    unsigned *cq_counters;  // [CQ_COUNTERS] arrival counters of the panel's sums (zero; left zero)
     int32_t *status;
 };
 constexpr int64_t CQ_MAX_CHUNKS = 256;
+constexpr int CQ_COUNTERS = 20;
 // Shifted CholeskyQR3 panel + Householder reconstruction (same outputs as the TSQR panel).
 void cqr_panel_f64(const QrWork &w, int64_t j0, int pw, double *Tout, hipStream_t s);
 void cqr_panel_f32(const QrWork &w, int64_t j0, int pw, double *Tout, hipStream_t s);
