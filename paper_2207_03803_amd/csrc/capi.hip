@@ -623,7 +623,7 @@ static gap_status launch_kmm_chol(gap_handle h, hipStream_t s)
     GAP_TRY(dev(launch_knm(k, (L.M + KNM_BM - 1) / KNM_BM, s)));
     h->mark_on(1, true, s);
     h->mark_on(2, false, s);
-    GAP_TRY(dev(launch_potrf_upper(h->A() + L.N, L.lda, L.M, h->status(), s)));
+    GAP_TRY(dev(launch_potrf_upper(h->A() + L.N, L.lda, L.M, h->at<double>(L.off_cq_G), h->status(), s)));
     h->mark_on(2, true, s);
     return GAP_OK;
 }

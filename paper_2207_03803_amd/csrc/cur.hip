@@ -464,7 +464,7 @@ hipError_t launch_cur_select(const CurLaunch &c, hipStream_t s)
                        part);
     hipLaunchKernelGGL(cur_gram_sum_kernel, dim3((unsigned)((pairs * CUR_NB * CUR_NB + 255) / 256)), dim3(256), 0, s,
                        part, nch, pairs, nb, d, G);
-    hipError_t e = launch_potrf_upper(G, d, d, &st->status, s);
+    hipError_t e = launch_potrf_upper(G, d, d, part, &st->status, s);
     if (e != hipSuccess)
         return e;
     hipLaunchKernelGGL(cur_trinv_kernel, dim3((unsigned)d), dim3(256), 0, s, G, d, W);

@@ -12,8 +12,9 @@ constexpr int CHOL_NB = 64;
 // In-place upper Cholesky K = U^T U of the n x n matrix at U (column-major,
 // leading dimension ld; only the upper triangle is read, U written there, the
 // strictly lower part of each diagonal block zeroed).  First non-positive
-// pivot -> status DST_ENOTPD.
-hipError_t launch_potrf_upper(double *U, int64_t ld, int64_t n, int32_t *status, hipStream_t s);
+// pivot -> status DST_ENOTPD.  scratch: CHOL_SCRATCH doubles.
+constexpr int64_t CHOL_SCRATCH = 2 * CHOL_NB * CHOL_NB;
+hipError_t launch_potrf_upper(double *U, int64_t ld, int64_t n, double *scratch, int32_t *status, hipStream_t s);
 
 // ----------------------------------------------------- CUR sparse-point selection
 // Leverages of the n rows of X [n x d] (row-major FP64) over its row space, keys

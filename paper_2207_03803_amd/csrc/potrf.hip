@@ -1,199 +1,230 @@
 // Blocked right-looking Cholesky factorisation K = U^T U (U = L^T, upper
 // triangular), in place, FP64 (Sec. Theory: the lower block of A is L_MM^T).
-// Per 64-column step: factor the diagonal block in LDS, solve the block row
-// U_kk^T X = A_kj by forward substitution, then update the trailing upper
-// triangle with an FP64 MFMA product A_ij -= U_ki^T U_kj.
+// Steps of 64 columns go in pairs.  One launch factors a step's diagonal block and solves its
+// block row; the second step of a pair first brings its own tiles up to date with the first
+// one's rows.  One product of depth 128 then applies both to everything below.
 #include "kernels.h"
+#include "small64.h"
 
 namespace gap {
 
 constexpr int CNB = CHOL_NB;
-constexpr int CLD = CNB + 1;
+static_assert(CNB == S64, "block rows of the 64 x 64 helpers");
 
-// Order the LDS accesses of one wave's lanes (no workgroup barrier: one wave).
-DEV void lane_sync()
+struct CholLds {
+    double D[S64][DL];  // the diagonal block, [row][column]
+    double E[S64][DL];  // the previous step's rows under it, [column][p]; then the block row's tile
+    double F[S64][DL];  // the previous step's rows under the tile, [column][p]; then U_kk packed
+    double T[4][16][17];
+    int ok;
+};
+static_assert(PACK <= S64 * DL, "a packed triangle fits a matrix buffer");
+
+// Columns x .. x + 63 (those below n) of the 64 rows from k0 on (rows past kb zero), as
+// M[column - x][row - k0]; 256 threads, consecutive lanes on consecutive rows.
+DEV void chol_load_cols(const double *U, int64_t ld, int64_t k0, int kb, int64_t x, int64_t n, double (*M)[DL])
 {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-}
-
-// Factor the kb x kb diagonal block starting at (k0, k0) on one wave: lane c
-// holds column c of the block in registers (rows and columns past kb padded
-// with the identity), and row j of each step is shared through LDS.  Each
-// element sees the right-looking order: U[j][j] = sqrt(pivot), U[j][c] /=
-// U[j][j], then U[r][c] -= U[j][r] U[j][c].
-__global__ __launch_bounds__(64) void chol_diag_kernel(double *U, int64_t ld, int64_t k0, int kb, int32_t *status)
-{
-    __shared__ double row[CNB];
-    const int c = threadIdx.x;
-    double x[CNB];
-    const double *col = U + (k0 + c) * ld + k0;
-#pragma unroll
-    for (int r = 0; r < CNB; ++r)
-        x[r] = (c < kb) ? ((r <= c) ? col[r] : 0.0) : (r == c ? 1.0 : 0.0);
-#pragma unroll
-    for (int j = 0; j < CNB; ++j) {
-        if (c == j) {
-            double piv = x[j];
-            if (!(piv > 0.0) || !isfinite(piv)) {
-                set_status(status, DST_ENOTPD);  // the first failure is kept
-                piv = 1.0;                       // keep the (discarded) rest finite
-            }
-            x[j] = sqrt(piv);
-            row[j] = x[j];
-        }
-        lane_sync();
-        const double dj = row[j];
-        if (c > j) {
-            x[j] = x[j] / dj;
-            row[c] = x[j];
-        }
-        lane_sync();
-        if (c > j) {
-            const double xj = x[j];
-#pragma unroll
-            for (int r = j + 1; r < CNB; ++r)
-                x[r] -= row[r] * xj;  // rows past c are below the diagonal: never stored
-        }
-        lane_sync();
-    }
-    if (c < kb) {
-        double *out = U + (k0 + c) * ld + k0;
-#pragma unroll
-        for (int r = 0; r < CNB; ++r)
-            if (r < kb)
-                out[r] = (r <= c) ? x[r] : 0.0;
-    }
-}
-
-// Block row: X = U_kk^-T B for the 64-column block `blockIdx.x` right of the
-// diagonal block, one wave per block and one column per lane (each column's
-// forward substitution is independent: no barriers), U_kk staged in LDS.
-__global__ __launch_bounds__(64) void chol_trsm_kernel(double *U, int64_t ld, int64_t k0, int kb, int64_t n)
-{
-    __shared__ double Ukk[CNB * CLD];
-    const int c = threadIdx.x;
-    const int64_t c0 = k0 + kb + (int64_t)blockIdx.x * CNB;
-    const int cw = (int)((n - c0) < CNB ? (n - c0) : CNB);
-    {
-        const double *col = U + (k0 + c) * ld + k0;
-#pragma unroll
-        for (int r = 0; r < CNB; ++r)
-            Ukk[r * CLD + c] = (c < kb && r <= c) ? col[r] : 0.0;
-    }
-    lane_sync();
-    if (c >= cw)
-        return;
-    double x[CNB];
-    double *bc = U + (c0 + c) * ld + k0;
-#pragma unroll
-    for (int r = 0; r < CNB; ++r)
-        x[r] = (r < kb) ? bc[r] : 0.0;
-#pragma unroll
-    for (int i = 0; i < CNB; ++i) {
-        if (i < kb) {
-            x[i] = x[i] / Ukk[i * CLD + i];
-#pragma unroll
-            for (int r = i + 1; r < CNB; ++r)
-                x[r] -= Ukk[i * CLD + r] * x[i];  // U_kk rows past kb are zero
-        }
-    }
-#pragma unroll
-    for (int r = 0; r < CNB; ++r)
-        if (r < kb)
-            bc[r] = x[r];
-}
-using SS = TileShape<128, 128, 16, 2, 2>;
-
-// Trailing update of the upper triangle: A[r][c] -= sum_{p < kb} U[k0+p][r] U[k0+p][c]
-// for k1 <= r <= c < n and r < rlim, one 128 x 128 tile per workgroup.  With
-// rlim = n the tiles are the upper ones of the trailing triangle (enumerated
-// column by column); with rlim < n (a strip of at most 128 rows) they are one
-// row of tiles across the columns.
-__global__ __launch_bounds__(256) void chol_syrk_kernel(double *U, int64_t ld, int64_t k0, int kb, int64_t k1,
-                                                        int64_t rlim, int64_t n)
-{
-    __shared__ double lds[2 * SS::STAGE];
-    const int64_t L = blockIdx.x;
-    int64_t ti = 0, tj = L;
-    if (rlim >= n) {  // linear id -> (ti, tj), ti <= tj
-        tj = (int64_t)((sqrt(8.0 * (double)L + 1.0) - 1.0) * 0.5);
-        while ((tj + 1) * (tj + 2) / 2 <= L)
-            ++tj;
-        while (tj * (tj + 1) / 2 > L)
-            --tj;
-        ti = L - tj * (tj + 1) / 2;
-    }
-    const int64_t r0 = k1 + ti * SS::BM, c0 = k1 + tj * SS::BN;
-
-    // The tile is computed transposed, acc(c, r), so that consecutive lanes
-    // update consecutive rows of the column-major matrix.
-    d4 acc[SS::FM][SS::FN];
-    zero_acc<SS>(acc);
-    const double *P = U + k0;  // element (row x, p) = U[k0 + p][x] at x * ld + p
-    auto fa = [&](int mi, int64_t p) -> double {
-        const int64_t x = c0 + mi;
-        return (x < n && p < kb) ? P[x * ld + p] : 0.0;
-    };
-    auto fb = [&](int ni, int64_t p) -> double {
-        const int64_t x = r0 + ni;
-        return (x < n && p < kb) ? P[x * ld + p] : 0.0;
-    };
-    gemm_tile<SS, true, true>(acc, lds, kb, fa, fb);
-
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int wm = wave / SS::WN, wn = wave % SS::WN;
+    double v[16];
 #pragma unroll
-    for (int i = 0; i < SS::FM; ++i)
+    for (int q = 0; q < 16; ++q) {
+        const int c = wave + 4 * q;
+        v[q] = (x + c < n && lane < kb) ? U[(x + c) * ld + k0 + lane] : 0.0;
+    }
 #pragma unroll
-        for (int j = 0; j < SS::FN; ++j)
+    for (int q = 0; q < 16; ++q)
+        M[wave + 4 * q][lane] = v[q];
+}
+
+// Step k0 (kb <= 64 columns): every workgroup factors the diagonal block for itself, then
+// solves U_kk^T X = B for its 64 columns right of it (one refinement per 16-row block keeps
+// each solve backward stable).  PREV: the 64 rows above (the pair's first step) are first
+// subtracted from the diagonal block and the tile.  Workgroup 0 leaves U_kk in diag
+// ([column][row], 64 x 64): the others still read the block in place, so the pair's
+// trailing update (chol_syrk_kernel) stores it; with no columns to the right it is
+// stored here.  Latency-bound: 24 us, 26 with PREV, where the diagonal block, the block row
+// and the strip update of each step took 35 + 35 + 30 us.
+template <bool PREV>
+__global__ __launch_bounds__(256) void chol_step_kernel(double *U, int64_t ld, int64_t k0, int kb, int64_t n,
+                                                        double *__restrict__ diag, int32_t *status)
+{
+    __shared__ CholLds L;
+    const int t = threadIdx.x, lane = t & 63, wave = t >> 6, g = lane >> 4, r = lane & 15;
+    const int64_t c0 = k0 + kb + (int64_t)blockIdx.x * CNB;  // this workgroup's columns (none: >= n)
+    const bool right = c0 < n;
+    chol_load_cols(U, ld, k0, kb, k0, k0 + kb, L.F);  // the block, transposed
+    if constexpr (PREV)
+        chol_load_cols(U, ld, k0 - CNB, CNB, k0, k0 + kb, L.E);
+    if (t == 0)
+        L.ok = 1;
+    __syncthreads();
+    for (int idx = wave; idx < NBLK; idx += 4) {
+        const int c = blk_col(idx), b = idx - c * (c + 1) / 2;
+        d4 acc;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const int i = 16 * b + g + 4 * e, l = 16 * c + r;
+            acc[e] = (i < kb && l < kb) ? L.F[l][i] : (i == l ? 1.0 : 0.0);
+        }
+        if constexpr (PREV) {
+#pragma unroll
+            for (int k = 0; k < CNB / 4; ++k)
+                acc = mfma16(-L.E[16 * b + r][4 * k + g], L.E[16 * c + r][4 * k + g], acc);
+        }
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            L.D[16 * b + g + 4 * e][16 * c + r] = acc[e];
+    }
+    __syncthreads();
+    // the tile as rows (one per column of the matrix), before the factorisation's chain
+    d4 y[4];
+    if constexpr (PREV) {
+        if (right)
+            chol_load_cols(U, ld, k0 - CNB, CNB, c0, n, L.F);
+        __syncthreads();
+        if (right)
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                y[c] = d4{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+                for (int k = 0; k < CNB / 4; ++k)
+                    y[c] = mfma16(-L.E[16 * c + r][4 * k + g], L.F[16 * wave + r][4 * k + g], y[c]);
+            }
+        __syncthreads();
+    }
+    if (right)
+        chol_load_cols(U, ld, k0, kb, c0, n, L.E);
+    chol64(L.D, &L.ok);
+    if (right)
+#pragma unroll
+        for (int c = 0; c < 4; ++c)
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-                const int64_t c = c0 + acc_row<SS>(wm, i, lane, e);
-                const int64_t r = r0 + acc_col<SS>(wn, j, lane, e);
-                if (r <= c && c < n && r < rlim)
+                const double v = L.E[16 * wave + r][16 * c + 4 * e + g];
+                y[c][e] = PREV ? y[c][e] + v : v;
+            }
+    double *P = &L.F[0][0];
+    pack_upper([&](int i, int j) { return L.D[i][j]; }, P, L.T);
+    if (blockIdx.x == 0) {
+        if (t == 0 && !L.ok)
+            set_status(status, DST_ENOTPD);
+        for (int e = t; e < CNB * CNB; e += 256) {
+            const int i = e & 63, l = e >> 6;
+            if (right)
+                diag[e] = L.D[i][l];
+            else if (i < kb && l < kb)
+                U[(k0 + l) * ld + k0 + i] = L.D[i][l];
+        }
+    }
+    if (!right)
+        return;
+    solve_rows<true>(y, P);
+#pragma unroll
+    for (int c = 0; c < 4; ++c)
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            L.E[16 * wave + r][16 * c + 4 * e + g] = y[c][e];
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < 16; ++q) {
+        const int c = wave + 4 * q;
+        if (c0 + c < n && lane < kb)
+            U[(c0 + c) * ld + k0 + lane] = L.E[c][lane];
+    }
+}
+
+// Trailing update of the upper triangle: A[r][c] -= sum_{p < kb} U[k0+p][r] U[k0+p][c]
+// for k1 <= r <= c < n, one tile per workgroup (enumerated column by column), both operands
+// contiguous along p.  The tile is computed transposed, acc(c, r), so that
+// consecutive lanes update consecutive rows of the column-major matrix.  The first workgroup
+// also stores the nd diagonal blocks that the steps left in diag.
+template <class S>
+__global__ __launch_bounds__(S::NT, S::NT == 512 ? 4 : 2) void chol_syrk_kernel(double *U, int64_t ld, int64_t k0,
+                                                                                int kb, int64_t k1, int64_t n,
+                                                                                const double *__restrict__ diag, int nd)
+{
+    __shared__ __align__(16) d2 lds[2 * S::UNITS];
+    static_assert(S::BM == S::BN, "square tiles");
+    const int64_t L = blockIdx.x;
+    int64_t tj = (int64_t)((sqrt(8.0 * (double)L + 1.0) - 1.0) * 0.5);
+    while ((tj + 1) * (tj + 2) / 2 <= L)
+        ++tj;
+    while (tj * (tj + 1) / 2 > L)
+        --tj;
+    const int64_t ti = L - tj * (tj + 1) / 2;
+    const int64_t r0 = k1 + ti * S::BM, c0 = k1 + tj * S::BN;
+    if (L == 0)
+        for (int e = threadIdx.x; e < nd * CNB * CNB; e += S::NT) {
+            const int b = e / (CNB * CNB), i = e & 63, l = (e >> 6) & 63;
+            U[(k0 + b * CNB + l) * ld + k0 + b * CNB + i] = diag[e];
+        }
+    const double *src[S::LPT];
+#pragma unroll
+    for (int i = 0; i < S::LPT; ++i) {
+        const int x = S::unit_row(i);
+        int64_t col = x < S::BM ? c0 + x : r0 + x - S::BM;
+        col = col < n ? col : n - 1;  // computed, not stored
+        src[i] = U + col * ld + k0 + S::unit_k(i);
+    }
+    d4 acc[S::FM][S::FN];
+    ktile_zero<S>(acc);
+    ktile_product<S>(acc, lds, src, kb, rows_aligned16(U + k0, ld));
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int wm = wave / S::WN, wn = wave % S::WN;
+#pragma unroll
+    for (int i = 0; i < S::FM; ++i)
+#pragma unroll
+        for (int j = 0; j < S::FN; ++j)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const int64_t c = c0 + acc_row<S>(wm, i, lane, e);
+                const int64_t r = r0 + acc_col<S>(wn, j, lane, e);
+                if (r <= c && c < n)
                     U[c * ld + r] -= acc[i][j][e];
             }
 }
 
-static void syrk(double *U, int64_t ld, int64_t k0, int kb, int64_t k1, int64_t rlim, int64_t n, hipStream_t s)
+// The diagonal block that a step with no trailing update after it left in diag.
+__global__ __launch_bounds__(256) void chol_store_kernel(double *U, int64_t ld, int64_t k0, const double *diag)
 {
-    const int64_t nc = (n - k1 + SS::BN - 1) / SS::BN;
-    const int64_t tiles = (rlim >= n) ? nc * (nc + 1) / 2 : nc;
-    hipLaunchKernelGGL(chol_syrk_kernel, dim3((unsigned)tiles), dim3(256), 0, s, U, ld, k0, kb, k1, rlim, n);
+    for (int e = threadIdx.x; e < CNB * CNB; e += 256)
+        U[(k0 + (e >> 6)) * ld + k0 + (e & 63)] = diag[e];
 }
 
-// Steps are taken in pairs: block k's rows update only block k + 1's rows
-// (a thin strip), block k + 1 is factored, then one trailing update of depth
-// 128 applies both blocks to everything below (half the trailing passes, each
-// twice as deep).
-hipError_t launch_potrf_upper(double *U, int64_t ld, int64_t n, int32_t *status, hipStream_t s)
+// diag: 2 x 64 x 64 doubles of scratch.
+hipError_t launch_potrf_upper(double *U, int64_t ld, int64_t n, double *diag, int32_t *status, hipStream_t s)
 {
-    auto factor_row = [&](int64_t k0, int kb) {
-        hipLaunchKernelGGL(chol_diag_kernel, dim3(1), dim3(64), 0, s, U, ld, k0, kb, status);
+    using SL = KTile<double, 128, 128, 4, 2, 4>;
+    using SS = KTile<double, 64, 64, 8, 2, 2>;
+    auto blocks = [](int64_t x, int64_t b) { return (x + b - 1) / b; };
+    auto step = [&](int64_t k0, int kb, bool prev, double *dg) {
         const int64_t rest = n - k0 - kb;
-        if (rest > 0)
-            hipLaunchKernelGGL(chol_trsm_kernel, dim3((unsigned)((rest + CNB - 1) / CNB)), dim3(64), 0, s, U, ld, k0,
-                               kb, n);
+        const dim3 grid((unsigned)(rest > 0 ? blocks(rest, CNB) : 1));
+        if (prev)
+            hipLaunchKernelGGL(chol_step_kernel<true>, grid, dim3(256), 0, s, U, ld, k0, kb, n, dg, status);
+        else
+            hipLaunchKernelGGL(chol_step_kernel<false>, grid, dim3(256), 0, s, U, ld, k0, kb, n, dg, status);
         return rest;
     };
-    int64_t k0 = 0;
-    while (k0 < n) {
+    for (int64_t k0 = 0; k0 < n; k0 += 2 * CNB) {
         const int kb = (int)((n - k0) < CNB ? (n - k0) : CNB);
-        const int64_t rest = factor_row(k0, kb);
-        if (rest <= 0)
+        if (step(k0, kb, false, diag) <= 0)
             break;
-        const int64_t k1 = k0 + kb;
-        if (rest <= CNB) {  // one block left
-            syrk(U, ld, k0, kb, k1, n, n, s);
-            k0 = k1;
-            continue;
+        const int64_t k1 = k0 + CNB;
+        const int kb1 = (int)((n - k1) < CNB ? (n - k1) : CNB);
+        const int64_t rest = step(k1, kb1, true, diag + CNB * CNB);
+        if (rest <= 0) {  // no trailing update: the first step's block is still in diag
+            hipLaunchKernelGGL(chol_store_kernel, dim3(1), dim3(256), 0, s, U, ld, k0, (const double *)diag);
+            break;
         }
-        syrk(U, ld, k0, kb, k1, k1 + CNB, n, s);  // block k's rows into block k + 1's rows
-        factor_row(k1, CNB);
-        syrk(U, ld, k0, kb + CNB, k1 + CNB, n, n, s);  // both blocks into the rest
-        k0 = k1 + CNB;
+        // 64 x 64 tiles where large ones would leave CUs without one
+        const int64_t nl = blocks(rest, SL::BM), ns = blocks(rest, SS::BM);
+        if (nl * (nl + 1) / 2 >= 256)
+            hipLaunchKernelGGL(chol_syrk_kernel<SL>, dim3((unsigned)(nl * (nl + 1) / 2)), dim3(SL::NT), 0, s, U, ld, k0,
+                               2 * CNB, k1 + CNB, n, (const double *)diag, 2);
+        else
+            hipLaunchKernelGGL(chol_syrk_kernel<SS>, dim3((unsigned)(ns * (ns + 1) / 2)), dim3(SS::NT), 0, s, U, ld, k0,
+                               2 * CNB, k1 + CNB, n, (const double *)diag, 2);
     }
     return hipGetLastError();
 }
