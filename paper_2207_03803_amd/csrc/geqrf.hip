@@ -20,6 +20,7 @@
 // beta = -sign(alpha) ||(alpha, x)||, tau = (beta - alpha)/beta,
 // v(1:) = x / (alpha - beta); tau = 0 when x is exactly zero.
 #include "kernels.h"
+#include "small64.h"
 
 namespace gap {
 
@@ -373,21 +374,6 @@ __global__ __launch_bounds__(256) void tsqr_trsm_kernel(QrWork w, int64_t j0, in
             qmat<T>(w)[(j0 + c) * w.lda + r] = (T)y[c];
 }
 
-// Householder vectors of the column block at (j0, j0), pw <= 2 * QR_NB wide:
-// unit lower trapezoidal.
-template <class T>
-DEV T ypanel(const T *A, int64_t lda, int64_t m, int64_t j0, int pw, int64_t r, int p)
-{
-    if (p >= pw || r >= m)
-        return T(0);
-    const int64_t d = r - (j0 + p);
-    if (d < 0)
-        return T(0);
-    if (d == 0)
-        return T(1);
-    return A[(j0 + p) * lda + r];
-}
-
 // Tile of a trailing-update product: logical tiles are numbered row block by
 // row block (the column tiles of one row block consecutive), and consecutive
 // logical tiles run on the same XCD, so that the row block's Y tile stays in
@@ -403,193 +389,218 @@ DEV bool update_tile(int64_t n_rb, int64_t n_cb, int64_t &rb, int64_t &cb)
     return true;
 }
 
-// Row-block split of a trailing update: PART 0 every row block, 1 the interior
-// ones (n_head .. n_rb - 2: full rows, below Y's unit triangle, loaded without
-// checks), 2 the edge ones (the n_head row blocks that meet Y's triangle, and
-// n_rb - 1).
-template <int PART>
-DEV bool update_tile_part(int64_t n_rb, int64_t n_cb, int n_head, int64_t &rb, int64_t &cb)
-{
-    if constexpr (PART == 1) {
-        if (!update_tile(n_rb - n_head - 1, n_cb, rb, cb))
-            return false;
-        rb += n_head;
-    } else if constexpr (PART == 2) {
-        if (!update_tile(n_head + 1, n_cb, rb, cb))
-            return false;
-        if (rb == n_head)
-            rb = n_rb - 1;
-    } else {
-        if (!update_tile(n_rb, n_cb, rb, cb))
-            return false;
-    }
-    return true;
-}
-
 constexpr int OB = 2 * NB;                 // a TSQR panel pair (one factor_block)
 constexpr int OB2 = 2 * OB;                // outer block of the trailing update: two panel pairs
-// Both on 16x16x4 MFMA.  The update's 64 x 128 tiles with 8-deep slices (122
-// VGPRs, up to four waves per SIMD) measured 1-2 % faster than 128 x 128 x 16
-// tiles at two waves per SIMD.
-using WS = TileShape<OB, 128, 16, 2, 2, true>;  // P = Y^T C over a row chunk
-using US = TileShape<64, 128, 8, 2, 2, true>;   // C^T -= W^T Y^T (rows of C along the MFMA N axis)
+
+// Tiles of the two products.  The large ones run at 4 waves per SIMD; the small ones spread
+// the narrow products of the panel chain (64 or 128 columns) and short matrices over more
+// workgroups (see wpart_small, update_small).
+template <class T>
+struct QrTiles;
+template <>
+struct QrTiles<double> {
+    using WL = KTile<double, OB, 128, 4, 2, 4>;  // P = Y^T C over a row chunk
+    using WS = KTile<double, 64, 64, 8, 2, 2>;
+    using UL = MTile<double, 128, 128, 8, 2, 4>;  // C^T -= W^T Y^T (rows of C along the MFMA N axis)
+    using US = MTile<double, 64, 64, 8, 2, 2>;
+};
+template <>
+struct QrTiles<float> {
+    using WL = KTile<float, OB, 128, 4, 2, 2>;
+    using WS = KTile<float, 64, 64, 4, 2, 2>;
+    using UL = MTile<float, 128, 128, 8, 2, 2>;
+    using US = MTile<float, 64, 64, 8, 1, 1>;
+};
+
+// Element of row r of a unit lower trapezoid's column whose diagonal row is diag (PLAIN: a
+// column that is taken as it is).
+constexpr int64_t PLAIN = INT64_MIN;
+template <class T>
+DEV T unit_lower(T v, int64_t r, int64_t diag)
+{
+    return r > diag ? v : (r == diag ? T(1) : T(0));
+}
 
 // P[ch][p][q] = sum over the chunk's rows r of Y[r][p] C[r][q].  Y is the
 // block at (j0, j0) of width pw; C is either columns c0 .. c0+nt of A
 // (ymode = 0) or the unit lower trapezoidal block at (c0, c0) of width nt
-// (ymode = 1, used for Y_A^T Y_B).  Rows r0 .. m.
-__global__ __launch_bounds__(256, 2) void qr_wpart_kernel(QrWork w, int64_t j0, int pw, int64_t c0, int64_t nt,
-                                                          int ymode, int64_t r0, int64_t chunk)
+// (ymode = 1, used for Y_A^T Y_B with rows below Y_A's triangle).  Rows r0 .. m.  Both operands
+// are contiguous along the summed rows and go straight to LDS, except in the stages that
+// meet a unit triangle and a ragged last one.
+template <class S>
+__global__ __launch_bounds__(S::NT, sizeof(typename S::elem) == 8 && S::NT == 512 ? 4 : 3) void qr_wpart_kernel(
+    QrWork w, int64_t j0, int pw, int64_t c0, int64_t nt, int ymode, int64_t r0, int64_t chunk)
 {
-    __shared__ double lds[2 * WS::STAGE];
-    // blockIdx.z: which 128-column half of a block of up to 256 (rows OB z .. of P)
-    const int prow0 = OB * (int)blockIdx.z;
+    using T = typename S::elem;
+    __shared__ __align__(16) typename S::unit lds[2 * S::UNITS];
+    // blockIdx.z: rows S::BM z .. of P
+    const int prow0 = S::BM * (int)blockIdx.z;
     j0 += prow0;
-    pw = (pw - prow0) < OB ? (pw - prow0) : OB;
+    pw = (pw - prow0) < S::BM ? (pw - prow0) : S::BM;
     if (pw <= 0)
         return;
     const int64_t ch = blockIdx.y;
-    const int64_t q0 = (int64_t)blockIdx.x * WS::BN;
+    const int64_t q0 = (int64_t)blockIdx.x * S::BN;
     const int64_t rlo = r0 + ch * chunk;
     int64_t rhi = rlo + chunk;
     if (rhi > w.m)
         rhi = w.m;
     if (rlo >= rhi)
         return;
-    d4 acc[WS::FM][WS::FN];
-    zero_acc<WS>(acc);
-    const double *A = w.A;
-    const int64_t lda = w.lda, m = w.m;
-    const bool masked = rlo < j0 + pw;  // the chunk meets Y's unit upper triangle
-    constexpr int VA = WS::BM * WS::BK / WS::NT, VB = WS::BN * WS::BK / WS::NT;
-    auto fa = [&](int p, int64_t k, double (&v)[VA]) {
-        const int64_t r = rlo + k;
-        if (p >= pw) {
+    const T *A = qmat<T>(w);
+    const int64_t lda = w.lda;
+    // rows of P past pw and columns past nt repeat the last one and are not stored
+    const T *src[S::LPT];
 #pragma unroll
-            for (int e = 0; e < VA; ++e)
-                v[e] = 0.0;
-        } else if (!masked && r + VA <= rhi) {
-            load_run(A + (j0 + p) * lda + r, v);
-        } else {
-#pragma unroll
-            for (int e = 0; e < VA; ++e)
-                v[e] = (r + e < rhi) ? ypanel(A, lda, m, j0, pw, r + e, p) : 0.0;
-        }
-    };
-    auto fb = [&](int qi, int64_t k, double (&v)[VB]) {
-        const int64_t r = rlo + k, q = q0 + qi;
-        if (q >= nt) {
-#pragma unroll
-            for (int e = 0; e < VB; ++e)
-                v[e] = 0.0;
-        } else if (ymode) {
-#pragma unroll
-            for (int e = 0; e < VB; ++e)
-                v[e] = (r + e < rhi) ? ypanel(A, lda, m, c0, (int)nt, r + e, (int)q) : 0.0;
-        } else {
-            const double *col = A + (c0 + q) * lda + r;
-            if (r + VB <= rhi) {
-                load_run(col, v);
-            } else {
-#pragma unroll
-                for (int e = 0; e < VB; ++e)
-                    v[e] = (r + e < rhi) ? col[e] : 0.0;
-            }
-        }
-    };
-    if (!masked && !ymode) {
-        // Full slices without checks: a P row past pw reads row pw - 1 of Y and a
-        // column past nt column nt - 1 of C, stored as zeros.
-        const int64_t colq_max = nt - 1;
-        auto faf = [&](int p, int64_t k, double (&v)[VA]) {
-            load_run(A + (j0 + (p < pw ? p : pw - 1)) * lda + rlo + k, v);
-            return p >= pw;
-        };
-        auto fbf = [&](int qi, int64_t k, double (&v)[VB]) {
-            const int64_t q = q0 + qi;
-            load_run(A + (c0 + (q < nt ? q : colq_max)) * lda + rlo + k, v);
-            return q >= nt;
-        };
-        gemm_tile_runs_ft<WS, true, true>(acc, lds, rhi - rlo, faf, fbf, fa, fb);
-    } else {
-        gemm_tile_runs<WS, true, true>(acc, lds, rhi - rlo, fa, fb);
+    for (int i = 0; i < S::LPT; ++i) {
+        const int r = S::unit_row(i);
+        const int64_t q = q0 + r - S::BM;
+        const int64_t col = r < S::BM ? j0 + (r < pw ? r : pw - 1) : c0 + (q < nt ? q : nt - 1);
+        src[i] = A + col * lda + rlo + S::unit_k(i);
     }
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int wm = wave / WS::WN, wn = wave % WS::WN;
+    const int64_t tri_end = ymode ? c0 + nt : j0 + pw;  // rows before it may meet the triangle
+    const int len = (int)(rhi - rlo), nk = (len + S::BK - 1) / S::BK;
+    const int km = tri_end > rlo ? (int)(tri_end - rlo) : 0;
+    typename S::acc4 acc[S::FM][S::FN];
+    ktile_zero<S>(acc);
+    ktile_product_masked<S>(acc, lds, src, nk, (km + S::BK - 1) / S::BK, len / S::BK, [&](int kt, int i) {
+        // (reads stay inside the column: rlo and BK are multiples of 16, lda of 64)
+        typename S::unit v;
+        __builtin_memcpy(&v, __builtin_assume_aligned(src[i] + (int64_t)kt * S::BK, 16), 16);
+        const int r = S::unit_row(i);
+        const int64_t row = rlo + kt * S::BK + S::unit_k(i);
+        const int64_t diag = r < S::BM ? (ymode ? PLAIN : j0 + r) : (ymode ? c0 + q0 + r - S::BM : PLAIN);
+#pragma unroll
+        for (int e = 0; e < S::V; ++e)
+            v[e] = row + e < rhi ? unit_lower<T>(v[e], row + e, diag) : T(0);
+        return v;
+    });
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, g = lane >> 4, rl = lane & 15;
+    const int wm = wave / S::WN, wn = wave % S::WN;
     double *P = w.wpart + (ch * OB2 + prow0) * w.wp_ld;
 #pragma unroll
-    for (int i = 0; i < WS::FM; ++i)
+    for (int i = 0; i < S::FM; ++i)
 #pragma unroll
-        for (int jj = 0; jj < WS::FN; ++jj)
+        for (int j = 0; j < S::FN; ++j)
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-                const int p = acc_row<WS>(wm, i, lane, e);
-                const int64_t q = q0 + acc_col<WS>(wn, jj, lane, e);
+                const int p = wm * S::TM + 16 * i + Unit<T>::acc_m(g, e);
+                const int64_t q = q0 + wn * S::TN + 16 * j + rl;
                 if (p < pw && q < nt)
-                    P[p * w.wp_ld + q] = acc[i][jj][e];
+                    P[p * w.wp_ld + q] = (double)acc[i][j][e];
             }
 }
 
-// W[p][q] = sum_{s <= p} T[s][p] sum_ch P[ch][s][q] (T upper triangular,
-// row-major with leading dimension tld); 64 columns per workgroup, thread
-// (q, part) handles panel rows p = part, part + 4, ...  The chunk partials
-// are summed in a fixed order (chunks ch = 0, 2, ... and 1, 3, ... then the
-// two sums); T is staged in LDS as its packed upper triangle.
+// W = T^T P of a block of one or two panel pairs a | b, from the chunk partials of P = Y^T C:
+// W_a = T_a^T P_a, and with pair b W_b = T_b^T (P_b - H^T P_a) (see the note on the blocks
+// below).  A workgroup takes 16 columns: it sums their chunk partials into LDS (even chunks,
+// odd chunks, then the two sums), and its four waves form the products on MFMA, the factors'
+// operands read straight from L2.  One launch instead of three; 64-column workgroups of
+// scalar sums took 41 us for the narrow updates of the panel chain, this 11-13 us.
+struct WArgs {
+    const double *Ta, *Tb, *H;  // row-major, T upper triangular with zeros below
+    int tld, pwa, pwb;          // T_a's leading dimension (T_b and H: OB); pair widths
+    int64_t nch, nt;
+};
 template <class TW>
-__global__ __launch_bounds__(256) void qr_wred_kernel(QrWork w, const double *__restrict__ T, int tld, int pw,
-                                                      int64_t nch, int64_t nt, TW *__restrict__ Wout, int prow0)
+__global__ __launch_bounds__(256) void qr_w_kernel(QrWork w, WArgs a, TW *__restrict__ W)
 {
-    __shared__ double Pm[OB][64 + 1];
-    __shared__ double Tt[OB * (OB + 1) / 2];  // column p at p (p + 1) / 2 holds T[0..p][p]
-    const int t = threadIdx.x;
-    const int ql = t & 63, part = t >> 6;
-    const int64_t q = (int64_t)blockIdx.x * 64 + ql;
+    __shared__ double Ps[OB2][16];
+    const int t = threadIdx.x, lane = t & 63, wave = t >> 6, g = lane >> 4, r = lane & 15;
+    const int64_t q0 = (int64_t)blockIdx.x * 16;
     {
-        double tv[OB * OB / 256];
+        const int ql = t & 15;
+        const int64_t q = q0 + ql, step = (int64_t)OB2 * w.wp_ld;
+        const int halves = a.pwb > 0 ? 2 : 1;
+        for (int h = 0; h < halves; ++h)
 #pragma unroll
-        for (int u = 0; u < OB * OB / 256; ++u) {
-            const int idx = t + 256 * u, r = idx / OB, p = idx % OB;
-            tv[u] = (r <= p && p < pw) ? T[r * tld + p] : 0.0;
-        }
-#pragma unroll
-        for (int u = 0; u < OB * OB / 256; ++u) {
-            const int idx = t + 256 * u, r = idx / OB, p = idx % OB;
-            if (r <= p)
-                Tt[p * (p + 1) / 2 + r] = tv[u];
-        }
-    }
-    for (int p = part; p < pw; p += 4) {
-        double s0 = 0.0, s1 = 0.0;
-        if (q < nt) {
-            const double *src = w.wpart + (prow0 + p) * w.wp_ld + q;
-            const int64_t step = (int64_t)OB2 * w.wp_ld;
-            int64_t ch = 0;
-            for (; ch + 1 < nch; ch += 2) {
-                s0 += src[ch * step];
-                s1 += src[(ch + 1) * step];
+            for (int u = 0; u < OB / 16; ++u) {
+                const int p = (t >> 4) + 16 * u;
+                double s0 = 0.0, s1 = 0.0;
+                if (q < a.nt && p < (h ? a.pwb : a.pwa)) {
+                    const double *src = w.wpart + (h * OB + p) * w.wp_ld + q;
+                    int64_t ch = 0;
+                    for (; ch + 1 < a.nch; ch += 2) {
+                        s0 += src[ch * step];
+                        s1 += src[(ch + 1) * step];
+                    }
+                    if (ch < a.nch)
+                        s0 += src[ch * step];
+                }
+                Ps[h * OB + p][ql] = s0 + s1;
             }
-            if (ch < nch)
-                s0 += src[ch * step];
-        }
-        Pm[p][ql] = s0 + s1;
     }
     __syncthreads();
-    if (q >= nt)
+    // rows 16 mb .. of T^T P (T upper triangular: terms s <= p), P rows from LDS row base
+    auto tri = [&](const double *T, int ld, int mb, int base, int pw) {
+        d4 acc = d4{0.0, 0.0, 0.0, 0.0};
+        for (int sb = 0; sb <= mb; ++sb) {
+            double av[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const int sr = 16 * sb + 4 * e + g, p = 16 * mb + r;
+                av[e] = (sr < pw && p < pw) ? T[sr * ld + p] : 0.0;
+            }
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                acc = Unit<double>::mfma(av[e], Ps[base + 16 * sb + 4 * e + g][r], acc);
+        }
+        return acc;
+    };
+    auto put = [&](int prow, int pw, int mb, const d4 &acc) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const int p = 16 * mb + g + 4 * e;
+            if (p < pw && q0 + r < a.nt)
+                W[(prow + p) * w.ldw + q0 + r] = (TW)acc[e];
+        }
+    };
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {  // block rows wave and 7 - wave: nine steps per wave
+        const int mb = q ? 7 - wave : wave;
+        if (16 * mb < a.pwa)
+            put(0, a.pwa, mb, tri(a.Ta, a.tld, mb, 0, a.pwa));
+    }
+    if (a.pwb <= 0)
         return;
-    for (int p = part; p < pw; p += 4) {
-        const double *tc = Tt + p * (p + 1) / 2;
-        double s = 0.0;
-        for (int r = 0; r <= p; ++r)
-            s += tc[r] * Pm[r][ql];
-        Wout[(prow0 + p) * w.ldw + q] = (TW)s;
+    // P_b -= H^T P_a
+    d4 pb[2];
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+        const int mb = wave + 4 * q;
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            pb[q][e] = Ps[OB + 16 * mb + g + 4 * e][r];
+        if (16 * mb < a.pwb)
+            for (int sb = 0; sb < OB / 16; ++sb) {
+                double av[4];
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    av[e] = a.H[(16 * sb + 4 * e + g) * OB + 16 * mb + r];  // zeros past pwa and pwb
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    pb[q] = Unit<double>::mfma(-av[e], Ps[16 * sb + 4 * e + g][r], pb[q]);
+            }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < 2; ++q)
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            Ps[OB + 16 * (wave + 4 * q) + g + 4 * e][r] = pb[q][e];
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+        const int mb = q ? 7 - wave : wave;
+        if (16 * mb < a.pwb)
+            put(OB, a.pwb, mb, tri(a.Tb, OB, mb, OB, a.pwb));
     }
 }
 
 // Sum of the split-K partials over the row chunks into chunk 0's slot, one
-// (p, q) element per thread (qr_wred_kernel's fixed order: even chunks, odd
-// chunks, then the two sums).  qr_wred_kernel then reads a single chunk: its
-// own reduction runs on only ceil(nt / 64) workgroups, two for the next
-// block's columns.
+// (p, q) element per thread (even chunks, odd chunks, then the two sums), for many
+// chunks: qr_w_kernel then reads a single one (its own sums run on only
+// ceil(nt / 16) workgroups).
 __global__ __launch_bounds__(256) void qr_psum_kernel(QrWork w, int pw, int64_t nch, int64_t nt)
 {
     const int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x;
@@ -612,7 +623,7 @@ __global__ __launch_bounds__(256) void qr_psum_kernel(QrWork w, int pw, int64_t 
 
 // G = Y_A^T Y_B from the chunk partials (one entry per thread: ld x ld
 // entries, rows p < ld of the partials, columns q < pwb, G row-major with leading
-// dimension ld; chunks summed in the same fixed order as qr_wred_kernel).
+// dimension ld; chunks summed in the same fixed order as qr_psum_kernel).
 __global__ __launch_bounds__(256) void qr_gsum_kernel(QrWork w, int pwb, int64_t nch, double *__restrict__ G, int ld)
 {
     const int e = blockIdx.x * 256 + threadIdx.x;
@@ -635,54 +646,49 @@ __global__ __launch_bounds__(256) void qr_gsum_kernel(QrWork w, int pwb, int64_t
 }
 
 // Combined compact-WY factor of two consecutive panels A | B:
-// T = [[T_A, -T_A G T_B], [0, T_B]] with G = Y_A^T Y_B (summed by qr_gsum_kernel).
+// T = [[T_A, -T_A G T_B], [0, T_B]] with G = Y_A^T Y_B (summed by qr_gsum_kernel).  The two
+// products run on MFMA, a wave per 16 rows (67 -> 25 us).
 __global__ __launch_bounds__(256) void qr_tcombine_kernel(QrWork w, const double *__restrict__ Gs,
                                                          double *__restrict__ Tout)
 {
-    __shared__ double TA[NB][NB + 1];
-    __shared__ double TB[NB][NB + 1];
-    __shared__ double G[NB][NB + 1];
-    __shared__ double X[NB][NB + 1];
-    const int t = threadIdx.x;
+    __shared__ double G[NB][DL], X[NB][DL];
+    const int t = threadIdx.x, lane = t & 63, wave = t >> 6, g = lane >> 4, r = lane & 15;
     const double *Ta = w.Tin, *Tb = w.Tin + NB * NB;
-    {
-        double a[16], b[16], g[16];
-#pragma unroll
-        for (int u = 0; u < 16; ++u) {
-            a[u] = Ta[t + 256 * u];
-            b[u] = Tb[t + 256 * u];
-            g[u] = Gs[t + 256 * u];
-        }
-#pragma unroll
-        for (int u = 0; u < 16; ++u) {
-            const int idx = t + 256 * u, r = idx / NB, c = idx % NB;
-            TA[r][c] = a[u];
-            TB[r][c] = b[u];
-            G[r][c] = g[u];
-        }
-    }
+    for (int idx = t; idx < NB * NB; idx += 256)
+        G[idx / NB][idx % NB] = Gs[idx];
     __syncthreads();
-    for (int idx = t; idx < NB * NB; idx += 256) {  // X = G T_B
-        const int r = idx / NB, c = idx % NB;
-        double v = 0.0;
-        for (int k = 0; k <= c; ++k)
-            v += G[r][k] * TB[k][c];
-        X[r][c] = v;
+    d4 acc[4];
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {  // X = G T_B
+        acc[c] = d4{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+        for (int k = 0; k < 4 * (c + 1); ++k)
+            acc[c] = mfma16(G[16 * wave + r][4 * k + g], Tb[(4 * k + g) * NB + 16 * c + r], acc[c]);
     }
+#pragma unroll
+    for (int c = 0; c < 4; ++c)
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            X[16 * wave + g + 4 * e][16 * c + r] = acc[c][e];
     __syncthreads();
+    for (int idx = t; idx < NB * NB; idx += 256)
+        G[idx / NB][idx % NB] = Ta[idx];
     for (int idx = t; idx < OB * OB; idx += 256) {
-        const int r = idx / OB, c = idx % OB;
-        double v = 0.0;
-        if (r < NB && c < NB) {
-            v = TA[r][c];
-        } else if (r >= NB && c >= NB) {
-            v = TB[r - NB][c - NB];
-        } else if (r < NB && c >= NB) {  // -T_A X
-            const int cc = c - NB;
-            for (int k = r; k < NB; ++k)
-                v -= TA[r][k] * X[k][cc];
-        }
-        Tout[idx] = v;
+        const int i = idx / OB, c = idx % OB;
+        if (c < NB)
+            Tout[idx] = i < NB ? Ta[i * NB + c] : 0.0;
+        else if (i >= NB)
+            Tout[idx] = Tb[(i - NB) * NB + c - NB];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {  // -T_A X (T_A's zeros below its diagonal included)
+        acc[c] = d4{0.0, 0.0, 0.0, 0.0};
+        for (int k = 4 * wave; k < NB / 4; ++k)
+            acc[c] = mfma16(-G[16 * wave + r][4 * k + g], X[4 * k + g][16 * c + r], acc[c]);
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            Tout[(16 * wave + g + 4 * e) * OB + NB + 16 * c + r] = acc[c][e];
     }
 }
 
@@ -694,60 +700,24 @@ __global__ __launch_bounds__(256) void qr_tcombine_kernel(QrWork w, const double
 // 128-column reduction, and the update C -= Y W runs once with depth 256.
 // ---------------------------------------------------------------------------
 
-// H = T_a G (T_a upper triangular pwa x pwa, row-major ld tld; G and H
-// row-major, leading dimension OB; columns q < pwb).  Grid OB: workgroup i
-// forms row i, one column per thread.
-__global__ __launch_bounds__(OB) void qr_hmat_kernel(const double *__restrict__ Ta, int tld, int pwa,
-                                                     const double *__restrict__ G, int pwb, double *__restrict__ H)
+// H = T_a G (T_a upper triangular pwa x pwa, row-major ld tld, zeros below; G and H row-major,
+// leading dimension OB; zeros past pwa and pwb): one 16 x 16 block per wave, 16 workgroups.
+__global__ __launch_bounds__(256) void qr_hmat_kernel(const double *__restrict__ Ta, int tld, int pwa,
+                                                      const double *__restrict__ G, int pwb, double *__restrict__ H)
 {
-    const int i = blockIdx.x, j = threadIdx.x;
-    double v = 0.0;
-    if (i < pwa && j < pwb)
-        for (int k = i; k < pwa; ++k)
-            v += Ta[i * tld + k] * G[k * OB + j];
-    H[i * OB + j] = v;
-}
-
-// P_b -= H^T P_a on the summed partials (chunk 0): P rows OB + p, p < pwb, columns
-// q < nt.  Workgroup (x, y) takes 64 columns and the 32 rows p of quarter y, with
-// P_a (rows s < pwa) and H's 32 columns staged in LDS; thread (q, part) forms
-// rows p = 32 y + 8 part .. + 7.
-constexpr int PC_ROWS = 32;
-__global__ __launch_bounds__(256) void qr_pcorr_kernel(QrWork w, const double *__restrict__ H, int pwa, int pwb,
-                                                       int64_t nt)
-{
-    __shared__ double Pa[OB][64];
-    __shared__ double Hs[OB][PC_ROWS];
-    const int t = threadIdx.x, ql = t & 63, part = t >> 6;
-    const int p0 = PC_ROWS * (int)blockIdx.y;
-    if (p0 >= pwb)
-        return;
-    const int64_t q = (int64_t)blockIdx.x * 64 + ql;
-    for (int sr = part; sr < OB; sr += 4)
-        Pa[sr][ql] = (sr < pwa && q < nt) ? w.wpart[sr * w.wp_ld + q] : 0.0;
-    for (int e = t; e < OB * PC_ROWS; e += 256) {
-        const int sr = e / PC_ROWS, pp = e % PC_ROWS;
-        Hs[sr][pp] = sr < pwa ? H[sr * OB + p0 + pp] : 0.0;
-    }
-    __syncthreads();
-    if (q >= nt)
-        return;
-    double acc[8];
-#pragma unroll
-    for (int u = 0; u < 8; ++u)
-        acc[u] = 0.0;
-    for (int sr = 0; sr < pwa; ++sr) {
-        const double a = Pa[sr][ql];
-#pragma unroll
-        for (int u = 0; u < 8; ++u)
-            acc[u] += Hs[sr][8 * part + u] * a;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, g = lane >> 4, r = lane & 15;
+    const int bi = blockIdx.x >> 1, bj = 4 * (blockIdx.x & 1) + wave;
+    d4 acc = d4{0.0, 0.0, 0.0, 0.0};
+    const int i = 16 * bi + r, j = 16 * bj + r;
+    for (int k0 = 16 * bi; k0 < pwa; k0 += 4) {
+        const int k = k0 + g;
+        const double a = (i < pwa && k < pwa) ? Ta[i * tld + k] : 0.0;
+        const double b = (k < pwa && j < pwb) ? G[k * OB + j] : 0.0;
+        acc = mfma16(a, b, acc);
     }
 #pragma unroll
-    for (int u = 0; u < 8; ++u) {
-        const int p = p0 + 8 * part + u;
-        if (p < pwb)
-            w.wpart[(OB + p) * w.wp_ld + q] -= acc[u];
-    }
+    for (int e = 0; e < 4; ++e)
+        H[(16 * bi + g + 4 * e) * OB + j] = acc[e];
 }
 
 // Copy a pw x pw row-major T (leading dimension sld) into dst (leading dimension OB).
@@ -761,253 +731,105 @@ __global__ __launch_bounds__(256) void qr_tcopy_kernel(const double *__restrict_
 }
 
 // C[r][q] -= sum_p Y[r][p] W[p][q] for rows j0.. and columns c0 .. c0+nt; the
-// tile is computed transposed so that consecutive lanes write consecutive rows.
-// The accumulators start from the C tile (its loads in flight with the first
-// operand slices) and take -W, so the epilogue is a plain store.
-template <int PART>
-__global__ __launch_bounds__(256, 3) void qr_update_kernel(QrWork w, int64_t j0, int pw, int64_t c0, int64_t nt,
-                                                          int n_head)
+// tile is computed transposed so that consecutive lanes own consecutive rows.
+// The accumulators start from -C (its loads in flight with the first
+// operand slices), so the epilogue is a plain store.  Y and W go straight to LDS, except
+// where a row block meets Y's unit triangle and in a ragged last slice.
+template <class S>
+__global__ __launch_bounds__(S::NT, sizeof(typename S::elem) == 8 && S::NT == 512 ? 4 : 3) void qr_update_kernel(
+    QrWork w, int64_t j0, int pw, int64_t c0, int64_t nt)
 {
-    __shared__ double lds[2 * US::STAGE];
+    using T = typename S::elem;
+    __shared__ __align__(16) typename S::unit lds[2 * S::UNITS];
     int64_t rb, cb;
-    if (!update_tile_part<PART>((w.m - j0 + US::BN - 1) / US::BN, (nt + US::BM - 1) / US::BM, n_head, rb,
-                                cb))
+    if (!update_tile((w.m - j0 + S::BN - 1) / S::BN, (nt + S::BM - 1) / S::BM, rb, cb))
         return;
-    const int64_t q0 = cb * US::BM;
-    const int64_t r0 = j0 + rb * US::BN;
-    const double *A = w.A;
+    const int64_t q0 = cb * S::BM, r0 = j0 + rb * S::BN;
+    const T *A = qmat<T>(w);
+    T *C = qmat<T>(w) + c0 * w.lda;
+    const T *W = sizeof(T) == 8 ? reinterpret_cast<const T *>(w.W) : reinterpret_cast<const T *>(w.W32);
     const int64_t lda = w.lda, m = w.m, ldW = w.ldw;
-    const double *W = w.W;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int wm = wave / US::WN, wn = wave % US::WN;
-    double *C = w.A + c0 * lda;
-    d4 acc[US::FM][US::FN];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, g = lane >> 4, rl = lane & 15;
+    const int wm = wave / S::WN, wn = wave % S::WN;
+    const bool inside = r0 + S::BN <= m && q0 + S::BM <= nt;  // no checks on C
+    typename S::acc4 acc[S::FM][S::FN];
 #pragma unroll
-    for (int i = 0; i < US::FM; ++i)
+    for (int i = 0; i < S::FM; ++i)
 #pragma unroll
-        for (int jj = 0; jj < US::FN; ++jj)
+        for (int j = 0; j < S::FN; j += S::V)
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-                const int64_t q = q0 + acc_row<US>(wm, i, lane, e);
-                const int64_t r = r0 + acc_col<US>(wn, jj, lane, e);
-                acc[i][jj][e] = ((PART == 1 || r < m) && q < nt) ? C[q * lda + r] : 0.0;
+                const int64_t q = q0 + S::row(wm, i, g, e), r = r0 + S::col(wn, j, rl);
+                typename S::unit v;
+                if (inside) {
+                    __builtin_memcpy(&v, __builtin_assume_aligned(C + q * lda + r, 16), 16);
+                } else {
+#pragma unroll
+                    for (int h = 0; h < S::V; ++h)
+                        v[h] = (q < nt && r + h < m) ? C[q * lda + r + h] : T(0);
+                }
+#pragma unroll
+                for (int h = 0; h < S::V; ++h)
+                    acc[i][j + h][e] = -v[h];
             }
+    // columns past nt and rows past m (and past lda: the next column's) are computed, not stored
+    const T *src[S::LPT];
+    int64_t step[S::LPT];
+#pragma unroll
+    for (int i = 0; i < S::LPT; ++i) {
+        const int x = S::unit_x(i);
+        const int64_t p = S::unit_p(i);
+        src[i] = x < S::UA ? W + p * ldW + q0 + S::V * x : A + (j0 + p) * lda + r0 + S::V * (x - S::UA);
+        step[i] = S::BK * (x < S::UA ? ldW : lda);
+    }
     const bool masked = r0 < j0 + pw;  // the row block meets Y's unit upper triangle
-    constexpr int VA = US::BM * US::BK / US::NT, VB = US::BN * US::BK / US::NT;
-    auto fa = [&](int qi, int64_t p, double (&v)[VA]) {
-        const int64_t q = q0 + qi;
-        if (p >= pw) {
+    mtile_product<S>(acc, lds, (pw + S::BK - 1) / S::BK, masked ? 0 : pw / S::BK, src, step, [&](int kt, int i) {
+        const int x = S::unit_x(i);
+        const int64_t p = kt * S::BK + S::unit_p(i);
+        const T *at = x < S::UA ? W + q0 + S::V * x : A + j0 * lda + r0 + S::V * (x - S::UA);
+        typename S::unit v;
+        __builtin_memcpy(&v, __builtin_assume_aligned(at + (p < pw ? p : 0) * (x < S::UA ? ldW : lda), 16), 16);
+        const int64_t diag = x < S::UA ? PLAIN : j0 + p;
 #pragma unroll
-            for (int e = 0; e < VA; ++e)
-                v[e] = 0.0;
-        } else if (q + VA <= nt) {
-            load_run(W + p * ldW + q, v);
-#pragma unroll
-            for (int e = 0; e < VA; ++e)
-                v[e] = -v[e];
-        } else {
-#pragma unroll
-            for (int e = 0; e < VA; ++e)
-                v[e] = (q + e < nt) ? -W[p * ldW + q + e] : 0.0;
-        }
-    };
-    auto fb = [&](int ri, int64_t p, double (&v)[VB]) {
-        const int64_t r = r0 + ri;
-        if (p >= pw) {
-#pragma unroll
-            for (int e = 0; e < VB; ++e)
-                v[e] = 0.0;
-        } else if (PART == 1 || (!masked && r + VB <= m)) {
-            load_run(A + (j0 + p) * lda + r, v);
-        } else {
-#pragma unroll
-            for (int e = 0; e < VB; ++e)
-                v[e] = ypanel(A, lda, m, j0, pw, r + e, (int)p);
-        }
-    };
-    gemm_tile_runs<US, false, false>(acc, lds, pw, fa, fb);
+        for (int h = 0; h < S::V; ++h)
+            v[h] = p < pw ? unit_lower<T>(v[h], r0 + S::V * (x - S::UA) + h, diag) : T(0);
+        return v;
+    });
     // recompute the store addresses rather than keep the loads' live through the product
     int64_t q0s = q0, r0s = r0;
     asm volatile("" : "+s"(q0s), "+s"(r0s));
 #pragma unroll
-    for (int i = 0; i < US::FM; ++i)
+    for (int i = 0; i < S::FM; ++i)
 #pragma unroll
-        for (int jj = 0; jj < US::FN; ++jj)
+        for (int j = 0; j < S::FN; j += S::V)
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-                const int64_t q = q0s + acc_row<US>(wm, i, lane, e);
-                const int64_t r = r0s + acc_col<US>(wn, jj, lane, e);
-                if ((PART == 1 || r < m) && q < nt)
-                    C[q * lda + r] = acc[i][jj][e];
+                const int64_t q = q0s + S::row(wm, i, g, e), r = r0s + S::col(wn, j, rl);
+                typename S::unit v;
+#pragma unroll
+                for (int h = 0; h < S::V; ++h)
+                    v[h] = -acc[i][j + h][e];
+                if (inside) {
+                    __builtin_memcpy(__builtin_assume_aligned(C + q * lda + r, 16), &v, 16);
+                } else if (q < nt) {
+#pragma unroll
+                    for (int h = 0; h < S::V; ++h)
+                        if (r + h < m)
+                            C[q * lda + r + h] = v[h];
+                }
             }
 }
 
-using WS32 = TileShape<OB, 128, 16, 2, 2>;   // FP32 P = Y^T C (16-deep: four waves per SIMD)
-using US32 = TileShape<128, 128, 16, 2, 2>;  // FP32 C^T -= W^T Y^T (16-deep: three waves per SIMD)
-
-// FP32-storage versions of qr_wpart_kernel / qr_update_kernel on FP32 MFMA.
-__global__ __launch_bounds__(256, 3) void qr_wpart32_kernel(QrWork w, int64_t j0, int pw, int64_t c0, int64_t nt,
-                                                            int ymode, int64_t r0, int64_t chunk)
-{
-    __shared__ float lds[2 * WS32::STAGE];
-    const int prow0 = OB * (int)blockIdx.z;
-    j0 += prow0;
-    pw = (pw - prow0) < OB ? (pw - prow0) : OB;
-    if (pw <= 0)
-        return;
-    const int64_t ch = blockIdx.y;
-    const int64_t q0 = (int64_t)blockIdx.x * WS32::BN;
-    const int64_t rlo = r0 + ch * chunk;
-    int64_t rhi = rlo + chunk;
-    if (rhi > w.m)
-        rhi = w.m;
-    if (rlo >= rhi)
-        return;
-    f4 acc[WS32::FM][WS32::FN];
-    zero_acc32<WS32>(acc);
-    const float *A = w.A32;
-    const int64_t lda = w.lda, m = w.m;
-    const bool masked = rlo < j0 + pw;
-    constexpr int VA = WS32::BM * WS32::BK / WS32::NT, VB = WS32::BN * WS32::BK / WS32::NT;
-    auto fa = [&](int p, int64_t k, float (&v)[VA]) {
-        const int64_t r = rlo + k;
-        if (p >= pw) {
-#pragma unroll
-            for (int e = 0; e < VA; ++e)
-                v[e] = 0.0f;
-        } else if (!masked && r + VA <= rhi) {
-            load_run(A + (j0 + p) * lda + r, v);
-        } else {
-#pragma unroll
-            for (int e = 0; e < VA; ++e)
-                v[e] = (r + e < rhi) ? ypanel(A, lda, m, j0, pw, r + e, p) : 0.0f;
-        }
-    };
-    auto fb = [&](int qi, int64_t k, float (&v)[VB]) {
-        const int64_t r = rlo + k, q = q0 + qi;
-        if (q >= nt) {
-#pragma unroll
-            for (int e = 0; e < VB; ++e)
-                v[e] = 0.0f;
-        } else if (ymode) {
-#pragma unroll
-            for (int e = 0; e < VB; ++e)
-                v[e] = (r + e < rhi) ? ypanel(A, lda, m, c0, (int)nt, r + e, (int)q) : 0.0f;
-        } else {
-            const float *col = A + (c0 + q) * lda + r;
-            if (r + VB <= rhi) {
-                load_run(col, v);
-            } else {
-#pragma unroll
-                for (int e = 0; e < VB; ++e)
-                    v[e] = (r + e < rhi) ? col[e] : 0.0f;
-            }
-        }
-    };
-    gemm_tile_runs32<WS32, true, true>(acc, lds, rhi - rlo, fa, fb);
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int wm = wave / WS32::WN, wn = wave % WS32::WN;
-    double *P = w.wpart + (ch * OB2 + prow0) * w.wp_ld;
-#pragma unroll
-    for (int i = 0; i < WS32::FM; ++i)
-#pragma unroll
-        for (int jj = 0; jj < WS32::FN; ++jj)
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const int p = acc32_row<WS32>(wm, i, lane, e);
-                const int64_t q = q0 + acc32_col<WS32>(wn, jj, lane, e);
-                if (p < pw && q < nt)
-                    P[p * w.wp_ld + q] = (double)acc[i][jj][e];
-            }
-}
-
-template <int PART>
-__global__ __launch_bounds__(256, 3) void qr_update32_kernel(QrWork w, int64_t j0, int pw, int64_t c0, int64_t nt,
-                                                          int n_head)
-{
-    __shared__ float lds[2 * US32::STAGE];
-    int64_t rb, cb;
-    if (!update_tile_part<PART>((w.m - j0 + US32::BN - 1) / US32::BN, (nt + US32::BM - 1) / US32::BM, n_head, rb,
-                                cb))
-        return;
-    const int64_t q0 = cb * US32::BM;
-    const int64_t r0 = j0 + rb * US32::BN;
-    const float *A = w.A32;
-    const int64_t lda = w.lda, m = w.m, ldW = w.ldw;
-    const float *W = w.W32;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int wm = wave / US32::WN, wn = wave % US32::WN;
-    float *C = w.A32 + c0 * lda;
-    f4 acc[US32::FM][US32::FN];  // starts from the C tile; the product takes -W
-#pragma unroll
-    for (int i = 0; i < US32::FM; ++i)
-#pragma unroll
-        for (int jj = 0; jj < US32::FN; ++jj)
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const int64_t q = q0 + acc32_row<US32>(wm, i, lane, e);
-                const int64_t r = r0 + acc32_col<US32>(wn, jj, lane, e);
-                acc[i][jj][e] = ((PART == 1 || r < m) && q < nt) ? C[q * lda + r] : 0.0f;
-            }
-    const bool masked = r0 < j0 + pw;
-    constexpr int VA = US32::BM * US32::BK / US32::NT, VB = US32::BN * US32::BK / US32::NT;
-    auto fa = [&](int qi, int64_t p, float (&v)[VA]) {
-        const int64_t q = q0 + qi;
-        if (p >= pw) {
-#pragma unroll
-            for (int e = 0; e < VA; ++e)
-                v[e] = 0.0f;
-        } else if (q + VA <= nt) {
-            load_run(W + p * ldW + q, v);
-#pragma unroll
-            for (int e = 0; e < VA; ++e)
-                v[e] = -v[e];
-        } else {
-#pragma unroll
-            for (int e = 0; e < VA; ++e)
-                v[e] = (q + e < nt) ? -W[p * ldW + q + e] : 0.0f;
-        }
-    };
-    auto fb = [&](int ri, int64_t p, float (&v)[VB]) {
-        const int64_t r = r0 + ri;
-        if (p >= pw) {
-#pragma unroll
-            for (int e = 0; e < VB; ++e)
-                v[e] = 0.0f;
-        } else if (PART == 1 || (!masked && r + VB <= m)) {
-            load_run(A + (j0 + p) * lda + r, v);
-        } else {
-#pragma unroll
-            for (int e = 0; e < VB; ++e)
-                v[e] = ypanel(A, lda, m, j0, pw, r + e, (int)p);
-        }
-    };
-    gemm_tile_runs32<US32, false, false>(acc, lds, pw, fa, fb);
-    int64_t q0s = q0, r0s = r0;
-    asm volatile("" : "+s"(q0s), "+s"(r0s));
-#pragma unroll
-    for (int i = 0; i < US32::FM; ++i)
-#pragma unroll
-        for (int jj = 0; jj < US32::FN; ++jj)
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const int64_t q = q0s + acc32_row<US32>(wm, i, lane, e);
-                const int64_t r = r0s + acc32_col<US32>(wn, jj, lane, e);
-                if ((PART == 1 || r < m) && q < nt)
-                    C[q * lda + r] = acc[i][jj][e];
-            }
-}
-
-// Split of rows [r0, m) into chunks for the split-K products.
+// Split of rows [r0, m) into chunks for the split-K products (whole tiles of 64 rows).
 static void chunking(int64_t rows, int64_t ncb, int64_t &chunk, int64_t &nch, int64_t cap, int64_t target = 2048)
 {
     nch = (target + ncb - 1) / ncb;
     if (nch > cap)
         nch = cap;
     chunk = (rows + nch - 1) / nch;
-    chunk = (chunk + 15) & ~int64_t(15);
-    if (chunk < 256)
-        chunk = 256;
+    chunk = (chunk + 63) & ~int64_t(63);
+    if (chunk < 128)
+        chunk = 128;
     nch = (rows + chunk - 1) / chunk;
 }
 
@@ -1049,17 +871,31 @@ static void factor_panel(const QrWork &wf, int64_t j0, int pw, double *Tout, hip
                            pw);
 }
 
-// P = Y^T C (split over row chunks) for the block at (j0, j0) of width pw.
+// P = Y^T C for the block at (j0, j0) of width pw, split over row chunks; returns their number.
+// The 64 x 64 tiles where either side is at most 64 wide, and where the large tiles would be
+// fewer than one per CU even with chunks of 512 rows.
 template <class T>
-static void launch_wpart(const QrWork &w, int64_t j0, int pw, int64_t c0, int64_t nt, int ymode, int64_t r0,
-                         int64_t chunk, int64_t ncb, int64_t nch, int halves, hipStream_t s)
+static int64_t launch_wpart(const QrWork &w, int64_t j0, int pw, int64_t c0, int64_t nt, int ymode, int64_t r0,
+                            int64_t target, hipStream_t s)
 {
-    if constexpr (sizeof(T) == 8)
-        hipLaunchKernelGGL(qr_wpart_kernel, dim3((unsigned)ncb, (unsigned)nch, (unsigned)halves), dim3(256), 0, s, w,
+    using L = typename QrTiles<T>::WL;
+    using M = typename QrTiles<T>::WS;
+    const int64_t rows = w.m - r0;
+    auto tiles = [](int64_t x, int64_t b) { return (x + b - 1) / b; };
+    int64_t chunk, nch;
+    const bool narrow = pw <= 64 || nt <= 64 || tiles(nt, L::BN) * tiles(pw, L::BM) * tiles(rows, 512) < 256;
+    if (narrow) {
+        const int64_t nq = tiles(nt, M::BN), np = tiles(pw, M::BM);
+        chunking(rows, nq * np, chunk, nch, w.max_chunks, target);
+        hipLaunchKernelGGL(qr_wpart_kernel<M>, dim3((unsigned)nq, (unsigned)nch, (unsigned)np), dim3(M::NT), 0, s, w,
                            j0, pw, c0, nt, ymode, r0, chunk);
-    else
-        hipLaunchKernelGGL(qr_wpart32_kernel, dim3((unsigned)ncb, (unsigned)nch, (unsigned)halves), dim3(256), 0, s,
-                           w, j0, pw, c0, nt, ymode, r0, chunk);
+    } else {
+        const int64_t nq = tiles(nt, L::BN), np = tiles(pw, L::BM);
+        chunking(rows, nq * np, chunk, nch, w.max_chunks, target);
+        hipLaunchKernelGGL(qr_wpart_kernel<L>, dim3((unsigned)nq, (unsigned)nch, (unsigned)np), dim3(L::NT), 0, s, w,
+                           j0, pw, c0, nt, ymode, r0, chunk);
+    }
+    return nch;
 }
 
 // The compact-WY data of a trailing-update block at column J: panel pair a
@@ -1086,61 +922,34 @@ static void apply_block(const QrWork &wf, int64_t J, const BlockT &bt, int64_t c
     const int pw = bt.pw();
     const QrWork w = rows_to(wf, J + pw);
     const int64_t rows = w.m - J;
-    const int64_t ncb = (nt + WS::BN - 1) / WS::BN;
-    int64_t chunk, nch;
-    const int halves = bt.pwb > 0 ? 2 : 1;  // 128-row halves of P, one grid layer each
-    chunking(rows, ncb * halves, chunk, nch, w.max_chunks, w.split_wgs > 0 ? w.split_wgs : 2048);
-    launch_wpart<T>(w, J, pw, c0, nt, 0, J, chunk, ncb, nch, halves, s);
-    if (nch > 1) {
+    WArgs a{};
+    a.nch = launch_wpart<T>(w, J, pw, c0, nt, 0, J, w.split_wgs > 0 ? w.split_wgs : 2048, s);
+    if (a.nch > 8) {
         hipLaunchKernelGGL(qr_psum_kernel, dim3((unsigned)(((int64_t)pw * nt + 255) / 256)), dim3(256), 0, s, w, pw,
-                           nch, nt);
-        nch = 1;
+                           a.nch, nt);
+        a.nch = 1;
     }
-    const unsigned gq = (unsigned)((nt + 63) / 64);
-    const double *ta = bt.ta ? bt.ta : bt.Ta();
-    const int tld = bt.ta ? bt.tld : OB;
-    if constexpr (sizeof(T) == 8) {
-        hipLaunchKernelGGL(qr_wred_kernel<double>, dim3(gq), dim3(256), 0, s, w, ta, tld, bt.pwa, nch, nt, w.W, 0);
-        if (bt.pwb > 0) {
-            hipLaunchKernelGGL(qr_pcorr_kernel, dim3(gq, OB / PC_ROWS), dim3(256), 0, s, w, (const double *)bt.H(),
-                               bt.pwa, bt.pwb, nt);
-            hipLaunchKernelGGL(qr_wred_kernel<double>, dim3(gq), dim3(256), 0, s, w, (const double *)bt.Tb(), OB,
-                               bt.pwb, nch, nt, w.W, OB);
-        }
-    } else {
-        hipLaunchKernelGGL(qr_wred_kernel<float>, dim3(gq), dim3(256), 0, s, w, ta, tld, bt.pwa, nch, nt, w.W32,
-                           0);
-        if (bt.pwb > 0) {
-            hipLaunchKernelGGL(qr_pcorr_kernel, dim3(gq, OB / PC_ROWS), dim3(256), 0, s, w, (const double *)bt.H(),
-                               bt.pwa, bt.pwb, nt);
-            hipLaunchKernelGGL(qr_wred_kernel<float>, dim3(gq), dim3(256), 0, s, w, (const double *)bt.Tb(), OB,
-                               bt.pwb, nch, nt, w.W32, OB);
-        }
-    }
-    const int n_head = (pw + US::BN - 1) / US::BN;  // row blocks of 128 that meet Y's unit triangle
-    static_assert(US::BN == US32::BN, "one row-block split for both update kernels");
-    auto grid = [](int64_t tiles) { return dim3((unsigned)((tiles + 7) & ~int64_t(7))); };
-    if constexpr (sizeof(T) == 8) {
-        const int64_t nrb = (rows + US::BN - 1) / US::BN, ncb_u = (nt + US::BM - 1) / US::BM;
-        if (nrb > n_head + 1) {  // interior row blocks without checks, then the edge ones
-            hipLaunchKernelGGL(qr_update_kernel<1>, grid((nrb - n_head - 1) * ncb_u), dim3(256), 0, s, w, J, pw, c0,
-                               nt, n_head);
-            hipLaunchKernelGGL(qr_update_kernel<2>, grid((n_head + 1) * ncb_u), dim3(256), 0, s, w, J, pw, c0, nt,
-                               n_head);
-        } else {
-            hipLaunchKernelGGL(qr_update_kernel<0>, grid(nrb * ncb_u), dim3(256), 0, s, w, J, pw, c0, nt, n_head);
-        }
-    } else {
-        const int64_t nrb = (rows + US32::BN - 1) / US32::BN, ncb_u = (nt + US32::BM - 1) / US32::BM;
-        if (nrb > n_head + 1) {
-            hipLaunchKernelGGL(qr_update32_kernel<1>, grid((nrb - n_head - 1) * ncb_u), dim3(256), 0, s, w, J, pw,
-                               c0, nt, n_head);
-            hipLaunchKernelGGL(qr_update32_kernel<2>, grid((n_head + 1) * ncb_u), dim3(256), 0, s, w, J, pw, c0, nt,
-                               n_head);
-        } else {
-            hipLaunchKernelGGL(qr_update32_kernel<0>, grid(nrb * ncb_u), dim3(256), 0, s, w, J, pw, c0, nt, n_head);
-        }
-    }
+    a.Ta = bt.ta ? bt.ta : bt.Ta();
+    a.tld = bt.ta ? bt.tld : OB;
+    a.Tb = bt.pwb > 0 ? bt.Tb() : nullptr;
+    a.H = bt.pwb > 0 ? bt.H() : nullptr;
+    a.pwa = bt.pwa;
+    a.pwb = bt.pwb;
+    a.nt = nt;
+    if constexpr (sizeof(T) == 8)
+        hipLaunchKernelGGL(qr_w_kernel<double>, dim3((unsigned)((nt + 15) / 16)), dim3(256), 0, s, w, a, w.W);
+    else
+        hipLaunchKernelGGL(qr_w_kernel<float>, dim3((unsigned)((nt + 15) / 16)), dim3(256), 0, s, w, a, w.W32);
+    // the large tiles where they fill the chip at least twice
+    using L = typename QrTiles<T>::UL;
+    using M = typename QrTiles<T>::US;
+    auto tiles = [](int64_t x, int64_t b) { return (x + b - 1) / b; };
+    auto grid = [](int64_t n) { return dim3((unsigned)((n + 7) & ~int64_t(7))); };
+    const int64_t nl = tiles(rows, L::BN) * tiles(nt, L::BM), nm = tiles(rows, M::BN) * tiles(nt, M::BM);
+    if (nl >= 512)
+        hipLaunchKernelGGL(qr_update_kernel<L>, grid(nl), dim3(L::NT), 0, s, w, J, pw, c0, nt);
+    else
+        hipLaunchKernelGGL(qr_update_kernel<M>, grid(nm), dim3(M::NT), 0, s, w, J, pw, c0, nt);
 }
 
 // Factor the panel pair at column J (main-stream scratch in w): panel A, its
@@ -1162,10 +971,7 @@ static int factor_pair(const QrWork &w, int64_t J, double *Tdst, hipStream_t s)
     apply_block<T>(w, J, pa, jb, pwb, s);
     factor_panel<T>(w, jb, pwb, Tb, s);
     const QrWork wg = rows_to(w, jb + pwb);  // G = Y_a^T Y_b
-    const int64_t rows = wg.m - jb;
-    int64_t chunk, nch;
-    chunking(rows, 1, chunk, nch, wg.max_chunks);
-    launch_wpart<T>(wg, J, pwa, jb, (int64_t)pwb, 1, jb, chunk, 1, nch, 1, s);
+    const int64_t nch = launch_wpart<T>(wg, J, pwa, jb, (int64_t)pwb, 1, jb, 2048, s);
     hipLaunchKernelGGL(qr_gsum_kernel, dim3(NB * NB / 256), dim3(256), 0, s, wg, pwb, nch, wg.cq_G, NB);
     hipLaunchKernelGGL(qr_tcombine_kernel, dim3(1), dim3(256), 0, s, w, (const double *)w.cq_G, Tdst);
     return pwa + pwb;
@@ -1187,12 +993,9 @@ static int factor_block(const QrWork &w, int64_t J, BlockT &bt, hipStream_t s)
     apply_block<T>(w, J, a, jb, pwb_max, s);
     bt.pwb = factor_pair<T>(w, jb, bt.Tb(), s);
     const QrWork wg = rows_to(w, jb + bt.pwb);  // G = Y_a^T Y_b
-    const int64_t rows = wg.m - jb;
-    int64_t chunk, nch;
-    chunking(rows, 1, chunk, nch, wg.max_chunks);
-    launch_wpart<T>(wg, J, bt.pwa, jb, (int64_t)bt.pwb, 1, jb, chunk, 1, nch, 1, s);
+    const int64_t nch = launch_wpart<T>(wg, J, bt.pwa, jb, (int64_t)bt.pwb, 1, jb, 2048, s);
     hipLaunchKernelGGL(qr_gsum_kernel, dim3(OB * OB / 256), dim3(256), 0, s, wg, bt.pwb, nch, bt.G(), OB);
-    hipLaunchKernelGGL(qr_hmat_kernel, dim3(OB), dim3(OB), 0, s, (const double *)bt.Ta(), OB, bt.pwa,
+    hipLaunchKernelGGL(qr_hmat_kernel, dim3(16), dim3(256), 0, s, (const double *)bt.Ta(), OB, bt.pwa,
                        (const double *)bt.G(), bt.pwb, bt.H());
     return bt.pw();
 }
