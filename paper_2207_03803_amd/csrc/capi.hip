@@ -27,7 +27,7 @@ struct Layout {
     TsqrTree tree;
     size_t off_A = 0, off_tau = 0, off_wpart = 0, off_T = 0, off_Tin = 0, off_U = 0, off_W = 0, off_ts_tiles = 0,
            off_ts_X = 0, off_ts_tau = 0, off_rhs = 0, off_misc = 0, off_tiles = 0, off_counters = 0,
-           off_status = 0, off_tflags = 0, n_tflags = 0, off_cq_S = 0, off_cq_part = 0, off_cq_G = 0, off_cq_R = 0,
+           off_status = 0, off_tflags = 0, off_tx = 0, off_cq_S = 0, off_cq_part = 0, off_cq_G = 0, off_cq_R = 0,
            off_T2 = 0, off_wpart_s = 0, off_W_s = 0, off_W32_s = 0, off_plan = 0, total = 0;
     // mixed precision only
     bool mixed = false;
@@ -109,10 +109,10 @@ Layout make_layout(int64_t NE, int64_t n_atoms, int64_t M, int32_t precision, in
     }
     L.off_counters = take(sizeof(unsigned) * N_COUNTERS);
     L.off_status = take(sizeof(int32_t) * 4);
-    L.n_tflags = trsv_sync_ints(M);
-    L.off_tflags = take(sizeof(int32_t) * (size_t)L.n_tflags);
+    L.off_tflags = take(sizeof(int32_t) * 2);
+    L.off_tx = take(sizeof(unsigned long long) * (size_t)M);
     L.off_cq_S = takep(sizeof(double) * QR_NB * (size_t)L.lda);
-    L.off_cq_part = takep(sizeof(double) * (size_t)CQ_MAX_CHUNKS * QR_NB * QR_NB);
+    L.off_cq_part = takep(sizeof(double) * (size_t)CQ_PART);
     L.off_cq_G = takep(sizeof(double) * 4 * QR_NB * QR_NB);
     L.off_cq_R = takep(sizeof(double) * 4 * QR_NB * QR_NB);
     L.off_T2 = takep(sizeof(double) * 16 * QR_NB * QR_NB);
@@ -183,8 +183,11 @@ struct gap_handle_s {
     int32_t *status() const { return at<int32_t>(L.off_status); }
     unsigned *counters() const { return at<unsigned>(L.off_counters); }
     double *misc() const { return at<double>(L.off_misc); }
-    // flags of the one-launch triangular solves; counters()[12] is their arrival counter
-    TrsvSync tsync() const { return TrsvSync{at<int32_t>(L.off_tflags), counters() + 12, status()}; }
+    // state of the one-launch triangular solves; counters()[12] is their arrival counter
+    TrsvSync tsync() const
+    {
+        return TrsvSync{at<int32_t>(L.off_tflags), at<unsigned long long>(L.off_tx), counters() + 12, status()};
+    }
 
     // diagnostics area: [8M] partials, partR, t, g, x, y, z [M each], sc[4], sumsq partials[256], out[4]
     DiagWork diag(double *g_override) const
@@ -230,17 +233,14 @@ __global__ void zero_u32_kernel(unsigned *p, int n)
         p[threadIdx.x] = 0u;
 }
 
-// The build's counters [N_COUNTERS], status words [4] and triangular-solve flags [n].
-__global__ __launch_bounds__(256) void build_clear_kernel(unsigned *counters, int32_t *status, int32_t *flags,
-                                                          int64_t n)
+// The build's counters [N_COUNTERS] and status words [4].
+__global__ __launch_bounds__(256) void build_clear_kernel(unsigned *counters, int32_t *status)
 {
     const int t = threadIdx.x;
     if (t < N_COUNTERS)
         counters[t] = 0u;
     else if (t < N_COUNTERS + 4)
         status[t - N_COUNTERS] = 0;
-    for (int64_t i = t; i < n; i += 256)
-        flags[i] = 0;
 }
 
 // All-ones words over n 4-byte words (GAP_FLAG_POISON_WORKSPACE).
@@ -541,8 +541,8 @@ static gap_status build_setup(gap_handle h, hipStream_t s, KnmArgs *a)
             const unsigned blocks = (unsigned)std::min<int64_t>((words + 255) / 256, 4096);
             hipLaunchKernelGGL(poison_kernel, dim3(blocks), dim3(256), 0, s, h->at<uint32_t>(L.poison_off[i]), words);
         }
-    hipLaunchKernelGGL(build_clear_kernel, dim3(1), dim3(256), 0, s, h->counters(), h->status(),
-                       h->at<int32_t>(L.off_tflags), (int64_t)L.n_tflags);
+    hipLaunchKernelGGL(build_clear_kernel, dim3(1), dim3(256), 0, s, h->counters(), h->status());
+    GAP_TRY(dev(launch_trsv_clear(h->tsync(), L.M, s)));
     const KnmPlan kp = plan_of(h);
     GAP_TRY(dev(launch_plan_tiles(h->offsets, L.NE, L.n_atoms, kp, L.max_tiles, h->status(), s)));
     *a = KnmArgs{};

@@ -27,9 +27,8 @@ namespace gap {
 constexpr int CB = QR_NB;        // panel width bound (64)
 static_assert(CB == S64, "panel blocks");
 constexpr int CQ_ROWS = 64;      // rows per workgroup and step (16 per wave)
-constexpr int CQ_WGS = 128;      // workgroups of one launch
 constexpr int CQ_GRP = 16;       // workgroups of one first-level sum
-static_assert(CQ_WGS <= CQ_MAX_CHUNKS && CQ_WGS / CQ_GRP < CQ_COUNTERS, "partials and counters");
+static_assert(CQ_WGS * NBLK * BLK == CQ_PART && CQ_WGS / CQ_GRP < CQ_COUNTERS, "partials and counters");
 
 enum CqStep { CQ_GRAM, CQ_PASS1, CQ_PASS2, CQ_PASS3 };
 

@@ -84,13 +84,14 @@ struct QrWork {
     int32_t panel;      // panel factorisation: 0 = shifted CholeskyQR3, 1 = TSQR
     double *cq_S;       // CholeskyQR: FP64 scratch panel [QR_NB x cq_ld] (column-major)
     int64_t cq_ld;      // >= m
-    double *cq_part;    // [CQ_MAX_CHUNKS * QR_NB * QR_NB] partial Gram matrices
+    double *cq_part;    // [CQ_PART] partial Gram matrices (upper 16 x 16 blocks)
     double *cq_G;       // [4 * QR_NB * QR_NB] Y_a^T Y_b of a panel pair
     double *cq_R;       // [4 * QR_NB * QR_NB] R1, R2, R2 R1, U R3 (packed upper triangles)
     unsigned *cq_counters;  // [CQ_COUNTERS] arrival counters of the panel's sums (zero; left zero)
     int32_t *status;
 };
-constexpr int64_t CQ_MAX_CHUNKS = 256;
+constexpr int CQ_WGS = 128;         // workgroups of one launch of the panel's passes
+constexpr int64_t CQ_PART = CQ_WGS * 10 * 256;
 constexpr int CQ_COUNTERS = 20;
 // Shifted CholeskyQR3 panel + Householder reconstruction (same outputs as the TSQR panel).
 void cqr_panel_f64(const QrWork &w, int64_t j0, int pw, double *Tout, hipStream_t s);
@@ -106,15 +107,16 @@ struct QrAsync {
 hipError_t launch_geqrf(const QrWork &w, hipStream_t s, const QrAsync *la);
 
 // -------------------------------------------------------- triangular solve
-// Flags of the one-launch blocked substitution: sync.flags holds
-// trsv_sync_ints(n) int32 (zero before the first solve; each solve leaves them
-// zero), sync.counter one unsigned (zero), sync.status the device status word.
+// State of the one-launch blocked substitution: xbuf [n] and flags [2], set by
+// launch_trsv_clear before the first solve (each solve leaves them as it found them), one
+// counter (zero), the device status word.
 struct TrsvSync {
     int32_t *flags;
+    unsigned long long *xbuf;
     unsigned *counter;
     int32_t *status;
 };
-int64_t trsv_sync_ints(int64_t n);
+hipError_t launch_trsv_clear(const TrsvSync &sync, int64_t n, hipStream_t s);
 // Solve R c = rhs for the n x n upper triangle of R (column-major, ld); then
 // check c is finite (DST_ENONFINITE otherwise).
 hipError_t launch_trsv_upper(const double *R, int64_t ld, int64_t n, const double *rhs, double *c,
