@@ -23,7 +23,7 @@ struct Layout {
     // N = all observation rows: NE energies (configurations) then n_obs derivative observations
     int64_t N = 0, M = 0, n_atoms = 0, m = 0, lda = 0, ncols = 0, max_tiles = 0;
     int64_t NE = 0, n_obs = 0, n_pos = 0, max_tiles_d = 0;
-    size_t off_tiles_d = 0, off_plan_d = 0, off_D = 0;
+    size_t off_tiles_d = 0, off_plan_d = 0, off_D = 0, end_scratch = 0;
     TsqrTree tree;
     size_t off_A = 0, off_tau = 0, off_wpart = 0, off_T = 0, off_Tin = 0, off_U = 0, off_W = 0, off_ts_tiles = 0,
            off_ts_X = 0, off_ts_tau = 0, off_rhs = 0, off_misc = 0, off_tiles = 0, off_counters = 0,
@@ -88,14 +88,19 @@ Layout make_layout(int64_t NE, int64_t n_atoms, int64_t M, int32_t precision, in
     };
     L.off_A = takep(sizeof(double) * (size_t)L.lda * (size_t)L.ncols);
     L.off_tau = takep(sizeof(double) * (size_t)M);
+    // the QR's large scratch, from off_wpart to end_scratch: free during the build (the
+    // derivative rows' blocks use it)
     L.off_wpart = takep(sizeof(double) * (size_t)qr_max_chunks() * 4 * QR_NB * (size_t)L.ncols);
-    L.off_T = takep(sizeof(double) * 16 * QR_NB * QR_NB);
-    L.off_Tin = takep(sizeof(double) * 2 * QR_NB * QR_NB);
-    L.off_U = takep(sizeof(double) * QR_NB * QR_NB);
     L.off_W = takep(sizeof(double) * 4 * QR_NB * (size_t)((L.ncols + 63) / 64 * 64));
     L.off_ts_tiles = takep(sizeof(double) * (size_t)L.tree.tiles_doubles);
     L.off_ts_X = takep(sizeof(double) * (size_t)L.tree.tiles_doubles);
     L.off_ts_tau = takep(sizeof(double) * (size_t)L.tree.tau_doubles);
+    L.off_cq_S = takep(sizeof(double) * QR_NB * (size_t)L.lda);
+    L.off_wpart_s = takep(sizeof(double) * (size_t)qr_max_chunks_s() * 4 * QR_NB * 2 * QR_NB);
+    L.end_scratch = o;
+    L.off_T = takep(sizeof(double) * 16 * QR_NB * QR_NB);
+    L.off_Tin = takep(sizeof(double) * 2 * QR_NB * QR_NB);
+    L.off_U = takep(sizeof(double) * QR_NB * QR_NB);
     L.off_rhs = takep(sizeof(double) * (size_t)M);
     L.off_misc = takep(sizeof(double) * 512);
     L.off_tiles = take(sizeof(int32_t) * (size_t)(L.max_tiles + 2));
@@ -111,12 +116,10 @@ Layout make_layout(int64_t NE, int64_t n_atoms, int64_t M, int32_t precision, in
     L.off_status = take(sizeof(int32_t) * 4);
     L.off_tflags = take(sizeof(int32_t) * 2);
     L.off_tx = take(sizeof(unsigned long long) * (size_t)M);
-    L.off_cq_S = takep(sizeof(double) * QR_NB * (size_t)L.lda);
     L.off_cq_part = takep(sizeof(double) * (size_t)CQ_PART);
     L.off_cq_G = takep(sizeof(double) * 4 * QR_NB * QR_NB);
     L.off_cq_R = takep(sizeof(double) * 4 * QR_NB * QR_NB);
     L.off_T2 = takep(sizeof(double) * 16 * QR_NB * QR_NB);
-    L.off_wpart_s = takep(sizeof(double) * (size_t)qr_max_chunks_s() * 4 * QR_NB * 2 * QR_NB);
     L.off_W_s = takep(sizeof(double) * 16 * QR_NB * QR_NB);
     L.off_W32_s = takep(sizeof(float) * 16 * QR_NB * QR_NB);
     L.off_diag = takep(sizeof(double) * (size_t)(14 * M + 512));
@@ -734,14 +737,9 @@ static gap_status build_derivatives(gap_handle h)
         k.status = h->status();
         GAP_TRY(dev(launch_knm(k, (L.M + KNM_BM - 1) / KNM_BM, s)));
     }
-    const KnmPlan kp = plan_of_d(h);
-    GAP_TRY(dev(launch_plan_tiles(o.obs_offsets, L.n_obs, L.n_pos, kp, L.max_tiles_d, h->status(), s)));
     KnmArgs a{};
     a.X = o.x_grad;
     a.offsets = o.obs_offsets;
-    a.tile_start = kp.tile_start;
-    a.cfg_list = kp.cfg_list;
-    a.n_tiles_dev = kp.n_tiles;
     a.XM = h->x_sparse;
     a.M = L.M;
     a.d = p.d;
@@ -759,7 +757,17 @@ static gap_status build_derivatives(gap_handle h)
     a.ldd = L.M;
     a.n_grad = o.n_grad;
     a.n_src = L.n_atoms;
-    GAP_TRY(dev(launch_kdm(a, L.max_tiles_d, s)));
+    const int w = kdm_block_cols(o.n_grad, L.n_pos, L.M, (int64_t)((L.end_scratch - L.off_wpart) / sizeof(double)));
+    if (w > 0) {
+        GAP_TRY(dev(launch_kdm_blocks(a, L.n_obs, L.n_pos, w, h->at<double>(L.off_wpart), s)));
+    } else {
+        const KnmPlan kp = plan_of_d(h);
+        GAP_TRY(dev(launch_plan_tiles(o.obs_offsets, L.n_obs, L.n_pos, kp, L.max_tiles_d, h->status(), s)));
+        a.tile_start = kp.tile_start;
+        a.cfg_list = kp.cfg_list;
+        a.n_tiles_dev = kp.n_tiles;
+        GAP_TRY(dev(launch_kdm(a, L.max_tiles_d, s)));
+    }
     h->mark(9, true);
     return GAP_OK;
 }

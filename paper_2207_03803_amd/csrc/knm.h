@@ -58,6 +58,10 @@ hipError_t launch_knm(KnmArgs a, int64_t max_tiles, hipStream_t s);
 // observations' positions, row o of out is sum_p w_p zeta sw2 D(i(p), j) (x'_{g(p)} . x_j),
 // divided by sigma[o].  a.X holds the gradients, a.zeta the kernel exponent.
 hipError_t launch_kdm(KnmArgs a, int64_t max_tiles, hipStream_t s);
+// The same rows without a tile plan, w columns at a time through scratch H [n_grad x w]
+// (w = kdm_block_cols(...) with the doubles of scratch there are; 0: use launch_kdm).
+int kdm_block_cols(int64_t n_grad, int64_t n_pos, int64_t M, int64_t room);
+hipError_t launch_kdm_blocks(const KnmArgs &a, int64_t n_obs, int64_t n_pos, int w, double *H, hipStream_t s);
 // The K_NM of n fits as grouped launches (up to KNM_GROUP fits per launch, the
 // table passed as the kernel argument); each fit's tiles compute exactly what
 // launch_knm computes for it.

@@ -4,6 +4,9 @@
 // A; Eqs. 1-2).  The n_atoms x M matrix of atom-level covariances is never
 // written to HBM.
 #include "knm.h"
+#include "small64.h"
+
+#include <type_traits>
 
 namespace gap {
 
@@ -521,6 +524,146 @@ __global__ __launch_bounds__(KNM_NT, 2) void knm_kernel(KnmArgs a) { knm_body<BN
 // Derivative observation rows: the K_NM tile loop over the observations' positions.
 __global__ __launch_bounds__(KNM_NT, 2) void kdm_kernel(KnmArgs a) { knm_body<64, true>(a, blockIdx.x); }
 
+// ---------------------------------------------------------------------------
+// Derivative rows in two steps, where gradient rows serve several positions (a force
+// component and the virials of its configuration): for a block of w columns, first
+// H[g][j] = zeta sw2 D(i(g), j) (x'_g . x_j) of every gradient row g, once, into scratch (bound
+// by the matrix cores), then each observation's weighted sum of rows of H (bound by the cache
+// that holds H).  The tile loop over positions (kdm_kernel) multiplies a row once per position:
+// 150 configurations (234,000 rows, 702,000 positions, M = 1,500, d = 400) take 8.1 ms here,
+// 20.0 there.  64-row tiles: 96-column blocks are 3.6 rounds of 128-row ones, 400 us against 364.
+// ---------------------------------------------------------------------------
+template <int BN>
+using GradTile = KTile<double, 64, BN, 8, 2, 2>;
+
+template <class S>
+__global__ __launch_bounds__(S::NT, 3) void grad_rows_kernel(KnmArgs a, int64_t col0, int w, double *__restrict__ H)
+{
+    __shared__ __align__(16) d2 lds[2 * S::UNITS];
+    const int64_t n_ct = (w + S::BN - 1) / S::BN, total = (a.n_grad + S::BM - 1) / S::BM * n_ct;
+    const int64_t lw = xcd_remap(blockIdx.x, (total + 7) & ~int64_t(7));
+    if (lw >= total)
+        return;
+    const int64_t r0 = lw / n_ct * S::BM, c0 = lw % n_ct * S::BN;  // rows, columns of the block
+    const int64_t cols = a.M - col0 < w ? a.M - col0 : w;
+    const double *src[S::LPT];
+#pragma unroll
+    for (int i = 0; i < S::LPT; ++i) {
+        const int r = S::unit_row(i);
+        const double *p;
+        if (r < S::BM)  // rows and columns past the end repeat the last one, unused
+            p = a.X + (r0 + r < a.n_grad ? r0 + r : a.n_grad - 1) * (int64_t)a.d;
+        else
+            p = a.XM + (col0 + (c0 + r - S::BM < cols ? c0 + r - S::BM : cols - 1)) * (int64_t)a.d;
+        src[i] = p + S::unit_k(i);
+    }
+    d4 acc[S::FM][S::FN];
+    ktile_zero<S>(acc);
+    ktile_product<S>(acc, lds, src, a.d, rows_aligned16(a.X, a.d) && rows_aligned16(a.XM, a.d));
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int wm = wave / S::WN, wn = wave % S::WN;
+    const double f = a.zeta * a.sw2;
+#pragma unroll
+    for (int i = 0; i < S::FM; ++i)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const int64_t g = r0 + acc_row<S>(wm, i, lane, e);
+            if (g >= a.n_grad)
+                continue;
+            const int64_t at = a.grad_atom[g];
+            const bool ok = at >= 0 && at < a.n_src;  // (reported where a position uses the row)
+#pragma unroll
+            for (int j = 0; j < S::FN; ++j) {
+                const int64_t c = c0 + acc_col<S>(wn, j, lane, e);
+                if (c < cols)
+                    H[g * w + c] = ok ? acc[i][j][e] * (f * (a.D ? a.D[at * a.ldd + col0 + c] : 1.0)) : 0.0;
+            }
+        }
+}
+
+// Rows of A for the columns col0 .. of the block: observation o's sum over its positions p of
+// w_p H[pos_grad[p]], in position order, one wave per observation and 64 columns (one column per
+// lane); an observation of more than LONG_OBS positions is cut into four runs, one per wave,
+// added in order.
+constexpr int LONG_OBS = 64;
+__global__ __launch_bounds__(256) void obs_sum_kernel(KnmArgs a, int64_t n_obs, int64_t n_pos, int64_t col0, int w,
+                                                      const double *__restrict__ H)
+{
+    __shared__ double part[4][64];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int64_t o0 = 4 * (int64_t)blockIdx.x;
+    const int64_t c = 64 * (int64_t)blockIdx.y + lane;
+    const bool in = c < w && col0 + c < a.M;
+    const double *Hc = H + (in ? c : 0);
+    auto run = [&](int64_t lo, int64_t hi) {
+        double s = 0.0;
+        for (int64_t p0 = lo; p0 < hi; p0 += 64) {
+            // 64 positions' rows and weights at once, one per lane; then rows of H in flight 16 (8, 4) at a time
+            const int cnt = (int)(hi - p0 < 64 ? hi - p0 : 64);
+            int64_t g = lane < cnt ? a.pos_grad[p0 + lane] : 0;
+            const bool ok = g >= 0 && g < a.n_grad;
+            const double wt = lane < cnt && ok ? a.pos_weight[p0 + lane] : 0.0;
+            const int row = ok ? (int)g : 0;
+            auto rows = [&](int p, auto n) {
+                double v[decltype(n)::value];
+#pragma unroll
+                for (int k = 0; k < decltype(n)::value; ++k)
+                    v[k] = Hc[(int64_t)__builtin_amdgcn_readlane(row, p + k) * w];
+#pragma unroll
+                for (int k = 0; k < decltype(n)::value; ++k)
+                    s += readlane_d(wt, p + k) * v[k];
+            };
+            int p = 0;
+            for (; p + 16 <= cnt; p += 16)
+                rows(p, std::integral_constant<int, 16>());
+            if (p + 8 <= cnt) {
+                rows(p, std::integral_constant<int, 8>());
+                p += 8;
+            }
+            if (p + 4 <= cnt) {
+                rows(p, std::integral_constant<int, 4>());
+                p += 4;
+            }
+            for (; p < cnt; ++p)
+                rows(p, std::integral_constant<int, 1>());
+        }
+        return s;
+    };
+    auto emit = [&](int64_t o, double s) {
+        if (in)
+            a.out[(col0 + c) * a.ldo + a.row_off + o] = s / a.sigma[o];
+    };
+    if (blockIdx.x == 0 && threadIdx.x == 0 && (a.offsets[0] != 0 || a.offsets[n_obs] != n_pos))
+        set_status(a.status, DST_EINVAL);
+    for (int k = 0; k < 4; ++k) {
+        const int64_t o = o0 + k;
+        if (o >= n_obs)
+            break;
+        const int64_t lo = a.offsets[o], hi = a.offsets[o + 1];
+        if (lo < 0 || hi < lo || hi > n_pos) {
+            if (threadIdx.x == 0)
+                set_status(a.status, DST_EINVAL);
+            continue;
+        }
+        if (col0 == 0 && blockIdx.y == 0)  // the positions' indices, checked once
+            for (int64_t p = lo + threadIdx.x; p < hi; p += 256)
+                if (!kdm_valid(a, p))
+                    set_status(a.status, DST_EINVAL);
+        if (hi - lo <= LONG_OBS) {
+            if (wave == k)
+                emit(o, run(lo, hi));
+        } else {
+            const int64_t q = (hi - lo + 3) / 4;
+            const int64_t l = lo + wave * q < hi ? lo + wave * q : hi, h = l + q < hi ? l + q : hi;
+            part[wave][lane] = run(l, h);
+            __syncthreads();
+            if (wave == 0)
+                emit(o, (part[0][lane] + part[1][lane]) + (part[2][lane] + part[3][lane]));
+            __syncthreads();
+        }
+    }
+}
+
 // The K_NM of several fits in one grid: fit i owns workgroups [base[i], base[i+1]).
 template <int BN>
 __global__ __launch_bounds__(KNM_NT, 2) void knm_group_kernel(KnmGroup g)
@@ -915,6 +1058,37 @@ hipError_t launch_knm_group(const KnmArgs *fits, const int64_t *max_tiles, int n
                 flush();
         }
         flush();
+    }
+    return hipGetLastError();
+}
+
+// Columns per block of the two-step derivative rows with `room` doubles of scratch; 0: use the
+// position tiles (too little room for 32 columns, or more gradient rows than positions).
+int kdm_block_cols(int64_t n_grad, int64_t n_pos, int64_t M, int64_t room)
+{
+    if (n_grad > n_pos || n_grad > INT32_MAX)
+        return 0;
+    for (int w : {256, 128, 96, 64, 32})
+        if (n_grad * w <= room && (w == 32 || w < 2 * M))
+            return w;
+    return 0;
+}
+
+hipError_t launch_kdm_blocks(const KnmArgs &a, int64_t n_obs, int64_t n_pos, int w, double *H, hipStream_t s)
+{
+    auto rows = [&](auto tile, int64_t col0) {
+        using S = decltype(tile);
+        const int64_t tiles = (a.n_grad + S::BM - 1) / S::BM * ((w + S::BN - 1) / S::BN);
+        hipLaunchKernelGGL(grad_rows_kernel<S>, dim3((unsigned)((tiles + 7) & ~int64_t(7))), dim3(S::NT), 0, s, a, col0,
+                           w, H);
+    };
+    for (int64_t col0 = 0; col0 < a.M; col0 += w) {
+        if (w == 96)
+            rows(GradTile<96>(), col0);
+        else
+            rows(GradTile<64>(), col0);
+        hipLaunchKernelGGL(obs_sum_kernel, dim3((unsigned)((n_obs + 3) / 4), (unsigned)((w + 63) / 64)), dim3(256), 0, s,
+                           a, n_obs, n_pos, col0, w, (const double *)H);
     }
     return hipGetLastError();
 }
