@@ -20,9 +20,14 @@
 
 namespace gap {
 
-using CS = TileShape<128, 128, 16, 2, 2>;  // Gram blocks and projection tiles
-constexpr int CUR_NB = 128;                // block of G / column tile of Y
-constexpr int64_t CUR_MAX_CHUNKS = 64;     // row chunks of the Gram product
+// Gram blocks of 64 x 64 (d = 400 pads to 448 columns; 128-wide blocks would pad to 512) and
+// projection tiles of 128 rows x 64 columns.
+using CG = MTile<double, 64, 64, 16, 2, 2>;
+using CP = KTile<double, 128, 64, 4, 2, 2>;
+constexpr int CUR_GB = 64;                 // block of G
+constexpr int CUR_NB = 128;                // columns of Y whose squares one workgroup sums
+constexpr int64_t CUR_MAX_CHUNKS = 64;     // row chunks the partials' space is sized for (128-wide blocks)
+constexpr int64_t CUR_PLACES = 1024;       // Gram workgroups resident at once (four per CU)
 constexpr int CUR_SEL_NT = 256;
 constexpr int CUR_SEL_PER = 4096;          // keys per workgroup in the compaction
 constexpr int CUR_MAX_D = 4096;
@@ -86,71 +91,96 @@ DEV void cur_pair(int64_t bp, int64_t nb, int64_t &bi, int64_t &bj)
     bj = bi + rem;
 }
 
-// v = X[r][c0 .. c0 + LEN) (zero past the row's end or for r >= r_hi).
-template <int LEN>
-DEV void cur_row_run(const double *__restrict__ X, int64_t r, int64_t r_hi, int d, int64_t c0, bool even,
-                     double (&v)[LEN])
+// Row chunks of the Gram product: what the partials' space holds, rounded down to whole rounds
+// of resident workgroups, at least 256 rows each.
+int64_t cur_gram_chunks(int64_t n, int d)
 {
-    if (r < r_hi && even && c0 + LEN <= d) {
-        load_run(X + r * d + c0, v);
-    } else {
-#pragma unroll
-        for (int e = 0; e < LEN; ++e)
-            v[e] = (r < r_hi && c0 + e < d) ? X[r * d + c0 + e] : 0.0;
-    }
+    const int64_t nb = cur_nb(d), room = cur_chunks(n, d) * (nb * (nb + 1) / 2) * CUR_NB * CUR_NB;
+    const int64_t gb = (d + CUR_GB - 1) / CUR_GB, pairs = gb * (gb + 1) / 2;
+    int64_t nch = room / (pairs * CUR_GB * CUR_GB);
+    if (nch * pairs > CUR_PLACES)
+        nch = nch * pairs / CUR_PLACES * CUR_PLACES / pairs;
+    if (nch > (n + 255) / 256)
+        nch = (n + 255) / 256;
+    return nch < 1 ? 1 : nch;
 }
 
-// Partial Gram block (bi, bj) over the rows of chunk blockIdx.y:
-// part[ch][bp][p][q] = sum_r X[r][128 bi + p] X[r][128 bj + q].
-__global__ __launch_bounds__(256, 2) void cur_gram_kernel(const double *__restrict__ X, int64_t n, int d,
-                                                          int64_t nb, int64_t chunk, double *__restrict__ part)
+// Partial Gram block (bi, bj) over the rows of a chunk:
+// part[ch][bp][p][q] = sum_r X[r][64 bi + p] X[r][64 bj + q].  Bound by the matrix cores; a
+// chunk's blocks run on one XCD, which then reads the chunk's rows once.  1e6 x 400:
+// 3.4 ms, 8.0 with 128 x 128 blocks on K-major stages filled through registers.
+__global__ __launch_bounds__(CG::NT, 4) void cur_gram_kernel(const double *__restrict__ X, int64_t n, int d,
+                                                             int64_t gb, int64_t nch, int64_t chunk,
+                                                             double *__restrict__ part)
 {
-    __shared__ double lds[2 * CS::STAGE];
-    const int64_t bp = blockIdx.x, ch = blockIdx.y, pairs = gridDim.x;
+    using S = CG;
+    __shared__ __align__(16) d2 lds[2 * S::UNITS];
+    const int64_t pairs = gb * (gb + 1) / 2, total = pairs * nch;
+    const int64_t lw = xcd_remap(blockIdx.x, (total + 7) & ~int64_t(7));
+    if (lw >= total)
+        return;
+    const int64_t ch = lw / pairs, bp = lw % pairs;
     int64_t bi, bj;
-    cur_pair(bp, nb, bi, bj);
-    const int64_t p0 = bi * CUR_NB, q0 = bj * CUR_NB;
+    cur_pair(bp, gb, bi, bj);
     const int64_t rlo = ch * chunk;
     const int64_t rhi = (rlo + chunk) < n ? (rlo + chunk) : n;
-    d4 acc[CS::FM][CS::FN];
-    zero_acc<CS>(acc);
+    d4 acc[S::FM][S::FN];
+    ktile_zero<S>(acc);
     if (rlo < rhi) {
-        constexpr int VA = CS::BM * CS::BK / CS::NT, VB = CS::BN * CS::BK / CS::NT;
-        const bool even = (d & 1) == 0;
-        // runs along the descriptor index (contiguous in a row of X)
-        auto fa = [&](int p, int64_t k, double (&v)[VA]) { cur_row_run<VA>(X, rlo + k, rhi, d, p0 + p, even, v); };
-        auto fb = [&](int q, int64_t k, double (&v)[VB]) { cur_row_run<VB>(X, rlo + k, rhi, d, q0 + q, even, v); };
-        gemm_tile_runs<CS, false, false>(acc, lds, rhi - rlo, fa, fb);
+        const int len = (int)(rhi - rlo), nk = (len + S::BK - 1) / S::BK;
+        const double *src[S::LPT];
+        int64_t step[S::LPT];
+        int64_t col[S::LPT];
+#pragma unroll
+        for (int i = 0; i < S::LPT; ++i) {
+            const int x = S::unit_x(i);
+            const int64_t c = x < S::UA ? bi * CUR_GB + 2 * x : bj * CUR_GB + 2 * (x - S::UA);
+            col[i] = c;
+            // columns past d repeat column 0 of the row and are not used
+            src[i] = X + (rlo + S::unit_p(i)) * (int64_t)d + (c < d ? c : 0);
+            step[i] = (int64_t)S::BK * d;
+        }
+        mtile_product<S>(acc, lds, nk, rows_aligned16(X, d) ? len / S::BK : 0, src, step, [&](int kt, int i) {
+            const int64_t r = rlo + (int64_t)kt * S::BK + S::unit_p(i);
+            const double *p = X + (r < rhi ? r : rlo) * (int64_t)d + (col[i] < d ? col[i] : 0);
+            d2 v;
+            v.x = p[0];
+            v.y = p[col[i] + 1 < d ? 1 : 0];
+            if (r >= rhi)
+                v = d2{0.0, 0.0};
+            return v;
+        });
     }
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int wm = wave / CS::WN, wn = wave % CS::WN;
-    double *P = part + (ch * pairs + bp) * (int64_t)(CUR_NB * CUR_NB);
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, g = lane >> 4, rl = lane & 15;
+    const int wm = wave / S::WN, wn = wave % S::WN;
+    double *P = part + (ch * pairs + bp) * (int64_t)(CUR_GB * CUR_GB);
 #pragma unroll
-    for (int i = 0; i < CS::FM; ++i)
+    for (int i = 0; i < S::FM; ++i)
 #pragma unroll
-        for (int j = 0; j < CS::FN; ++j)
+        for (int j = 0; j < S::FN; ++j)
 #pragma unroll
             for (int e = 0; e < 4; ++e)
-                P[acc_row<CS>(wm, i, lane, e) * CUR_NB + acc_col<CS>(wn, j, lane, e)] = acc[i][j][e];
+                P[S::row(wm, i, g, e) * CUR_GB + S::col(wn, j, rl)] = acc[i][j][e];
 }
 
 // G (column-major, leading dimension d, both triangles) from the partials, the
 // chunks summed in order.  One element of one block pair per thread.
 __global__ __launch_bounds__(256) void cur_gram_sum_kernel(const double *__restrict__ part, int64_t nch,
-                                                           int64_t pairs, int64_t nb, int d, double *__restrict__ G)
+                                                           int64_t pairs, int64_t gb, int d, double *__restrict__ G)
 {
     const int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (e >= pairs * CUR_NB * CUR_NB)
+    if (e >= pairs * CUR_GB * CUR_GB)
         return;
-    const int64_t bp = e / (CUR_NB * CUR_NB), pq = e % (CUR_NB * CUR_NB);
+    const int64_t bp = e / (CUR_GB * CUR_GB), pq = e % (CUR_GB * CUR_GB);
     int64_t bi, bj;
-    cur_pair(bp, nb, bi, bj);
-    const int64_t p = bi * CUR_NB + pq / CUR_NB, q = bj * CUR_NB + pq % CUR_NB;
+    cur_pair(bp, gb, bi, bj);
+    const int64_t p = bi * CUR_GB + pq / CUR_GB, q = bj * CUR_GB + pq % CUR_GB;
     if (p >= d || q >= d)
         return;
     double s = 0.0;
+#pragma unroll 8
     for (int64_t ch = 0; ch < nch; ++ch)
-        s += part[(ch * pairs + bp) * (int64_t)(CUR_NB * CUR_NB) + pq];
+        s += part[(ch * pairs + bp) * (int64_t)(CUR_GB * CUR_GB) + pq];
     G[q * d + p] = s;
     G[p * d + q] = s;
 }
@@ -181,66 +211,61 @@ __global__ __launch_bounds__(256) void cur_trinv_kernel(const double *__restrict
     }
 }
 
-// Y = X W for the rows of tile blockIdx.x and the 128 columns of tile
-// blockIdx.y; rowpart[ct][r] = sum over the tile's columns of Y[r][q]^2, the
-// columns summed in order.
-__global__ __launch_bounds__(256, 2) void cur_proj_kernel(const double *__restrict__ X, int64_t n, int d,
-                                                          const double *__restrict__ W, double *__restrict__ rowpart)
+// Y = X W for 128 rows and the 64 columns of tile 2 ct + odd; rowpart[ct][r] = the sum of
+// Y[r][q]^2 over the tile's columns (a fixed order), added to the even tile's by the odd one's
+// launch.  A row tile's column tiles start together on one XCD and walk its rows of X in step,
+// so that they are read from HBM once per launch; both halves in one workgroup, one after
+// the other, read them at their own pace (1e6 x 400: 5.4 ms against 4.7; 6.0 on K-major
+// 128 x 128 tiles).
+__global__ __launch_bounds__(CP::NT, 3) void cur_proj_kernel(const double *__restrict__ X, int64_t n, int d,
+                                                             const double *__restrict__ W, int64_t nct, int odd,
+                                                             double *__restrict__ rowpart)
 {
-    __shared__ double lds[2 * CS::STAGE];
-    const int64_t r0 = (int64_t)blockIdx.x * CS::BM, ct = blockIdx.y, q0 = ct * CUR_NB;
-    const int64_t K = (q0 + CUR_NB) < d ? (q0 + CUR_NB) : d;  // W[k][q] = 0 for k > q
-    d4 acc[CS::FM][CS::FN];
-    zero_acc<CS>(acc);
-    constexpr int VA = CS::BM * CS::BK / CS::NT, VB = CS::BN * CS::BK / CS::NT;
-    const bool even = (d & 1) == 0;
-    auto fa = [&](int r, int64_t k, double (&v)[VA]) {  // X[r0 + r][k .. k + VA)
-        const int64_t row = r0 + r;
-        if (row < n && even && k + VA <= K) {
-            load_run(X + row * d + k, v);
-        } else {
+    using S = CP;
+    __shared__ __align__(16) d2 lds[2 * S::UNITS];
+    __shared__ double rsum[S::WN][S::BM];
+    const int64_t total = (n + S::BM - 1) / S::BM * nct;
+    const int64_t lw = xcd_remap(blockIdx.x, (total + 7) & ~int64_t(7));
+    if (lw >= total)
+        return;
+    const int64_t r0 = lw / nct * S::BM, ct = lw % nct, q0 = (2 * ct + odd) * S::BN;
+    const int t = threadIdx.x, lane = t & 63, wave = t >> 6, g = lane >> 4, rl = lane & 15;
+    const int wm = wave / S::WN, wn = wave % S::WN;
+    const int K = (int)((q0 + S::BN) < d ? (q0 + S::BN) : d);  // W[k][q] = 0 for k > q
+    const double *src[S::LPT];
 #pragma unroll
-            for (int e = 0; e < VA; ++e)
-                v[e] = (row < n && k + e < K) ? X[row * d + k + e] : 0.0;
-        }
-    };
-    auto fb = [&](int q, int64_t k, double (&v)[VB]) {  // W[k .. k + VB)[q0 + q], contiguous along k
-        const int64_t col = q0 + q;
-        if (col < d && even && k + VB <= K) {
-            load_run(W + col * d + k, v);
-        } else {
-#pragma unroll
-            for (int e = 0; e < VB; ++e)
-                v[e] = (col < d && k + e < K) ? W[col * d + k + e] : 0.0;
-        }
-    };
-    gemm_tile_runs<CS, true, true>(acc, lds, K, fa, fb);
-    // squares parked 64 columns at a time (the columns of waves wn = h), then
-    // thread r < 128 sums row r over them in column order
-    const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
-    const int wm = wave / CS::WN, wn = wave % CS::WN;
-    double *E = lds;  // [128][65]
-    double rs = 0.0;
-    for (int h = 0; h < CS::WN; ++h) {
-        if (wn == h) {
-#pragma unroll
-            for (int i = 0; i < CS::FM; ++i)
-#pragma unroll
-                for (int j = 0; j < CS::FN; ++j)
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        const int rr = acc_row<CS>(wm, i, lane, e), cc = acc_col<CS>(wn, j, lane, e) - h * CS::TN;
-                        E[rr * (CS::TN + 1) + cc] = acc[i][j][e] * acc[i][j][e];
-                    }
-        }
-        __syncthreads();
-        if (t < CS::BM)
-            for (int c = 0; c < CS::TN; ++c)
-                rs += E[t * (CS::TN + 1) + c];
-        __syncthreads();
+    for (int i = 0; i < S::LPT; ++i) {
+        const int r = S::unit_row(i);
+        // rows past n and columns past d repeat the last one; the columns count as zero below
+        const int64_t row = r < S::BM ? (r0 + r < n ? r0 + r : n - 1) : (q0 + r - S::BM < d ? q0 + r - S::BM : d - 1);
+        src[i] = (r < S::BM ? X : W) + row * (int64_t)d + S::unit_k(i);
     }
-    if (t < CS::BM && r0 + t < n)
-        rowpart[ct * n + r0 + t] = rs;
+    d4 acc[S::FM][S::FN];
+    ktile_zero<S>(acc);
+    ktile_product<S>(acc, lds, src, K, rows_aligned16(X, d) && rows_aligned16(W, d));
+#pragma unroll
+    for (int i = 0; i < S::FM; ++i)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            double s = 0.0;
+#pragma unroll
+            for (int j = 0; j < S::FN; ++j) {
+                const double y = q0 + acc_col<S>(wn, j, lane, e) < d ? acc[i][j][e] : 0.0;
+                s += y * y;
+            }
+            s += __shfl_xor(s, 1, 64);
+            s += __shfl_xor(s, 2, 64);
+            s += __shfl_xor(s, 4, 64);
+            s += __shfl_xor(s, 8, 64);
+            if (rl == 0)
+                rsum[wn][wm * S::TM + 16 * i + g + 4 * e] = s;
+        }
+    __syncthreads();
+    if (t < S::BM && r0 + t < n) {
+        double *out = rowpart + ct * n + r0 + t;
+        const double rs = rsum[0][t] + rsum[1][t];
+        *out = odd ? *out + rs : rs;
+    }
 }
 
 // lev = sum of the column tiles' parts in order; key = draw / lev (1 / lev
@@ -456,20 +481,25 @@ hipError_t launch_cur_select(const CurLaunch &c, hipStream_t s)
     unsigned *hist = reinterpret_cast<unsigned *>(ws + L.hist);
     long long *cnt = reinterpret_cast<long long *>(ws + L.cnt);
     long long *base = reinterpret_cast<long long *>(ws + L.base);
-    const int64_t nb = cur_nb(d), pairs = nb * (nb + 1) / 2, nch = cur_chunks(n, d);
+    const int64_t nb = cur_nb(d), gb = (d + CUR_GB - 1) / CUR_GB, pairs = gb * (gb + 1) / 2;
+    const int64_t nch = cur_gram_chunks(n, d);
     int64_t chunk = (n + nch - 1) / nch;
     chunk = (chunk + 15) / 16 * 16;
     hipLaunchKernelGGL(cur_select_init_kernel, dim3(1), dim3(256), 0, s, st, hist, (long long)c.M);
-    hipLaunchKernelGGL(cur_gram_kernel, dim3((unsigned)pairs, (unsigned)nch), dim3(256), 0, s, c.x, n, d, nb, chunk,
-                       part);
-    hipLaunchKernelGGL(cur_gram_sum_kernel, dim3((unsigned)((pairs * CUR_NB * CUR_NB + 255) / 256)), dim3(256), 0, s,
-                       part, nch, pairs, nb, d, G);
+    hipLaunchKernelGGL(cur_gram_kernel, dim3((unsigned)((pairs * nch + 7) & ~int64_t(7))), dim3(CG::NT), 0, s, c.x, n, d,
+                       gb, nch, chunk, part);
+    hipLaunchKernelGGL(cur_gram_sum_kernel, dim3((unsigned)((pairs * CUR_GB * CUR_GB + 255) / 256)), dim3(256), 0, s,
+                       part, nch, pairs, gb, d, G);
     hipError_t e = launch_potrf_upper(G, d, d, part, &st->status, s);
     if (e != hipSuccess)
         return e;
     hipLaunchKernelGGL(cur_trinv_kernel, dim3((unsigned)d), dim3(256), 0, s, G, d, W);
-    hipLaunchKernelGGL(cur_proj_kernel, dim3((unsigned)((n + CS::BM - 1) / CS::BM), (unsigned)nb), dim3(256), 0, s,
-                       c.x, n, d, W, rowpart);
+    for (int odd = 0; odd < 2; ++odd) {
+        const int64_t nct = (gb + 1 - odd) / 2, ptiles = (n + CP::BM - 1) / CP::BM * nct;
+        if (ptiles > 0)
+            hipLaunchKernelGGL(cur_proj_kernel, dim3((unsigned)((ptiles + 7) & ~int64_t(7))), dim3(CP::NT), 0, s, c.x, n,
+                               d, W, nct, odd, rowpart);
+    }
     hipLaunchKernelGGL(cur_keys_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, rowpart, n, nb, c.draws,
                        c.lev_out, keys);
     int64_t hg = (n + 255) / 256;
