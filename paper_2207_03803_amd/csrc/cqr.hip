@@ -13,12 +13,14 @@
 //
 // Four launches per panel, each one pass over its rows: the Gram matrix of P; then twice
 // a triangular solve of the rows together with the Gram matrix of the result; then the
-// last solve.  The Gram partials of the workgroups are summed by the last one of them to
-// arrive (in a fixed order, in two levels above 16 workgroups), which then factors the
-// 64 x 64 matrix that the next launch needs.  A panel of a few hundred to a few thousand
-// rows is bound by the latency of this chain: 456 rows take 23 + 30 + 59 + 8 us (387 us with
-// twelve launches, each 64 x 64 factorisation a chain of 64 steps on one wave), 7,000 rows
-// 156 us (400).
+// last solve, with R, T and tau formed on a workgroup beside it.  The Gram partials of the
+// workgroups are summed by the last one of them to arrive (in a fixed order, in two levels
+// above 16 workgroups), which then factors the 64 x 64 matrix that the next launch needs.
+// Bound by the latency of this chain: at 456 rows 20 + 25 + 44 + 12 us (of the first three, 9
+// us each for the Cholesky factorisation, 13 for the LU, 4 for an arrival and the sum), 387
+// us with twelve launches and chains of 64 steps on one wave; at 16,000 rows 36 + 43 + 58 +
+// 13 (8 us more for the rows' loads, 10 for the second level of sums).  Workgroups of 256
+// threads and 64-row steps took 41 + 47 + 70 + 12 there.
 #include "kernels.h"
 #include "small64.h"
 
@@ -26,26 +28,31 @@ namespace gap {
 
 constexpr int CB = QR_NB;        // panel width bound (64)
 static_assert(CB == S64, "panel blocks");
-constexpr int CQ_ROWS = 64;      // rows per workgroup and step (16 per wave)
+constexpr int CQ_NT = 512;       // threads of a workgroup; the 64 x 64 factorisations take the first 256
+constexpr int CQ_ROWS = CQ_NT / 4;  // rows per workgroup and step (16 per wave)
+constexpr int DT = CQ_ROWS + 2;  // LDS row stride of the transposed tile (free of bank conflicts like DL)
 constexpr int CQ_GRP = 16;       // workgroups of one first-level sum
+constexpr int NENT = NBLK * BLK / CQ_NT;  // entries of a partial Gram matrix per thread
 static_assert(CQ_WGS * NBLK * BLK == CQ_PART && CQ_WGS / CQ_GRP < CQ_COUNTERS, "partials and counters");
+static_assert(NENT * CQ_NT == NBLK * BLK, "whole entries");
 
 enum CqStep { CQ_GRAM, CQ_PASS1, CQ_PASS2, CQ_PASS3 };
 
 struct CqArgs {
     QrWork w;
-    int64_t j0, rows, chunk;  // panel column, its rows, rows per workgroup (a multiple of CQ_ROWS)
+    int64_t j0, rows, chunk;  // panel column, its rows, rows per workgroup (64, or a multiple of CQ_ROWS)
     int pw;
     double shift;
     double *Tout;
 };
 
 struct CqLds {
-    double A[S64][DL];   // the rows' transposed tile; then the 64 x 64 matrix being factored
-    double B[S64][DL];   // the packed triangle; then Q_top and its LU
+    double tile[S64 * DT];  // the rows' transposed tile; then the 64 x 64 matrix being factored
+    double B[S64][DL];      // the packed triangle; then Q_top and its LU
     double T[4][16][17];
     double sg[S64];
     int flag, ok;
+    DEV double (*A())[DL] { return reinterpret_cast<double (*)[DL]>(tile); }
 };
 static_assert(PACK <= S64 * DL, "a packed triangle fits a matrix buffer");
 
@@ -77,21 +84,24 @@ DEV void store_rows(const d4 (&y)[4], T *dst, int64_t ld, int64_t row, int64_t r
         }
 }
 
-// Sum of the workgroups' partial Gram blocks in the last workgroup to arrive: entry t of
-// block idx in v[idx].  True there.
-DEV bool sum_partials(double *part, unsigned *counters, double (&v)[NBLK], int *flag)
+// Sum of the workgroups' partial Gram blocks in the last workgroup to arrive: entry
+// t + CQ_NT q in v[q].  True there.  All loads of a group are in flight together.
+DEV bool sum_partials(double *part, unsigned *counters, double (&v)[NENT], int *flag)
 {
     const int t = threadIdx.x, n = (int)gridDim.x, ch = (int)blockIdx.x;
     auto add = [&](int first, int count, int step) {
+        double x[CQ_GRP][NENT];
 #pragma unroll
-        for (int idx = 0; idx < NBLK; ++idx)
-            v[idx] = 0.0;
-#pragma unroll 4
-        for (int q = 0; q < count; ++q) {
-            const double *p = part + (int64_t)(first + q * step) * (NBLK * BLK) + t;
+        for (int q = 0; q < CQ_GRP; ++q)
 #pragma unroll
-            for (int idx = 0; idx < NBLK; ++idx)
-                v[idx] += p[idx * BLK];
+            for (int i = 0; i < NENT; ++i)
+                x[q][i] = q < count ? part[(int64_t)(first + q * step) * (NBLK * BLK) + i * CQ_NT + t] : 0.0;
+#pragma unroll
+        for (int i = 0; i < NENT; ++i) {
+            v[i] = 0.0;
+#pragma unroll
+            for (int q = 0; q < CQ_GRP; ++q)
+                v[i] += x[q][i];
         }
     };
     if (n <= CQ_GRP) {
@@ -106,59 +116,66 @@ DEV bool sum_partials(double *part, unsigned *counters, double (&v)[NBLK], int *
         return false;
     add(g0, gn, 1);
 #pragma unroll
-    for (int idx = 0; idx < NBLK; ++idx)
-        part[(int64_t)g0 * (NBLK * BLK) + idx * BLK + t] = v[idx];
+    for (int i = 0; i < NENT; ++i)
+        part[(int64_t)g0 * (NBLK * BLK) + i * CQ_NT + t] = v[i];
     if (!arrive_last(counters, ngrp, flag))
         return false;
     add(0, ngrp, CQ_GRP);
     return true;
 }
+static_assert(CQ_WGS / CQ_GRP <= CQ_GRP, "second level");
 
-// The summed Gram matrix into S (upper blocks; identity beyond pw, shift_coef * trace on the
-// diagonal) and its Cholesky factor in place.
-DEV void factor_gram(const double (&v)[NBLK], int pw, double shift_coef, CqLds &L, int32_t *status)
+// The summed Gram matrix into L.A() (upper blocks; identity beyond pw, shift_coef * trace on
+// the diagonal); 256 threads carry on, the others have returned false.
+DEV bool place_gram(const double (&v)[NENT], int pw, double shift_coef, CqLds &L)
 {
-    const int t = threadIdx.x, i0 = t >> 4, j0 = t & 15;
+    const int t = threadIdx.x;
+    double(*A)[DL] = L.A();
 #pragma unroll
-    for (int idx = 0; idx < NBLK; ++idx) {
-        const int c = blk_col(idx), b = idx - c * (c + 1) / 2;
-        const int i = 16 * b + i0, l = 16 * c + j0;
-        L.A[i][l] = (i < pw && l < pw) ? v[idx] : (i == l ? 1.0 : 0.0);
+    for (int q = 0; q < NENT; ++q) {
+        const int idx = (q * CQ_NT + t) >> 8, c = blk_col(idx), b = idx - c * (c + 1) / 2;
+        const int i = 16 * b + ((t >> 4) & 15), l = 16 * c + (t & 15);
+        A[i][l] = (i < pw && l < pw) ? v[q] : (i == l ? 1.0 : 0.0);
     }
     if (t == 0)
         L.ok = 1;
     __syncthreads();
-    if (shift_coef != 0.0 && t < 64) {
-        const double d = (t < pw) ? L.A[t][t] : 0.0;
-        const double tr = wave_sum(d);
-        if (t < pw)
-            L.A[t][t] = d + shift_coef * tr;
+    if (t >= 256)
+        return false;
+    if (shift_coef != 0.0) {
+        if (t < 64) {
+            const double d = (t < pw) ? A[t][t] : 0.0;
+            const double tr = wave_sum(d);
+            if (t < pw)
+                A[t][t] = d + shift_coef * tr;
+        }
+        __syncthreads();
     }
-    __syncthreads();
-    chol64(L.A, &L.ok);
-    if (t == 0 && !L.ok)
-        set_status(status, DST_ERANK);
+    return true;
 }
 
 DEV void copy_pack(double *dst, const double *src)
 {
-    for (int e = threadIdx.x; e < PACK; e += 256)
-        dst[e] = src[e];
+    static_assert(PACK % CQ_NT == 0, "whole rounds");
+    double v[PACK / CQ_NT];
+#pragma unroll
+    for (int q = 0; q < PACK / CQ_NT; ++q)
+        v[q] = src[q * CQ_NT + threadIdx.x];
+#pragma unroll
+    for (int q = 0; q < PACK / CQ_NT; ++q)
+        dst[q * CQ_NT + threadIdx.x] = v[q];
     __syncthreads();
 }
 
-// After the second pass: R3 = chol(G), Q_top = Q2[0:pw] R3^-1, LU of Q_top - S, the compact-WY
-// T, R = S R3 R2 R1 and Y1 into the panel's top block, tau, and U R3 for the last pass.
-template <class T>
-DEV void panel_top(const CqArgs &a, CqLds &L)
+// Once R3 = chol(G) is in L.A() and packed in L.B, with this wave's rows of Q2 in y: Q_top =
+// Q2[0:pw] R3^-1, the LU of Q_top - S, and U R3 for the last pass.  LU, R3 and S go to cq_G
+// for panel_rest.
+DEV void panel_top(const CqArgs &a, CqLds &L, d4 (&y)[4])
 {
     const QrWork &w = a.w;
     const int pw = a.pw, t = threadIdx.x, lane = t & 63, wave = t >> 6, g = lane >> 4, r = lane & 15;
-    double *P = &L.B[0][0], *R21 = w.cq_R + 2 * CB * CB;
-    pack_upper([&](int i, int j) { return L.A[i][j]; }, P, L.T);
-    d4 y[4];
-    load_rows(y, (const double *)w.cq_S, w.cq_ld, 16 * wave + r, (int64_t)pw, pw);
-    solve_rows<false>(y, P);
+    double(*A)[DL] = L.A();
+    solve_rows<false>(y, &L.B[0][0]);
     __syncthreads();
 #pragma unroll
     for (int c = 0; c < 4; ++c)
@@ -167,8 +184,14 @@ DEV void panel_top(const CqArgs &a, CqLds &L)
             L.B[16 * wave + r][16 * c + 4 * e + g] = y[c][e];
     __syncthreads();
     lu64_signs(L.B, L.sg, pw);
-    // R = S R3 (R2 R1) and U R3: blocks wave, wave + 4, wave + 8 of their upper triangles
-    T *Ap = ((sizeof(T) == 8) ? reinterpret_cast<T *>(w.A) : reinterpret_cast<T *>(w.A32)) + a.j0 * w.lda + a.j0;
+#pragma unroll
+    for (int q = 0; q < CB * CB / 256; ++q) {
+        const int e = q * 256 + t;
+        w.cq_G[CB * CB + e] = L.B[e >> 6][e & 63];
+        w.cq_G[2 * CB * CB + e] = A[e >> 6][e & 63];
+    }
+    if (t < CB)
+        w.cq_G[3 * CB * CB + t] = L.sg[t];
     d4 ur[3];
 #pragma unroll
     for (int q = 0; q < 3; ++q) {
@@ -176,11 +199,79 @@ DEV void panel_top(const CqArgs &a, CqLds &L)
         if (idx >= NBLK)
             break;
         const int c = blk_col(idx), b = idx - c * (c + 1) / 2;
-        const d4 rc = upper_product_block(
-            b, c, [&](int i, int k) { return L.A[i][k]; },
-            [&](int k, int j) { return R21[blk_at(k >> 4, c) * BLK + (k & 15) * 16 + (j & 15)]; });
         ur[q] = upper_product_block(
-            b, c, [&](int i, int k) { return i <= k ? L.B[i][k] : 0.0; }, [&](int k, int j) { return L.A[k][j]; });
+            b, c, [&](int i, int k) { return i <= k ? L.B[i][k] : 0.0; }, [&](int k, int j) { return A[k][j]; });
+    }
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {
+        const int idx = wave + 4 * q;
+        if (idx >= NBLK)
+            break;
+        const int c = blk_col(idx), b = idx - c * (c + 1) / 2;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const int i = 16 * b + g + 4 * e, j = 16 * c + r;
+            A[i][j] = (i < pw && j < pw) ? ur[q][e] : (i == j ? 1.0 : 0.0);
+        }
+    }
+    __syncthreads();
+    pack_upper([&](int i, int j) { return A[i][j]; }, w.cq_R + 3 * CB * CB, L.T);
+}
+
+// What the last pass does not wait for, on a workgroup of its own beside it: R = S R3 (R2 R1)
+// and Y1 into the panel's top block, the compact-WY T = -U S Y1^-T, and tau.
+template <class T>
+DEV void panel_rest(const CqArgs &a, CqLds &L)
+{
+    const QrWork &w = a.w;
+    const int pw = a.pw, t = threadIdx.x, lane = t & 63, wave = t >> 6, g = lane >> 4, r = lane & 15;
+    double(*A)[DL] = L.A();
+    const double *R21 = w.cq_R + 2 * CB * CB;
+    double lu[CB * CB / CQ_NT], r3[CB * CB / CQ_NT];
+#pragma unroll
+    for (int q = 0; q < CB * CB / CQ_NT; ++q) {
+        lu[q] = w.cq_G[CB * CB + q * CQ_NT + t];
+        r3[q] = w.cq_G[2 * CB * CB + q * CQ_NT + t];
+    }
+    d4 r21[3][4];  // the blocks of R2 R1 that this wave's products take
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {
+        const int idx = wave + 4 * q;
+        if (wave < 4 && idx < NBLK) {
+            const int c = blk_col(idx), b = idx - c * (c + 1) / 2;
+#pragma unroll
+            for (int k = 0; k < 4; ++k)
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    r21[q][k][e] = (k >= b && k <= c) ? R21[blk_at(k, c) * BLK + (4 * e + g) * 16 + r] : 0.0;
+        }
+    }
+    if (t < CB)
+        L.sg[t] = w.cq_G[3 * CB * CB + t];
+#pragma unroll
+    for (int q = 0; q < CB * CB / CQ_NT; ++q) {
+        const int e = q * CQ_NT + t;
+        L.B[e >> 6][e & 63] = lu[q];
+        A[e >> 6][e & 63] = r3[q];
+    }
+    __syncthreads();
+    if (t >= 256)
+        return;
+    T *Ap = ((sizeof(T) == 8) ? reinterpret_cast<T *>(w.A) : reinterpret_cast<T *>(w.A32)) + a.j0 * w.lda + a.j0;
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {
+        const int idx = wave + 4 * q;
+        if (idx >= NBLK)
+            break;
+        const int c = blk_col(idx), b = idx - c * (c + 1) / 2;
+        d4 rc = d4{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+            if (k >= b && k <= c)
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    rc = mfma16(A[16 * b + r][16 * k + 4 * e + g], r21[q][k][e], rc);
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
             const int i = 16 * b + g + 4 * e, j = 16 * c + r;
@@ -189,15 +280,17 @@ DEV void panel_top(const CqArgs &a, CqLds &L)
         }
     }
     // Y1 below the diagonal
-    for (int e = t; e < CB * CB; e += 256) {
-        const int i = e & 63, j = e >> 6;
+#pragma unroll
+    for (int q = 0; q < CB * CB / 256; ++q) {
+        const int e = q * 256 + t, i = e & 63, j = e >> 6;
         if (i > j && i < pw)
             Ap[j * w.lda + i] = (T)L.B[i][j];
     }
     __syncthreads();
     // T = -U S Y1^-T: rows of -U S times the inverse of Y1^T (unit upper)
-    double *P1 = &L.A[0][0];
+    double *P1 = L.tile;
     pack_upper([&](int i, int j) { return i == j ? 1.0 : ((j < pw) ? L.B[j][i] : 0.0); }, P1, L.T);
+    d4 y[4];
 #pragma unroll
     for (int c = 0; c < 4; ++c)
 #pragma unroll
@@ -216,34 +309,26 @@ DEV void panel_top(const CqArgs &a, CqLds &L)
             if (i == j && i < pw)
                 w.tau[a.j0 + i] = tv;
         }
-    __syncthreads();
-#pragma unroll
-    for (int q = 0; q < 3; ++q) {
-        const int idx = wave + 4 * q;
-        if (idx >= NBLK)
-            break;
-        const int c = blk_col(idx), b = idx - c * (c + 1) / 2;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const int i = 16 * b + g + 4 * e, j = 16 * c + r;
-            L.A[i][j] = (i < pw && j < pw) ? ur[q][e] : (i == j ? 1.0 : 0.0);
-        }
-    }
-    __syncthreads();
-    pack_upper([&](int i, int j) { return L.A[i][j]; }, w.cq_R + 3 * CB * CB, L.T);
 }
 
 // One pass over the panel's rows (see CqStep).  TS: what it reads, TD: what it writes, T: the
 // factored matrix's storage.
 template <int STEP, class TS, class TD, class T>
-__global__ __launch_bounds__(256, 2) void cqr_step_kernel(CqArgs a, const TS *src, int64_t lds_, TD *dst,
-                                                          int64_t ldd)
+__global__ __launch_bounds__(CQ_NT) void cqr_step_kernel(CqArgs a, const TS *src, int64_t lds_, TD *dst, int64_t ldd)
 {
     __shared__ CqLds L;
     const QrWork &w = a.w;
     const int pw = a.pw;
     const int t = threadIdx.x, lane = t & 63, wave = t >> 6, g = lane >> 4, r = lane & 15;
-    const int64_t lo = (int64_t)blockIdx.x * a.chunk;
+    int64_t wg = blockIdx.x;
+    if constexpr (STEP == CQ_PASS3) {
+        if (wg == 0) {
+            panel_rest<T>(a, L);
+            return;
+        }
+        --wg;
+    }
+    const int64_t lo = wg * a.chunk;
     const int64_t hi = (lo + a.chunk) < a.rows ? (lo + a.chunk) : a.rows;
     double *P = &L.B[0][0];
     double *pack_in = w.cq_R + (STEP == CQ_PASS1 ? 0 : (STEP == CQ_PASS2 ? 1 : 3)) * CB * CB;
@@ -251,10 +336,7 @@ __global__ __launch_bounds__(256, 2) void cqr_step_kernel(CqArgs a, const TS *sr
     load_rows(nxt, src, lds_, lo + 16 * wave + r, hi, pw);
     if constexpr (STEP != CQ_GRAM)
         copy_pack(P, pack_in);
-    d4 acc[3];
-#pragma unroll
-    for (int q = 0; q < 3; ++q)
-        acc[q] = d4{0.0, 0.0, 0.0, 0.0};
+    d4 acc[2] = {d4{0.0, 0.0, 0.0, 0.0}, d4{0.0, 0.0, 0.0, 0.0}};  // Gram blocks wave, wave + 8
     for (int64_t r0 = lo; r0 < hi; r0 += CQ_ROWS) {
         const int64_t row = r0 + 16 * wave + r;
 #pragma unroll
@@ -262,7 +344,8 @@ __global__ __launch_bounds__(256, 2) void cqr_step_kernel(CqArgs a, const TS *sr
             y[c] = nxt[c];
         if (r0 + CQ_ROWS < hi)
             load_rows(nxt, src, lds_, row + CQ_ROWS, hi, pw);
-        if constexpr (STEP != CQ_GRAM) {
+        const int nr = (int)((hi - r0) < CQ_ROWS ? (hi - r0) : CQ_ROWS);
+        if (STEP != CQ_GRAM && 16 * wave < nr) {
             solve_rows<STEP == CQ_PASS1>(y, P);
             // the last pass leaves the top block (rows below pw) to the reconstruction
             store_rows(y, dst, ldd, row, STEP == CQ_PASS3 ? (int64_t)pw : (int64_t)0, hi, pw);
@@ -273,37 +356,43 @@ __global__ __launch_bounds__(256, 2) void cqr_step_kernel(CqArgs a, const TS *sr
             for (int c = 0; c < 4; ++c)
 #pragma unroll
                 for (int e = 0; e < 4; ++e)
-                    L.A[16 * c + 4 * e + g][16 * wave + r] = y[c][e];
+                    L.tile[(16 * c + 4 * e + g) * DT + 16 * wave + r] = y[c][e];
             __syncthreads();
 #pragma unroll
-            for (int q = 0; q < 3; ++q) {
-                const int idx = wave + 4 * q;
+            for (int q = 0; q < 2; ++q) {
+                const int idx = wave + 8 * q;
                 if (idx < NBLK) {
                     const int c = blk_col(idx), b = idx - c * (c + 1) / 2;
+                    const double *Ta = L.tile + (16 * b + r) * DT + g, *Tb = L.tile + (16 * c + r) * DT + g;
+                    for (int k = 0; k < nr; k += 64)  // rows past nr are zero
 #pragma unroll
-                    for (int k = 0; k < CQ_ROWS / 4; ++k)
-                        acc[q] = mfma16(L.A[16 * b + r][4 * k + g], L.A[16 * c + r][4 * k + g], acc[q]);
+                        for (int kk = 0; kk < 64; kk += 4)
+                            acc[q] = mfma16(Ta[k + kk], Tb[k + kk], acc[q]);
                 }
             }
         }
     }
     if constexpr (STEP != CQ_PASS3) {
 #pragma unroll
-        for (int q = 0; q < 3; ++q) {
-            const int idx = wave + 4 * q;
+        for (int q = 0; q < 2; ++q) {
+            const int idx = wave + 8 * q;
             if (idx < NBLK)
 #pragma unroll
                 for (int e = 0; e < 4; ++e)
                     w.cq_part[(int64_t)blockIdx.x * (NBLK * BLK) + idx * BLK + (g + 4 * e) * 16 + r] = acc[q][e];
         }
-        double v[NBLK];
+        double v[NENT];
         if (!sum_partials(w.cq_part, w.cq_counters, v, &L.flag))
             return;
-        factor_gram(v, pw, STEP == CQ_GRAM ? a.shift : 0.0, L, w.status);
-        if constexpr (STEP == CQ_GRAM) {
-            pack_upper([&](int i, int j) { return L.A[i][j]; }, w.cq_R, L.T);
-        } else if constexpr (STEP == CQ_PASS1) {
-            pack_upper([&](int i, int j) { return L.A[i][j]; }, w.cq_R + CB * CB, L.T);
+        if (!place_gram(v, pw, STEP == CQ_GRAM ? a.shift : 0.0, L))
+            return;
+        if constexpr (STEP == CQ_PASS2)  // the top rows, on their way during the factorisation
+            load_rows(y, (const double *)w.cq_S, w.cq_ld, 16 * wave + r, (int64_t)pw, pw);
+        double(*A)[DL] = L.A();
+        chol64(A, STEP == CQ_PASS2 ? P : w.cq_R + (STEP == CQ_GRAM ? 0 : CB * CB), &L.ok);
+        if (t == 0 && !L.ok)
+            set_status(w.status, DST_ERANK);
+        if constexpr (STEP == CQ_PASS1) {
             // R2 R1 (R1 is the pack this pass solved with, still in P)
 #pragma unroll
             for (int q = 0; q < 3; ++q) {
@@ -311,15 +400,15 @@ __global__ __launch_bounds__(256, 2) void cqr_step_kernel(CqArgs a, const TS *sr
                 if (idx < NBLK) {
                     const int c = blk_col(idx), b = idx - c * (c + 1) / 2;
                     const d4 p = upper_product_block(
-                        b, c, [&](int i, int k) { return L.A[i][k]; },
+                        b, c, [&](int i, int k) { return A[i][k]; },
                         [&](int k, int j) { return P[blk_at(k >> 4, c) * BLK + (k & 15) * 16 + (j & 15)]; });
 #pragma unroll
                     for (int e = 0; e < 4; ++e)
                         w.cq_R[2 * CB * CB + idx * BLK + (g + 4 * e) * 16 + r] = p[e];
                 }
             }
-        } else {
-            panel_top<T>(a, L);
+        } else if constexpr (STEP == CQ_PASS2) {
+            panel_top(a, L, y);
         }
     }
 }
@@ -335,21 +424,21 @@ static void cqr_panel(const QrWork &w, int64_t j0, int pw, double *Tout, hipStre
     a.rows = mk;
     a.pw = pw;
     a.chunk = (mk + CQ_WGS - 1) / CQ_WGS;
-    a.chunk = (a.chunk + CQ_ROWS - 1) / CQ_ROWS * CQ_ROWS;
+    // 64 rows per workgroup while one level of sums is enough, else whole steps
+    a.chunk = mk <= CQ_GRP * 64 ? 64 : (a.chunk + CQ_ROWS - 1) / CQ_ROWS * CQ_ROWS;
     const double u = 0x1p-53;
     a.shift = 11.0 * ((double)mk * pw + (double)pw * (pw + 1)) * u;
     a.Tout = Tout;
     const dim3 grid((unsigned)((mk + a.chunk - 1) / a.chunk));
     double *S = w.cq_S;
-    hipLaunchKernelGGL((cqr_step_kernel<CQ_GRAM, T, T, T>), grid, dim3(256), 0, s, a, (const T *)base, w.lda, base,
+    hipLaunchKernelGGL((cqr_step_kernel<CQ_GRAM, T, T, T>), grid, dim3(CQ_NT), 0, s, a, (const T *)base, w.lda, base,
                        w.lda);
-    hipLaunchKernelGGL((cqr_step_kernel<CQ_PASS1, T, double, T>), grid, dim3(256), 0, s, a, (const T *)base, w.lda, S,
+    hipLaunchKernelGGL((cqr_step_kernel<CQ_PASS1, T, double, T>), grid, dim3(CQ_NT), 0, s, a, (const T *)base, w.lda, S,
                        w.cq_ld);
-    hipLaunchKernelGGL((cqr_step_kernel<CQ_PASS2, double, double, T>), grid, dim3(256), 0, s, a, (const double *)S,
+    hipLaunchKernelGGL((cqr_step_kernel<CQ_PASS2, double, double, T>), grid, dim3(CQ_NT), 0, s, a, (const double *)S,
                        w.cq_ld, S, w.cq_ld);
-    if (mk > pw)
-        hipLaunchKernelGGL((cqr_step_kernel<CQ_PASS3, double, T, T>), grid, dim3(256), 0, s, a, (const double *)S,
-                           w.cq_ld, base, w.lda);
+    hipLaunchKernelGGL((cqr_step_kernel<CQ_PASS3, double, T, T>), dim3(grid.x + 1), dim3(CQ_NT), 0, s, a,
+                       (const double *)S, w.cq_ld, base, w.lda);
 }
 
 void cqr_panel_f64(const QrWork &w, int64_t j0, int pw, double *Tout, hipStream_t s)

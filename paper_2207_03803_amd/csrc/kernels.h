@@ -85,7 +85,7 @@ struct QrWork {
     double *cq_S;       // CholeskyQR: FP64 scratch panel [QR_NB x cq_ld] (column-major)
     int64_t cq_ld;      // >= m
     double *cq_part;    // [CQ_PART] partial Gram matrices (upper 16 x 16 blocks)
-    double *cq_G;       // [4 * QR_NB * QR_NB] Y_a^T Y_b of a panel pair
+    double *cq_G;       // [4 * QR_NB * QR_NB] Y_a^T Y_b of a panel pair; a panel's LU, R3, signs
     double *cq_R;       // [4 * QR_NB * QR_NB] R1, R2, R2 R1, U R3 (packed upper triangles)
     unsigned *cq_counters;  // [CQ_COUNTERS] arrival counters of the panel's sums (zero; left zero)
     int32_t *status;

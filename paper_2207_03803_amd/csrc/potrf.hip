@@ -15,7 +15,6 @@ struct CholLds {
     double D[S64][DL];  // the diagonal block, [row][column]
     double E[S64][DL];  // the previous step's rows under it, [column][p]; then the block row's tile
     double F[S64][DL];  // the previous step's rows under the tile, [column][p]; then U_kk packed
-    double T[4][16][17];
     int ok;
 };
 static_assert(PACK <= S64 * DL, "a packed triangle fits a matrix buffer");
@@ -42,7 +41,7 @@ DEV void chol_load_cols(const double *U, int64_t ld, int64_t k0, int kb, int64_t
 // subtracted from the diagonal block and the tile.  Workgroup 0 leaves U_kk in diag
 // ([column][row], 64 x 64): the others still read the block in place, so the pair's
 // trailing update (chol_syrk_kernel) stores it; with no columns to the right it is
-// stored here.  Latency-bound: 24 us, 26 with PREV, where the diagonal block, the block row
+// stored here.  Latency-bound: 19 us, 21 with PREV, where the diagonal block, the block row
 // and the strip update of each step took 35 + 35 + 30 us.
 template <bool PREV>
 __global__ __launch_bounds__(256) void chol_step_kernel(double *U, int64_t ld, int64_t k0, int kb, int64_t n,
@@ -94,7 +93,8 @@ __global__ __launch_bounds__(256) void chol_step_kernel(double *U, int64_t ld, i
     }
     if (right)
         chol_load_cols(U, ld, k0, kb, c0, n, L.E);
-    chol64(L.D, &L.ok);
+    double *P = &L.F[0][0];
+    chol64(L.D, P, &L.ok);
     if (right)
 #pragma unroll
         for (int c = 0; c < 4; ++c)
@@ -103,8 +103,6 @@ __global__ __launch_bounds__(256) void chol_step_kernel(double *U, int64_t ld, i
                 const double v = L.E[16 * wave + r][16 * c + 4 * e + g];
                 y[c][e] = PREV ? y[c][e] + v : v;
             }
-    double *P = &L.F[0][0];
-    pack_upper([&](int i, int j) { return L.D[i][j]; }, P, L.T);
     if (blockIdx.x == 0) {
         if (t == 0 && !L.ok)
             set_status(status, DST_ENOTPD);

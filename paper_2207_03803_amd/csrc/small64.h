@@ -6,6 +6,8 @@
 // is C(m = g + 4 e, n = r).
 #pragma once
 
+#include <utility>
+
 #include "common.h"
 
 namespace gap {
@@ -30,55 +32,201 @@ DEV double readlane_d(double v, int lane)
     return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
 }
 
-// 1 / d for a normal d, to about one ulp: the hardware's estimate and two Newton steps (a
-// third of a division's latency, which the chains below would wait for at each step).
+// Lane N of each row of 16 lanes, to the whole row: one instruction, and no scalar register
+// for the next one to wait on.
+template <int N>
+DEV double row_bcast(double v)
+{
+    const long long b = __double_as_longlong(v);
+    return __longlong_as_double(__builtin_amdgcn_mov_dpp(b, 0x150 + N, 0xf, 0xf, true));
+}
+
+// f(integral_constant<int, A>) ... f(integral_constant<int, B - 1>)
+template <int A, int B, class F>
+DEV void static_for(F f)
+{
+    if constexpr (A < B) {
+        f(std::integral_constant<int, A>{});
+        static_for<A + 1, B>(f);
+    }
+}
+
+// 1 / d for a normal d, to about one ulp: the hardware's estimate (error e below 2^-20) and one
+// step of third order, x + x (e + e^2) (a third of a division's latency, which the chains
+// below would wait for at each step).
 DEV double fast_rcp(double d)
 {
-    double x = __builtin_amdgcn_rcp(d);
-    x = fma(x, fma(-d, x, 1.0), x);
-    return fma(x, fma(-d, x, 1.0), x);
+    const double x = __builtin_amdgcn_rcp(d);
+    const double e = fma(-d, x, 1.0);
+    return fma(x, fma(e, e, e), x);
+}
+
+// The four rows 4 e .. 4 e + 3 that element e of a 16 x 16 block holds (row 4 e + g in lanes
+// 16 g + r), each in every row of 16 lanes.
+DEV void rows_of(double v, double (&y)[4])
+{
+    const long long b = __double_as_longlong(v);
+    const unsigned w[2] = {(unsigned)b, (unsigned)(b >> 32)};
+    unsigned o[4][2];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        const auto p = __builtin_amdgcn_permlane32_swap(w[h], w[h], false, false);
+        const auto lo = __builtin_amdgcn_permlane16_swap(p[0], p[0], false, false);
+        const auto hi = __builtin_amdgcn_permlane16_swap(p[1], p[1], false, false);
+        o[0][h] = lo[0];
+        o[1][h] = lo[1];
+        o[2][h] = hi[0];
+        o[3][h] = hi[1];
+    }
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+        y[j] = __longlong_as_double(((long long)o[j][1] << 32) | o[j][0]);
+}
+
+// y[g]: the four rows back in one element.
+DEV double row_pick(const double (&y)[4], int g)
+{
+    const double a = (g & 1) ? y[1] : y[0], b = (g & 1) ? y[3] : y[2];
+    return (g & 2) ? b : a;
+}
+
+// The inverse of a 16 x 16 upper triangle (zeros below; row i, column c at U[i * ld + c], LDS),
+// one wave, to inv[16 i + c].  Four rows at a time, the products on MFMA.
+DEV void invert_upper16(const double *U, int ld, double *inv)
+{
+    const int lane = threadIdx.x & 63, g = lane >> 4, r = lane & 15;
+    const double dinv = 1.0 / U[r * ld + r];
+    d4 acc;
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+        acc[e] = g + 4 * e == r ? 1.0 : 0.0;
+    static_for<0, 4>([&](auto bc) {
+        constexpr int b = 3 - bc;
+        double y[4], x[4], row[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            row[j] = U[(4 * b + j) * ld + r];
+        const double below = -U[r * ld + 4 * b + g];
+        rows_of(acc[b], y);
+        static_for<0, 4>([&](auto jc) {
+            constexpr int j = 3 - jc;
+            x[j] = y[j] * row_bcast<4 * b + j>(dinv);
+            static_for<0, j>([&](auto ic) { y[ic] -= row_bcast<4 * b + j>(row[ic]) * x[j]; });
+        });
+        const double xg = row_pick(x, g);
+        inv[(4 * b + g) * 16 + r] = xg;
+        if constexpr (b > 0)
+            acc = mfma16(below, xg, acc);
+    });
+}
+
+// The ten blocks of the upper triangle read through f(row, col) (row <= col; zeros below) to P
+// (LDS or global).
+template <class F>
+DEV void pack_blocks(F f, double *P)
+{
+    const int t = threadIdx.x, i0 = t >> 4, j0 = t & 15;
+#pragma unroll
+    for (int idx = 0; idx < NBLK; ++idx) {
+        const int c = blk_col(idx), b = idx - c * (c + 1) / 2;
+        const int row = 16 * b + i0, col = 16 * c + j0;
+        P[idx * BLK + t] = row <= col ? f(row, col) : 0.0;
+    }
+}
+
+// A PACK: the ten blocks, then the inverses of the four diagonal blocks (wave w inverts block
+// w).  T: 16 x 17 scratch per wave.  No barrier at the start; f's data must be visible.  Ends
+// with a barrier.
+template <class F>
+DEV void pack_upper(F f, double *P, double (*T)[16][17])
+{
+    const int t = threadIdx.x, i0 = t >> 4, j0 = t & 15;
+    pack_blocks(f, P);
+#pragma unroll
+    for (int b = 0; b < 4; ++b)
+        T[b][i0][j0] = i0 <= j0 ? f(16 * b + i0, 16 * b + j0) : 0.0;
+    __syncthreads();
+    const int wave = t >> 6;
+    invert_upper16(&T[wave][0][0], 17, P + (NBLK + wave) * BLK);
+    __syncthreads();
 }
 
 // Cholesky S = U^T U of the 64 x 64 matrix in LDS (upper triangle read), in place: U above,
-// zeros below.  Per 16 rows: one wave eliminates them over all 64 columns (lane = column, the
-// 16 rows in registers, square roots and row scaling afterwards, off the chain), then the
-// trailing blocks take the rank-16 update on all four waves.  A pivot that is not positive
-// and finite counts as 1 and clears *ok (LDS, set to 1 by the caller).  13 us where a chain of
-// 64 steps on one wave took about 40.
-DEV void chol64(double (*S)[DL], int *ok)
+// zeros below, and U as a PACK in P (LDS or global).  A pivot that is not positive and finite
+// counts as 1 and clears *ok (LDS, set to 1 by the caller).
+//
+// Block row by block row: wave c eliminates the block row's column block c together with a copy
+// of the diagonal block, four rows at a time: those four replicated in every row of 16 lanes,
+// so that a step is a reciprocal (its pivot formed ahead, in every lane), row broadcasts and a
+// few updates; then one MFMA for the rows below.  Square roots and row scaling come
+// after the chain.  The wave whose columns are done inverts the diagonal block before.
+// 9.3 us where one wave with all 64 columns and scalar broadcasts took 13, and 2 us more for the
+// pack.
+DEV void chol64(double (*S)[DL], double *P, int *ok)
 {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, g = lane >> 4, r = lane & 15;
-#pragma unroll
+#pragma unroll 1
     for (int kb = 0; kb < 4; ++kb) {
-        if (wave == 0) {
-            double x[16], dv = 1.0;
+        const int k0 = 16 * kb, c0 = 16 * wave;
+        d4 u, p, out;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            u[e] = S[k0 + g + 4 * e][k0 + r];
+            p[e] = S[k0 + g + 4 * e][c0 + r];
+        }
+        __syncthreads();
+        if (wave >= kb) {
+            double dv = 1.0;
             bool bad = false;
-#pragma unroll
-            for (int i = 0; i < 16; ++i)
-                x[i] = S[16 * kb + i][lane];
-#pragma unroll
-            for (int k = 0; k < 16; ++k) {
-                double d = readlane_d(x[k], 16 * kb + k);
-                if (!(d > 0.0) || !(d < INFINITY)) {
-                    bad = true;
-                    d = 1.0;
+            static_for<0, 4>([&](auto bc) {
+                constexpr int b = bc;
+                double y[4], q[4], w[4];
+                rows_of(u[b], y);
+                rows_of(p[b], q);
+                double d = row_bcast<4 * b>(y[0]);
+                static_for<0, 4>([&](auto jc) {
+                    constexpr int j = jc, k = 4 * b + j;
+                    const bool good = d > 0.0 && d < INFINITY;
+                    const double rc = good ? fast_rcp(d) : 1.0;
+                    bad |= !good;
+                    if (r == k)
+                        dv = y[j];
+                    w[j] = y[j] * rc;
+                    if constexpr (j < 3) {
+                        const double f = row_bcast<k + 1>(y[j]);
+                        d = row_bcast<k + 1>(y[j + 1]) - (f * rc) * f;
+                    }
+                    static_for<j + 1, 4>([&](auto ic) {
+                        constexpr int i = ic;
+                        const double m = row_bcast<4 * b + i>(w[j]);
+                        y[i] -= m * y[j];
+                        q[i] -= m * q[j];
+                    });
+                });
+                out[b] = row_pick(q, g);
+                if constexpr (b < 3) {
+                    const double wg = -row_pick(w, g);
+                    u = mfma16(wg, row_pick(y, g), u);
+                    p = mfma16(wg, out[b], p);
                 }
-                if (lane == k)
-                    dv = d;
-                const double wv = x[k] * fast_rcp(d);
-#pragma unroll
-                for (int i = k + 1; i < 16; ++i)
-                    x[i] -= readlane_d(wv, 16 * kb + i) * x[k];
-            }
-            const double sq = sqrt(dv), rs = 1.0 / sq;
-#pragma unroll
-            for (int k = 0; k < 16; ++k) {
-                const int row = 16 * kb + k;
-                const double v = lane == row ? readlane_d(sq, k) : x[k] * readlane_d(rs, k);
-                S[row][lane] = lane >= row ? v : 0.0;
-            }
-            if (bad && lane == 0)
+            });
+            const double sq = sqrt(dv > 0.0 && dv < INFINITY ? dv : 1.0), rs = 1.0 / sq;
+            static_for<0, 4>([&](auto bc) {
+                constexpr int b = bc;
+                const double f[4] = {row_bcast<4 * b>(rs), row_bcast<4 * b + 1>(rs), row_bcast<4 * b + 2>(rs),
+                                     row_bcast<4 * b + 3>(rs)};
+                const int row = k0 + 4 * b + g, col = c0 + r;
+                const double v = out[b] * row_pick(f, g);
+                S[row][col] = col > row ? v : (col == row ? sq : 0.0);
+            });
+            if (bad && lane == 0 && wave == kb)
                 *ok = 0;
+        } else {
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                S[k0 + g + 4 * e][c0 + r] = 0.0;
+            if (wave == kb - 1)
+                invert_upper16(&S[c0][c0], DL, P + (NBLK + wave) * BLK);
         }
         __syncthreads();
         const int nb = 3 - kb;
@@ -91,49 +239,17 @@ DEV void chol64(double (*S)[DL], int *ok)
                 acc[e] = S[rb + g + 4 * e][cb + r];
 #pragma unroll
             for (int e = 0; e < 4; ++e)
-                acc = mfma16(-S[16 * kb + 4 * e + g][rb + r], S[16 * kb + 4 * e + g][cb + r], acc);
+                acc = mfma16(-S[k0 + 4 * e + g][rb + r], S[k0 + 4 * e + g][cb + r], acc);
 #pragma unroll
             for (int e = 0; e < 4; ++e)
                 S[rb + g + 4 * e][cb + r] = acc[e];
         }
-        __syncthreads();
+        if (nb > 0)
+            __syncthreads();
     }
-}
-
-// The upper triangle read through f(row, col) (row <= col) as a PACK in P (LDS or global):
-// its ten blocks (zeros below the diagonal), then the inverses of the four diagonal blocks
-// (wave w inverts block w, one column per lane).  T: 16 x 17 scratch per wave.  No barrier at
-// the start; f's data must be visible.  Ends with a barrier.
-template <class F>
-DEV void pack_upper(F f, double *P, double (*T)[16][17])
-{
-    const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
-    const int i0 = t >> 4, j0 = t & 15;
-#pragma unroll
-    for (int idx = 0; idx < NBLK; ++idx) {
-        const int c = blk_col(idx), b = idx - c * (c + 1) / 2;
-        const int row = 16 * b + i0, col = 16 * c + j0;
-        const double v = row <= col ? f(row, col) : 0.0;
-        P[idx * BLK + t] = v;
-        if (b == c)
-            T[b][i0][j0] = v;
-    }
-    __syncthreads();
-    if (lane < 16) {
-        double x[16];
-        const double dinv = 1.0 / T[wave][lane][lane];
-#pragma unroll
-        for (int i = 15; i >= 0; --i) {
-            double v = i == lane ? 1.0 : 0.0;
-#pragma unroll
-            for (int p = i + 1; p < 16; ++p)
-                v -= T[wave][i][p] * x[p];
-            x[i] = v * readlane_d(dinv, i);
-        }
-#pragma unroll
-        for (int i = 0; i < 16; ++i)
-            P[NBLK * BLK + wave * BLK + i * 16 + lane] = x[i];
-    }
+    pack_blocks([&](int i, int j) { return S[i][j]; }, P);
+    if (wave == 3)
+        invert_upper16(&S[48][48], DL, P + (NBLK + 3) * BLK);
     __syncthreads();
 }
 
@@ -190,58 +306,77 @@ DEV d4 upper_product_block(int bi, int bj, FA fa, FB fb)
 
 // LU of B - diag(sg) (64 x 64 in LDS, order pw) without pivoting, sg_k = -sign of the pivot
 // (sign(0) = +1), so that every pivot is at least 1 in magnitude.  In place: U on and above the
-// diagonal, the unit lower factor's entries below.  Blocked by 16 like chol64.
+// diagonal, the unit lower factor's entries below.  Blocked like chol64; wave c takes column
+// block c of the block row and row block c of the block column (as rows of the transpose),
+// with copies of the diagonal block and its transpose.
 DEV void lu64_signs(double (*B)[DL], double *sg, int pw)
 {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, g = lane >> 4, r = lane & 15;
-#pragma unroll
+#pragma unroll 1
     for (int kb = 0; kb < 4; ++kb) {
-        const int k0 = 16 * kb;
-        if (wave == 0) {
-            double q[16], sv = 1.0;
+        const int k0 = 16 * kb, c0 = 16 * wave;
+        d4 u, l, pu, pl;
 #pragma unroll
-            for (int c = 0; c < 16; ++c)
-                q[c] = B[lane][k0 + c];
-#pragma unroll
-            for (int k = 0; k < 16; ++k) {
-                if (k0 + k < pw) {
-                    const double d = readlane_d(q[k], k0 + k);
-                    const double s = (d >= 0.0) ? -1.0 : 1.0, piv = d - s;
-                    const bool below = lane > k0 + k && lane < pw;
-                    const double li = below ? q[k] * fast_rcp(piv) : 0.0;
-#pragma unroll
-                    for (int c = k + 1; c < 16; ++c)
-                        q[c] -= li * readlane_d(q[c], k0 + k);
-                    if (below)
-                        q[k] = li;
-                    if (lane == k0 + k)
-                        q[k] = piv;
-                    if (lane == k)
-                        sv = s;
-                }
-            }
-            if (lane >= k0)
-#pragma unroll
-                for (int c = 0; c < 16; ++c)
-                    B[lane][k0 + c] = q[c];
-            if (lane < 16)
-                sg[k0 + lane] = sv;
+        for (int e = 0; e < 4; ++e) {
+            u[e] = B[k0 + g + 4 * e][k0 + r];
+            l[e] = B[k0 + r][k0 + g + 4 * e];
+            pu[e] = B[k0 + g + 4 * e][c0 + r];
+            pl[e] = B[c0 + r][k0 + g + 4 * e];
         }
         __syncthreads();
-        // the block row: one column per lane, L11 x = b
-        if (wave == 0 && lane >= k0 + 16) {
-            double x[16];
-#pragma unroll
-            for (int i = 0; i < 16; ++i)
-                x[i] = B[k0 + i][lane];
-#pragma unroll
-            for (int k = 0; k < 16; ++k)
-#pragma unroll
-                for (int i = k + 1; i < 16; ++i)
-                    x[i] -= B[k0 + i][k0 + k] * x[k];
-#pragma unroll
-            for (int i = 0; i < 16; ++i)
-                B[k0 + i][lane] = x[i];
+        if (wave >= kb) {
+            double sv = 1.0, pv = 0.0;
+            static_for<0, 4>([&](auto bc) {
+                constexpr int b = bc;
+                double y[4], z[4], qu[4], ql[4];
+                rows_of(u[b], y);
+                rows_of(l[b], z);
+                rows_of(pu[b], qu);
+                rows_of(pl[b], ql);
+                double d = row_bcast<4 * b>(y[0]);
+                static_for<0, 4>([&](auto jc) {
+                    constexpr int j = jc, k = 4 * b + j;
+                    const double s = (d >= 0.0) ? -1.0 : 1.0, piv = d - s;
+                    const double rp = k0 + k < pw ? fast_rcp(piv) : 0.0;
+                    if (r == k) {
+                        sv = k0 + k < pw ? s : 1.0;
+                        pv = piv;
+                    }
+                    // columns k of the lower factor: zero on and above the diagonal, and past pw
+                    const double zj = z[j];
+                    z[j] = (r > k && k0 + r < pw) ? zj * rp : 0.0;
+                    ql[j] = (c0 + r > k0 + k && c0 + r < pw) ? ql[j] * rp : 0.0;
+                    if constexpr (j < 3)
+                        d = row_bcast<k + 1>(y[j + 1]) - (row_bcast<k + 1>(zj) * rp) * row_bcast<k + 1>(y[j]);
+                    static_for<j + 1, 4>([&](auto ic) {
+                        constexpr int i = ic;
+                        const double m = row_bcast<4 * b + i>(z[j]);
+                        y[i] -= m * y[j];
+                        qu[i] -= m * qu[j];
+                        const double n = row_bcast<4 * b + i>(y[j]);
+                        z[i] -= n * z[j];
+                        ql[i] -= n * ql[j];
+                    });
+                });
+                const double ug = row_pick(qu, g), lg = row_pick(ql, g);
+                if constexpr (b < 3) {
+                    const double zg = row_pick(z, g), yg = row_pick(y, g);
+                    u = mfma16(-zg, yg, u);
+                    pu = mfma16(-zg, ug, pu);
+                    l = mfma16(-yg, zg, l);
+                    pl = mfma16(-yg, lg, pl);
+                }
+                const int k = k0 + 4 * b + g, x = c0 + r;  // row or column k against column or row x
+                if (x > k) {
+                    B[k][x] = ug;
+                    B[x][k] = lg;
+                }
+            });
+            if (wave == kb && lane < 16) {
+                sg[k0 + lane] = sv;
+                if (k0 + lane < pw)
+                    B[k0 + lane][k0 + lane] = pv;
+            }
         }
         __syncthreads();
         const int nb = 3 - kb;
