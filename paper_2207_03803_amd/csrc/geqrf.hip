@@ -720,16 +720,6 @@ __global__ __launch_bounds__(256) void qr_hmat_kernel(const double *__restrict__
         H[(16 * bi + g + 4 * e) * OB + j] = acc[e];
 }
 
-// Copy a pw x pw row-major T (leading dimension sld) into dst (leading dimension OB).
-__global__ __launch_bounds__(256) void qr_tcopy_kernel(const double *__restrict__ src, int sld, int pw,
-                                                       double *__restrict__ dst)
-{
-    for (int e = threadIdx.x; e < OB * OB; e += 256) {
-        const int i = e / OB, j = e % OB;
-        dst[e] = (i < pw && j < pw) ? src[i * sld + j] : 0.0;
-    }
-}
-
 // C[r][q] -= sum_p Y[r][p] W[p][q] for rows j0.. and columns c0 .. c0+nt; the
 // tile is computed transposed so that consecutive lanes own consecutive rows.
 // The accumulators start from -C (its loads in flight with the first
@@ -952,24 +942,42 @@ static void apply_block(const QrWork &wf, int64_t J, const BlockT &bt, int64_t c
         hipLaunchKernelGGL(qr_update_kernel<M>, grid(nm), dim3(M::NT), 0, s, w, J, pw, c0, nt);
 }
 
+// The small-scratch view w for products with up to OB2 columns (the same buffers).
+static QrWork wide_view(const QrWork &w)
+{
+    QrWork r = w;
+    r.wp_ld = OB2;
+    r.ldw = OB2;
+    r.max_chunks = MAX_CHUNKS_S / 2;
+    return r;
+}
+
 // Factor the panel pair at column J (main-stream scratch in w): panel A, its
 // update of panel B, panel B, and the pair's compact-WY T (row-major, copied
 // to Tdst with leading dimension OB).  Returns the pair's width.
+//
+// With the matrix's last column in the pair, only the right-hand side is left: each panel is
+// applied to it directly (it lies beside panel B's columns) and no T is combined.  64 x 200
+// configurations, M = 256: 126 us less than combining the last block's T for one column.
 template <class T>
 static int factor_pair(const QrWork &w, int64_t J, double *Tdst, hipStream_t s)
 {
     double *Ta = w.Tin, *Tb = w.Tin + NB * NB;
     const int pwa = (int)((w.n - J) < NB ? (w.n - J) : NB);
-    factor_panel<T>(w, J, pwa, Ta, s);
-    const int64_t jb = J + pwa;
+    const int64_t jb = J + pwa, nrhs = w.ncols - w.n;
     const int pwb = (int)((w.n - jb) < NB ? (w.n - jb) : NB);
-    if (pwb <= 0) {
-        hipLaunchKernelGGL(qr_tcopy_kernel, dim3(1), dim3(256), 0, s, (const double *)Ta, NB, pwa, Tdst);
+    const bool last = jb + pwb == w.n;
+    factor_panel<T>(w, J, pwa, Ta, s);
+    const BlockT pa{nullptr, pwa, 0, Ta, NB};  // panel A alone
+    apply_block<T>(w, J, pa, jb, pwb + (last ? nrhs : 0), s);
+    if (pwb == 0)
         return pwa;
-    }
-    BlockT pa{nullptr, pwa, 0, Ta, NB};  // panel A alone
-    apply_block<T>(w, J, pa, jb, pwb, s);
     factor_panel<T>(w, jb, pwb, Tb, s);
+    if (last) {
+        const BlockT pb{nullptr, pwb, 0, Tb, NB};
+        apply_block<T>(w, jb, pb, w.n, nrhs, s);
+        return pwa + pwb;
+    }
     const QrWork wg = rows_to(w, jb + pwb);  // G = Y_a^T Y_b
     const int64_t nch = launch_wpart<T>(wg, J, pwa, jb, (int64_t)pwb, 1, jb, 2048, s);
     hipLaunchKernelGGL(qr_gsum_kernel, dim3(NB * NB / 256), dim3(256), 0, s, wg, pwb, nch, wg.cq_G, NB);
@@ -979,7 +987,8 @@ static int factor_pair(const QrWork &w, int64_t J, double *Tdst, hipStream_t s)
 
 // Factor the trailing-update block at column J: panel pair a, its update of
 // pair b's columns, pair b, then G = Y_a^T Y_b and H = T_a G.  bt.store holds the
-// results; returns the block's width (up to OB2).
+// results; returns the block's width (up to OB2).  The last block also updates the
+// right-hand side, and leaves no T.
 template <class T>
 static int factor_block(const QrWork &w, int64_t J, BlockT &bt, hipStream_t s)
 {
@@ -987,11 +996,17 @@ static int factor_block(const QrWork &w, int64_t J, BlockT &bt, hipStream_t s)
     bt.pwb = 0;
     const int64_t jb = J + bt.pwa;
     const int pwb_max = (int)((w.n - jb) < OB ? (w.n - jb) : OB);
-    if (bt.pwa < OB || pwb_max <= 0)
+    if (pwb_max <= 0)
         return bt.pwa;
+    const bool last = jb + pwb_max == w.n;
     BlockT a{bt.store, bt.pwa, 0};
-    apply_block<T>(w, J, a, jb, pwb_max, s);
+    if (last)
+        apply_block<T>(wide_view(w), J, a, jb, w.ncols - jb, s);
+    else
+        apply_block<T>(w, J, a, jb, pwb_max, s);
     bt.pwb = factor_pair<T>(w, jb, bt.Tb(), s);
+    if (last)
+        return bt.pw();
     const QrWork wg = rows_to(w, jb + bt.pwb);  // G = Y_a^T Y_b
     const int64_t nch = launch_wpart<T>(wg, J, bt.pwa, jb, (int64_t)bt.pwb, 1, jb, 2048, s);
     hipLaunchKernelGGL(qr_gsum_kernel, dim3(OB * OB / 256), dim3(256), 0, s, wg, bt.pwb, nch, bt.G(), OB);
@@ -1004,7 +1019,7 @@ template <class T>
 static void geqrf(const QrWork &w, hipStream_t s, const QrAsync *la)
 {
     // small-scratch views: wn for the products inside a block (at most OB rows
-    // and columns of P), wm for the main stream's update of the next block (OB2)
+    // and columns of P), its wide view for the main stream's update of the next block (OB2)
     QrWork wn = w;
     wn.wpart = w.wpart_s;
     wn.wp_ld = OB;
@@ -1012,15 +1027,13 @@ static void geqrf(const QrWork &w, hipStream_t s, const QrAsync *la)
     wn.W32 = w.W32_s;
     wn.ldw = OB;
     wn.max_chunks = MAX_CHUNKS_S;  // more row chunks keep the panel chain's GEMMs wide
-    QrWork wm = wn;
-    wm.wp_ld = OB2;
-    wm.ldw = OB2;
-    wm.max_chunks = MAX_CHUNKS_S / 2;  // same buffer
+    const QrWork wm = wide_view(wn);
     if (!la) {
         BlockT bt{w.T};
         for (int64_t J = 0; J < w.n; J += bt.pw()) {
             factor_block<T>(wn, J, bt, s);
-            apply_block<T>(w, J, bt, J + bt.pw(), w.ncols - (J + bt.pw()), s);
+            if (J + bt.pw() < w.n)
+                apply_block<T>(w, J, bt, J + bt.pw(), w.ncols - (J + bt.pw()), s);
         }
         return;
     }
@@ -1033,18 +1046,20 @@ static void geqrf(const QrWork &w, hipStream_t s, const QrAsync *la)
     for (int64_t J = 0; J < w.n; ++k) {
         const BlockT &cur = bt[k & 1];
         const int64_t cn = J + cur.pw();                          // first column of block k+1
-        const int64_t nn = (w.n - cn) < OB2 ? (w.n - cn) : OB2;   // its width (0 after the last block)
+        const int64_t nn = (w.n - cn) < OB2 ? (w.n - cn) : OB2;   // its width
+        if (nn <= 0)
+            break;
         // side: block k's update of everything right of block k+1 (b included)
         (void)hipStreamWaitEvent(la->side, la->t_ready, 0);
         apply_block<T>(w, J, cur, cn + nn, w.ncols - (cn + nn), la->side);
         (void)hipEventRecord(la->bulk[k & 1], la->side);
-        if (nn <= 0)
-            break;
         // main: block k+1's columns need every earlier block's update first; its
         // T buffer is the one block k-1's side update read
         if (k > 0)
             (void)hipStreamWaitEvent(s, la->bulk[(k - 1) & 1], 0);
         apply_block<T>(wm, J, cur, cn, nn, s);
+        if (cn + nn == w.n)  // the last block updates the right-hand side itself
+            (void)hipStreamWaitEvent(s, la->bulk[k & 1], 0);
         factor_block<T>(wn, cn, bt[(k + 1) & 1], s);
         (void)hipEventRecord(la->t_ready, s);
         J = cn;

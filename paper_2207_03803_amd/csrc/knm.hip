@@ -237,9 +237,14 @@ DEV bool kdm_valid(const KnmArgs &a, int64_t pos)
     return g >= 0 && g < a.n_grad && a.grad_atom[g] >= 0 && a.grad_atom[g] < a.n_src;
 }
 
-template <int BN, bool DERIV = false>
+// What a segment's rows are: a configuration's atoms, one point (K_MM), or an observation's
+// positions.
+enum KnmRows { CONFIGS, POINTS, POSITIONS };
+
+template <int BN, KnmRows ROWS = CONFIGS>
 DEV void knm_body(const KnmArgs &a, int64_t bid)
 {
+    constexpr bool DERIV = ROWS == POSITIONS, unit = ROWS == POINTS;
     using KS = KSB<BN>;
     constexpr int KNM_BN = BN;
     static_assert(BN == 32 || BN == 64, "column tile of 32 or 64 sparse points");
@@ -255,7 +260,6 @@ DEV void knm_body(const KnmArgs &a, int64_t bid)
 
     // The grid is sized for the largest possible tile count; the remap uses
     // the actual count so that all eight XCDs get an equal share of the tiles.
-    const bool unit = (a.offsets == nullptr);
     const int64_t n_tiles = unit ? (a.n_rows_unit + KNM_BM - 1) / KNM_BM : (int64_t)*a.n_tiles_dev;
     int64_t t, ct;
     if constexpr (DERIV) {
@@ -467,7 +471,17 @@ DEV void knm_body(const KnmArgs &a, int64_t bid)
                         }
             }
             __syncthreads();
-            if (!multi) {
+            if (unit) {  // one row per thread
+                if (tid < n_seg) {
+                    const double sg = sig(tid);
+#pragma unroll 8
+                    for (int c = 0; c < EPC; ++c) {
+                        const int64_t colg = col0 + p * EPC + c;
+                        if (colg < a.M)
+                            emit(tid, colg, E[tid * EPLD + c], sg);
+                    }
+                }
+            } else if (!multi) {
                 for (int item = tid; item < n_seg * EPC; item += KS::NT) {
                     const int s = item % n_seg, c = item / n_seg;
                     const int64_t colg = col0 + p * EPC + c;
@@ -518,11 +532,14 @@ DEV void knm_body(const KnmArgs &a, int64_t bid)
     }
 }
 
-template <int BN>
-__global__ __launch_bounds__(KNM_NT, 2) void knm_kernel(KnmArgs a) { knm_body<BN>(a, blockIdx.x); }
+template <int BN, KnmRows ROWS>
+__global__ __launch_bounds__(KNM_NT, 2) void knm_kernel(KnmArgs a)
+{
+    knm_body<BN, ROWS>(a, blockIdx.x);
+}
 
 // Derivative observation rows: the K_NM tile loop over the observations' positions.
-__global__ __launch_bounds__(KNM_NT, 2) void kdm_kernel(KnmArgs a) { knm_body<64, true>(a, blockIdx.x); }
+__global__ __launch_bounds__(KNM_NT, 2) void kdm_kernel(KnmArgs a) { knm_body<64, POSITIONS>(a, blockIdx.x); }
 
 // ---------------------------------------------------------------------------
 // Derivative rows in two steps, where gradient rows serve several positions (a force
@@ -1111,10 +1128,9 @@ hipError_t launch_knm(KnmArgs a, int64_t max_tiles, hipStream_t s)
     a.total_pad = (total + 7) & ~int64_t(7);
     if (a.total_pad == 0)
         return hipSuccess;
-    if (bn == 64)
-        hipLaunchKernelGGL(knm_kernel<64>, dim3((unsigned)a.total_pad), dim3(KNM_NT), 0, s, a);
-    else
-        hipLaunchKernelGGL(knm_kernel<32>, dim3((unsigned)a.total_pad), dim3(KNM_NT), 0, s, a);
+    const auto kernel = a.offsets ? (bn == 64 ? knm_kernel<64, CONFIGS> : knm_kernel<32, CONFIGS>)
+                                  : (bn == 64 ? knm_kernel<64, POINTS> : knm_kernel<32, POINTS>);
+    hipLaunchKernelGGL(kernel, dim3((unsigned)a.total_pad), dim3(KNM_NT), 0, s, a);
     return hipGetLastError();
 }
 
