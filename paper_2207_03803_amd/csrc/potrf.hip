@@ -11,10 +11,12 @@ namespace gap {
 constexpr int CNB = CHOL_NB;
 static_assert(CNB == S64, "block rows of the 64 x 64 helpers");
 
+// Two matrices only: with 68 KB a workgroup fits beside a K_NM one on a CU.  With three it waited
+// for both of a CU's to end at once, so the steps on the side stream starved until
+// the K_NM was over.
 struct CholLds {
-    double D[S64][DL];  // the diagonal block, [row][column]
-    double E[S64][DL];  // the previous step's rows under it, [column][p]; then the block row's tile
-    double F[S64][DL];  // the previous step's rows under the tile, [column][p]; then U_kk packed
+    double D[S64][DL];  // the diagonal block, [row][column]; then the block row's tile, [column][row]
+    double E[S64][DL];  // the previous step's rows above the block, [column][p]; then U_kk packed
     int ok;
 };
 static_assert(PACK <= S64 * DL, "a packed triangle fits a matrix buffer");
@@ -35,13 +37,26 @@ DEV void chol_load_cols(const double *U, int64_t ld, int64_t k0, int kb, int64_t
         M[wave + 4 * q][lane] = v[q];
 }
 
+// Column x (below n) of the 64 rows from k0 on (rows past kb zero): rows 16 c + 4 e + g at y[c][e].
+DEV void chol_load_frag(const double *U, int64_t ld, int64_t k0, int kb, int64_t x, int64_t n, d4 (&y)[4])
+{
+    const int g = (threadIdx.x & 63) >> 4;
+#pragma unroll
+    for (int c = 0; c < 4; ++c)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const int row = 16 * c + 4 * e + g;
+            y[c][e] = (x < n && row < kb) ? U[x * ld + k0 + row] : 0.0;
+        }
+}
+
 // Step k0 (kb <= 64 columns): every workgroup factors the diagonal block for itself, then
 // solves U_kk^T X = B for its 64 columns right of it (one refinement per 16-row block keeps
 // each solve backward stable).  PREV: the 64 rows above (the pair's first step) are first
 // subtracted from the diagonal block and the tile.  Workgroup 0 leaves U_kk in diag
 // ([column][row], 64 x 64): the others still read the block in place, so the pair's
 // trailing update (chol_syrk_kernel) stores it; with no columns to the right it is
-// stored here.  Latency-bound: 19 us, 21 with PREV, where the diagonal block, the block row
+// stored here.  Latency-bound: 18 us, 25 with PREV (65 and 85 beside a K_NM), where the diagonal block, the block row
 // and the strip update of each step took 35 + 35 + 30 us.
 template <bool PREV>
 __global__ __launch_bounds__(256) void chol_step_kernel(double *U, int64_t ld, int64_t k0, int kb, int64_t n,
@@ -51,58 +66,53 @@ __global__ __launch_bounds__(256) void chol_step_kernel(double *U, int64_t ld, i
     const int t = threadIdx.x, lane = t & 63, wave = t >> 6, g = lane >> 4, r = lane & 15;
     const int64_t c0 = k0 + kb + (int64_t)blockIdx.x * CNB;  // this workgroup's columns (none: >= n)
     const bool right = c0 < n;
-    chol_load_cols(U, ld, k0, kb, k0, k0 + kb, L.F);  // the block, transposed
-    if constexpr (PREV)
-        chol_load_cols(U, ld, k0 - CNB, CNB, k0, k0 + kb, L.E);
-    if (t == 0)
-        L.ok = 1;
-    __syncthreads();
-    for (int idx = wave; idx < NBLK; idx += 4) {
-        const int c = blk_col(idx), b = idx - c * (c + 1) / 2;
-        d4 acc;
+    // the diagonal block's upper 16 x 16 blocks wave, wave + 4, wave + 8
+    d4 acc[3];
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {
+        const int idx = wave + 4 * q, c = blk_col(idx), b = idx - c * (c + 1) / 2;
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
             const int i = 16 * b + g + 4 * e, l = 16 * c + r;
-            acc[e] = (i < kb && l < kb) ? L.F[l][i] : (i == l ? 1.0 : 0.0);
+            acc[q][e] = (idx < NBLK && i < kb && l < kb) ? U[(k0 + l) * ld + k0 + i] : (i == l ? 1.0 : 0.0);
         }
+    }
+    // this wave's 16 columns of the block row (one per lane r), and of the rows above
+    d4 y[4], f[4];
+    chol_load_frag(U, ld, k0, kb, c0 + 16 * wave + r, n, y);
+    if constexpr (PREV) {
+        chol_load_frag(U, ld, k0 - CNB, CNB, c0 + 16 * wave + r, n, f);
+        chol_load_cols(U, ld, k0 - CNB, CNB, k0, k0 + kb, L.E);
+    }
+    if (t == 0)
+        L.ok = 1;
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {
+        const int idx = wave + 4 * q;
+        if (idx >= NBLK)
+            break;
+        const int c = blk_col(idx), b = idx - c * (c + 1) / 2;
         if constexpr (PREV) {
 #pragma unroll
             for (int k = 0; k < CNB / 4; ++k)
-                acc = mfma16(-L.E[16 * b + r][4 * k + g], L.E[16 * c + r][4 * k + g], acc);
+                acc[q] = mfma16(-L.E[16 * b + r][4 * k + g], L.E[16 * c + r][4 * k + g], acc[q]);
         }
 #pragma unroll
         for (int e = 0; e < 4; ++e)
-            L.D[16 * b + g + 4 * e][16 * c + r] = acc[e];
+            L.D[16 * b + g + 4 * e][16 * c + r] = acc[q][e];
     }
-    __syncthreads();
-    // the tile as rows (one per column of the matrix), before the factorisation's chain
-    d4 y[4];
     if constexpr (PREV) {
         if (right)
-            chol_load_cols(U, ld, k0 - CNB, CNB, c0, n, L.F);
-        __syncthreads();
-        if (right)
 #pragma unroll
-            for (int c = 0; c < 4; ++c) {
-                y[c] = d4{0.0, 0.0, 0.0, 0.0};
+            for (int c = 0; c < 4; ++c)
 #pragma unroll
                 for (int k = 0; k < CNB / 4; ++k)
-                    y[c] = mfma16(-L.E[16 * c + r][4 * k + g], L.F[16 * wave + r][4 * k + g], y[c]);
-            }
-        __syncthreads();
+                    y[c] = mfma16(-L.E[16 * c + r][4 * k + g], f[k / 4][k % 4], y[c]);
     }
-    if (right)
-        chol_load_cols(U, ld, k0, kb, c0, n, L.E);
-    double *P = &L.F[0][0];
+    __syncthreads();
+    double *P = &L.E[0][0];
     chol64(L.D, P, &L.ok);
-    if (right)
-#pragma unroll
-        for (int c = 0; c < 4; ++c)
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const double v = L.E[16 * wave + r][16 * c + 4 * e + g];
-                y[c][e] = PREV ? y[c][e] + v : v;
-            }
     if (blockIdx.x == 0) {
         if (t == 0 && !L.ok)
             set_status(status, DST_ENOTPD);
@@ -117,17 +127,18 @@ __global__ __launch_bounds__(256) void chol_step_kernel(double *U, int64_t ld, i
     if (!right)
         return;
     solve_rows<true>(y, P);
+    __syncthreads();
 #pragma unroll
     for (int c = 0; c < 4; ++c)
 #pragma unroll
         for (int e = 0; e < 4; ++e)
-            L.E[16 * wave + r][16 * c + 4 * e + g] = y[c][e];
+            L.D[16 * wave + r][16 * c + 4 * e + g] = y[c][e];
     __syncthreads();
 #pragma unroll
     for (int q = 0; q < 16; ++q) {
         const int c = wave + 4 * q;
         if (c0 + c < n && lane < kb)
-            U[(c0 + c) * ld + k0 + lane] = L.E[c][lane];
+            U[(c0 + c) * ld + k0 + lane] = L.D[c][lane];
     }
 }
 
