@@ -23,6 +23,7 @@ struct Layout {
     // N = all observation rows: NE energies (configurations) then n_obs derivative observations
     int64_t N = 0, M = 0, n_atoms = 0, m = 0, lda = 0, ncols = 0, max_tiles = 0;
     int64_t NE = 0, n_obs = 0, n_pos = 0, max_tiles_d = 0;
+    int plan_chunk = 0, plan_chunk_d = 0;
     size_t off_tiles_d = 0, off_plan_d = 0, off_D = 0, end_scratch = 0;
     TsqrTree tree;
     size_t off_A = 0, off_tau = 0, off_wpart = 0, off_T = 0, off_Tin = 0, off_U = 0, off_W = 0, off_ts_tiles = 0,
@@ -70,7 +71,8 @@ Layout make_layout(int64_t NE, int64_t n_atoms, int64_t M, int32_t precision, in
     L.m = N + M;
     L.lda = (L.m + 63) / 64 * 64;
     L.ncols = M + 1;
-    L.max_tiles = knm_max_tiles(NE, n_atoms);
+    L.plan_chunk = knm_plan_chunk(n_atoms, M, d);
+    L.max_tiles = knm_max_tiles(NE, n_atoms, L.plan_chunk);
     L.tree = tsqr_tree(L.m);
     size_t o = 0;
     auto take = [&](size_t bytes) {
@@ -104,12 +106,13 @@ Layout make_layout(int64_t NE, int64_t n_atoms, int64_t M, int32_t precision, in
     L.off_rhs = takep(sizeof(double) * (size_t)M);
     L.off_misc = takep(sizeof(double) * 512);
     L.off_tiles = take(sizeof(int32_t) * (size_t)(L.max_tiles + 2));
-    L.off_plan = take(sizeof(int32_t) * (size_t)knm_plan_ints(NE));
+    L.off_plan = take(sizeof(int32_t) * (size_t)knm_plan_ints(NE, L.plan_chunk));
     if (n_obs > 0) {
         // derivative observations: their tile plan over the positions, and D = (X X_M^T)^(zeta - 1)
-        L.max_tiles_d = knm_max_tiles(n_obs, n_pos);
+        L.plan_chunk_d = knm_plan_chunk(n_pos, M, d);
+        L.max_tiles_d = knm_max_tiles(n_obs, n_pos, L.plan_chunk_d);
         L.off_tiles_d = take(sizeof(int32_t) * (size_t)(L.max_tiles_d + 2));
-        L.off_plan_d = take(sizeof(int32_t) * (size_t)knm_plan_ints(n_obs));
+        L.off_plan_d = take(sizeof(int32_t) * (size_t)knm_plan_ints(n_obs, L.plan_chunk_d));
         L.off_D = takep(sizeof(double) * (size_t)n_atoms * (size_t)M);
     }
     L.off_counters = take(sizeof(unsigned) * N_COUNTERS);
@@ -547,7 +550,7 @@ static gap_status build_setup(gap_handle h, hipStream_t s, KnmArgs *a)
     hipLaunchKernelGGL(build_clear_kernel, dim3(1), dim3(256), 0, s, h->counters(), h->status());
     GAP_TRY(dev(launch_trsv_clear(h->tsync(), L.M, s)));
     const KnmPlan kp = plan_of(h);
-    GAP_TRY(dev(launch_plan_tiles(h->offsets, L.NE, L.n_atoms, kp, L.max_tiles, h->status(), s)));
+    GAP_TRY(dev(launch_plan_tiles(h->offsets, L.NE, L.n_atoms, L.plan_chunk, kp, L.max_tiles, h->status(), s)));
     *a = KnmArgs{};
     a->X = h->x_atoms;
     a->offsets = h->offsets;
@@ -760,7 +763,8 @@ static gap_status build_derivatives(gap_handle h)
         GAP_TRY(dev(launch_kdm_blocks(a, L.n_obs, L.n_pos, w, h->at<double>(L.off_wpart), s)));
     } else {
         const KnmPlan kp = plan_of_d(h);
-        GAP_TRY(dev(launch_plan_tiles(o.obs_offsets, L.n_obs, L.n_pos, kp, L.max_tiles_d, h->status(), s)));
+        GAP_TRY(dev(launch_plan_tiles(o.obs_offsets, L.n_obs, L.n_pos, L.plan_chunk_d, kp, L.max_tiles_d, h->status(),
+                                      s)));
         a.tile_start = kp.tile_start;
         a.cfg_list = kp.cfg_list;
         a.n_tiles_dev = kp.n_tiles;

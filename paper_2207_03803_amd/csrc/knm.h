@@ -43,16 +43,18 @@ struct KnmArgs {
     int64_t n_grad, n_src;     // bounds of pos_grad and grad_atom values (out of range: zero row, DST_EINVAL)
 };
 
-int64_t knm_max_tiles(int64_t N, int64_t n_atoms);
+// Configurations per chunk of the tile plan for a K_NM of these sizes.
+int knm_plan_chunk(int64_t n_atoms, int64_t M, int64_t d);
+int64_t knm_max_tiles(int64_t N, int64_t n_atoms, int chunk);
 // Plan arrays (device): tile_start [max_tiles + 1], n_tiles [1], cfg_list [N] followed by
-// the chunks' tile lists (knm_plan_ints(N) int32 together).
-int64_t knm_plan_ints(int64_t N);
+// the chunks' tile lists (knm_plan_ints(N, chunk) int32 together).
+int64_t knm_plan_ints(int64_t N, int chunk);
 struct KnmPlan {
     int32_t *tile_start, *n_tiles, *cfg_list;
     uint16_t *lists;
 };
-hipError_t launch_plan_tiles(const int64_t *offsets, int64_t N, int64_t n_atoms, const KnmPlan &p, int64_t max_tiles,
-                             int32_t *status, hipStream_t s);
+hipError_t launch_plan_tiles(const int64_t *offsets, int64_t N, int64_t n_atoms, int chunk, const KnmPlan &p,
+                             int64_t max_tiles, int32_t *status, hipStream_t s);
 hipError_t launch_knm(KnmArgs a, int64_t max_tiles, hipStream_t s);
 // Derivative observation rows (forces, virials): with the tile plan built over the
 // observations' positions, row o of out is sum_p w_p zeta sw2 D(i(p), j) (x'_{g(p)} . x_j),

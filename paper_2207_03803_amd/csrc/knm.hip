@@ -13,7 +13,7 @@ namespace gap {
 // ---------------------------------------------------------------------------
 // Tile plan.  The rows of K_NM are independent per configuration, so a tile
 // may hold any set of whole configurations.  The configurations are split, in
-// order, into chunks of PLAN_C; each chunk is sorted by atom count (largest
+// order, into chunks of at most PLAN_C; each chunk is sorted by atom count (largest
 // first, then by index) and packed: a configuration of more than
 // KNM_CAP atoms gets a tile of its own (processed in atom chunks); the others
 // fill tiles of at most KNM_CAP atoms and KNM_MAX_SEG configurations, each
@@ -22,32 +22,41 @@ namespace gap {
 // (the first position of tile t in cfg_list).  The offsets are validated too.
 //
 // One wave packs a chunk; each step takes as many configurations of one size as fit, so a
-// chunk is about 200 dependent steps.  Chunks of 512: 115 us (57 us for 200
-// configurations), where one thread per chunk of 2048 took 743 us (143 us); the tiles of
-// U[8, 64]-atom configurations are 99.1 % full (99.6 % with chunks of 2048).
+// chunk of 512 is about 200 dependent steps: 82 us (50 with 256, 33 with 128), where one
+// thread per chunk of 2048 took 743 us (143 us for 200 configurations).  The tiles of U[8, 64]-atom
+// configurations are 99.1 % full with chunks of 512, about 3.5 / chunk short of full.
 // ---------------------------------------------------------------------------
-constexpr int PLAN_C = 512;                // configurations per chunk
+constexpr int PLAN_C = 512;                // configurations per chunk, at most (a power of two)
+
+// Configurations per chunk: a chunk costs 0.15 us per configuration, and a K_NM of T us loses
+// 3.5 T / chunk to its chunks' last tiles; 128 up to 1.3 ms, 256 up to 4.5 ms (at 63 TFLOP/s).
+int knm_plan_chunk(int64_t n_atoms, int64_t M, int64_t d)
+{
+    const double flops = 2.0 * (double)n_atoms * (double)M * (double)d;
+    return flops < 8.2e10 ? 128 : (flops < 2.8e11 ? 256 : PLAN_C);
+}
 constexpr int PLAN_LARGE = KNM_CAP + 1;    // bucket of the configurations above KNM_CAP atoms
 constexpr int PLAN_WORDS = (KNM_CAP + 64) / 64;
 
-int64_t knm_plan_chunks(int64_t N) { return (N + PLAN_C - 1) / PLAN_C; }
+static int64_t plan_chunks(int64_t N, int chunk) { return (N + chunk - 1) / chunk; }
 // cfg_list [N] and, per chunk, its tile count and first positions (16 bits each)
-int64_t knm_plan_ints(int64_t N) { return N + knm_plan_chunks(N) * (PLAN_C / 2); }
+int64_t knm_plan_ints(int64_t N, int chunk) { return N + plan_chunks(N, chunk) * (chunk / 2); }
 
-// lists: chunk c's tile starts at [c * PLAN_C]; entry 0, always position 0, holds the tile
+// lists: chunk c's tile starts at [c * chunk]; entry 0, always position 0, holds the tile
 // count instead.
 __global__ __launch_bounds__(256) void plan_chunk_kernel(const int64_t *__restrict__ offsets, int64_t N,
-                                                         int64_t n_atoms, int32_t *__restrict__ cfg_list,
+                                                         int64_t n_atoms, int chunk, int32_t *__restrict__ cfg_list,
                                                          uint16_t *__restrict__ lists, int32_t *status)
 {
     __shared__ int32_t key[PLAN_C];
     __shared__ int32_t bfirst[64 * PLAN_WORDS], blast[64 * PLAN_WORDS];
+    __shared__ uint32_t bucket[64 * PLAN_WORDS];  // bfirst | items left << 16
     __shared__ uint16_t order[PLAN_C];
     __shared__ int bad_s, nlarge_s;
     const int t = threadIdx.x;
-    const int64_t c0 = (int64_t)blockIdx.x * PLAN_C;
-    const int cnt = (int)((N - c0) < PLAN_C ? (N - c0) : PLAN_C);
-    uint16_t *ls = lists + blockIdx.x * (int64_t)PLAN_C;
+    const int64_t c0 = (int64_t)blockIdx.x * chunk;
+    const int cnt = (int)((N - c0) < chunk ? (N - c0) : chunk);
+    uint16_t *ls = lists + blockIdx.x * (int64_t)chunk;
     if (t == 0) {
         bad_s = 0;
         nlarge_s = 0;
@@ -60,7 +69,7 @@ __global__ __launch_bounds__(256) void plan_chunk_kernel(const int64_t *__restri
         bfirst[b] = blast[b] = 0;
     __syncthreads();
     // key = (PLAN_LARGE - bucket) << 16 | local index: ascending = largest first
-    for (int i = t; i < PLAN_C; i += 256) {
+    for (int i = t; i < chunk; i += 256) {
         int32_t k = INT32_MAX;
         if (i < cnt) {
             const int64_t sz = offsets[c0 + i + 1] - offsets[c0 + i];
@@ -72,14 +81,16 @@ __global__ __launch_bounds__(256) void plan_chunk_kernel(const int64_t *__restri
         key[i] = k;
     }
     __syncthreads();
-    for (int kk = 2; kk <= PLAN_C; kk <<= 1)
+    for (int kk = 2; kk <= chunk; kk <<= 1)
         for (int jj = kk >> 1; jj > 0; jj >>= 1) {
             // pair p: its lower element i has bit jj clear
             const int i = 2 * t - (t & (jj - 1)), l = i | jj;
-            const int32_t x = key[i], y = key[l];
-            if ((x > y) == ((i & kk) == 0)) {
-                key[i] = y;
-                key[l] = x;
+            if (l < chunk) {
+                const int32_t x = key[i], y = key[l];
+                if ((x > y) == ((i & kk) == 0)) {
+                    key[i] = y;
+                    key[l] = x;
+                }
             }
             __syncthreads();
         }
@@ -113,11 +124,22 @@ __global__ __launch_bounds__(256) void plan_chunk_kernel(const int64_t *__restri
             if (i > 0)
                 ls[i] = (uint16_t)i;
         }
-        // non-empty buckets 0..KNM_CAP as a bit set; bfirst[] is each bucket's next item
-        uint64_t nonempty[PLAN_WORDS];
+        // non-empty buckets 0..KNM_CAP as a bit set, word w in lane w; some: its non-empty words
+        uint64_t word = 0;
+        uint32_t some = 0;
 #pragma unroll
-        for (int w = 0; w < PLAN_WORDS; ++w)
-            nonempty[w] = __ballot(bfirst[64 * w + t] < blast[64 * w + t]);
+        for (int w = 0; w < PLAN_WORDS; ++w) {
+            const int b = 64 * w + t, left = blast[b] - bfirst[b];
+            bucket[b] = (uint32_t)bfirst[b] | (uint32_t)left << 16;
+            const uint64_t m = __ballot(left > 0);
+            if (t == w)
+                word = m;
+            some |= m ? 1u << w : 0u;
+        }
+        auto word_of = [&](int w) -> uint64_t {
+            return (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(word >> 32), w) << 32 |
+                   (uint32_t)__builtin_amdgcn_readlane((int)word, w);
+        };
         int pos = nlarge, ntile = nlarge;
         while (pos < cnt) {
             if (t == 0 && ntile > 0)
@@ -126,30 +148,34 @@ __global__ __launch_bounds__(256) void plan_chunk_kernel(const int64_t *__restri
             int r = KNM_CAP, nseg = 0;
             while (nseg < KNM_MAX_SEG) {
                 // largest non-empty bucket b <= r
-                int found = -1;
-#pragma unroll
-                for (int w = PLAN_WORDS - 1; w >= 0; --w) {
-                    const int top = r - 64 * w;
-                    const uint64_t m = top < 0 ? 0 : (top >= 63 ? nonempty[w] : nonempty[w] & ((2ull << top) - 1));
-                    if (found < 0 && m)
-                        found = w * 64 + 63 - __clzll(m);
+                int w = r >> 6;
+                uint64_t m = word_of(w) & ((2ull << (r & 63)) - 1);
+                if (m == 0) {
+                    const uint32_t lower = some & ((1u << w) - 1);
+                    if (lower == 0)
+                        break;
+                    w = 31 - __clz(lower);
+                    m = word_of(w);
                 }
-                if (found < 0)
-                    break;
-                // as many of its items as fit
-                const int i0 = __builtin_amdgcn_readfirstlane(bfirst[found]);
-                const int left = __builtin_amdgcn_readfirstlane(blast[found]) - i0;
-                int take = found > 0 ? r / found : left;
+                const int found = w * 64 + 63 - __clzll(m);
+                // as many of its items as fit (r / found: the half keeps the quotient of these
+                // small integers away from a whole number)
+                const uint32_t bk = __builtin_amdgcn_readfirstlane(bucket[found]);
+                const int i0 = bk & 0xffff, left = bk >> 16;
+                int take = found > 0 ? (int)(((float)r + 0.5f) * __builtin_amdgcn_rcpf((float)found)) : left;
+                take = __builtin_amdgcn_readfirstlane(take);
                 take = take < left ? take : left;
                 take = take < KNM_MAX_SEG - nseg ? take : KNM_MAX_SEG - nseg;
                 for (int q = t; q < take; q += 64)
                     order[pos + q] = (uint16_t)(i0 + q);
                 if (t == 0)
-                    bfirst[found] = i0 + take;
-#pragma unroll
-                for (int w = 0; w < PLAN_WORDS; ++w)
-                    if (take == left && (found >> 6) == w)
-                        nonempty[w] &= ~(1ull << (found & 63));
+                    bucket[found] = (uint32_t)(i0 + take) | (uint32_t)(left - take) << 16;
+                if (take == left) {
+                    if (t == w)
+                        word &= ~(1ull << (found & 63));
+                    if (word_of(w) == 0)
+                        some &= ~(1u << w);
+                }
                 pos += take;
                 nseg += take;
                 r -= take * found;
@@ -165,7 +191,7 @@ __global__ __launch_bounds__(256) void plan_chunk_kernel(const int64_t *__restri
 
 // Global tile table: tile_start[base_c + j] = chunk c's j-th tile, n_tiles.
 __global__ __launch_bounds__(256) void plan_publish_kernel(const uint16_t *__restrict__ lists, int64_t n_chunks,
-                                                           int64_t N, int32_t *__restrict__ tile_start,
+                                                           int chunk, int64_t N, int32_t *__restrict__ tile_start,
                                                            int32_t *__restrict__ n_tiles, int64_t max_tiles,
                                                            int32_t *status)
 {
@@ -173,18 +199,18 @@ __global__ __launch_bounds__(256) void plan_publish_kernel(const uint16_t *__res
     const int64_t c = blockIdx.x;
     int64_t before = 0;
     for (int64_t q = threadIdx.x; q < c; q += 256)
-        before += lists[q * PLAN_C];
+        before += lists[q * chunk];
 #pragma unroll
     for (int o = 32; o >= 1; o >>= 1)
         before += __shfl_xor(before, o, 64);
     if ((threadIdx.x & 63) == 0)
         sum_s[threadIdx.x >> 6] = before;
     __syncthreads();
-    const int64_t base = (sum_s[0] + sum_s[1]) + (sum_s[2] + sum_s[3]), nt = lists[c * PLAN_C];
+    const int64_t base = (sum_s[0] + sum_s[1]) + (sum_s[2] + sum_s[3]), nt = lists[c * chunk];
     const bool bad = (*status != 0) || base + nt > max_tiles;
     if (!bad)
         for (int64_t j = threadIdx.x; j < nt; j += 256)
-            tile_start[base + j] = (int32_t)(c * PLAN_C + (j > 0 ? lists[c * PLAN_C + j] : 0));
+            tile_start[base + j] = (int32_t)(c * chunk + (j > 0 ? lists[c * chunk + j] : 0));
     if (c == n_chunks - 1 && threadIdx.x == 0) {
         if (bad) {
             if (base + nt > max_tiles)
@@ -197,14 +223,14 @@ __global__ __launch_bounds__(256) void plan_publish_kernel(const uint16_t *__res
     }
 }
 
-int64_t knm_max_tiles(int64_t N, int64_t n_atoms)
+int64_t knm_max_tiles(int64_t N, int64_t n_atoms, int chunk)
 {
     // Within a chunk, a tile closes only when the largest remaining
     // configuration does not fit, so two consecutive tiles hold more than
     // KNM_CAP atoms unless the first was closed by the configuration cap; each
     // chunk may end with one more partial tile.
     int64_t bound = 2 * ((n_atoms + KNM_CAP - 1) / KNM_CAP) + (N + KNM_MAX_SEG - 1) / KNM_MAX_SEG +
-                    knm_plan_chunks(N) + 1;
+                    plan_chunks(N, chunk) + 1;
     return bound < N ? bound : N;
 }
 
@@ -1036,14 +1062,14 @@ hipError_t launch_predict(const double *X, int64_t n_atoms, const int64_t *offse
     return hipGetLastError();
 }
 
-hipError_t launch_plan_tiles(const int64_t *offsets, int64_t N, int64_t n_atoms, const KnmPlan &p, int64_t max_tiles,
-                             int32_t *status, hipStream_t s)
+hipError_t launch_plan_tiles(const int64_t *offsets, int64_t N, int64_t n_atoms, int chunk, const KnmPlan &p,
+                             int64_t max_tiles, int32_t *status, hipStream_t s)
 {
-    const int64_t nc = knm_plan_chunks(N);
-    hipLaunchKernelGGL(plan_chunk_kernel, dim3((unsigned)nc), dim3(256), 0, s, offsets, N, n_atoms, p.cfg_list,
+    const int64_t nc = plan_chunks(N, chunk);
+    hipLaunchKernelGGL(plan_chunk_kernel, dim3((unsigned)nc), dim3(256), 0, s, offsets, N, n_atoms, chunk, p.cfg_list,
                        p.lists, status);
     hipLaunchKernelGGL(plan_publish_kernel, dim3((unsigned)nc), dim3(256), 0, s, (const uint16_t *)p.lists,
-                       nc, N, p.tile_start, p.n_tiles, max_tiles, status);
+                       nc, chunk, N, p.tile_start, p.n_tiles, max_tiles, status);
     return hipGetLastError();
 }
 
