@@ -497,6 +497,7 @@ __global__ __launch_bounds__(S::NT, sizeof(typename S::elem) == 8 && S::NT == 51
 // odd chunks, then the two sums), and its four waves form the products on MFMA, the factors'
 // operands read straight from L2.  One launch instead of three; 64-column workgroups of
 // scalar sums took 41 us for the narrow updates of the panel chain, this 11-13 us.
+constexpr int W_CHUNKS = 8;  // chunk partials that qr_w_kernel sums itself (an even number)
 struct WArgs {
     const double *Ta, *Tb, *H;  // row-major, T upper triangular with zeros below
     int tld, pwa, pwb;          // T_a's leading dimension (T_b and H: OB); pair widths
@@ -512,39 +513,49 @@ __global__ __launch_bounds__(256) void qr_w_kernel(QrWork w, WArgs a, TW *__rest
         const int ql = t & 15;
         const int64_t q = q0 + ql, step = (int64_t)OB2 * w.wp_ld;
         const int halves = a.pwb > 0 ? 2 : 1;
-        for (int h = 0; h < halves; ++h)
+        constexpr int NU = OB / 16;
+        for (int h = 0; h < halves; ++h) {
+            double v[NU][W_CHUNKS];  // all loads in flight
 #pragma unroll
-            for (int u = 0; u < OB / 16; ++u) {
+            for (int u = 0; u < NU; ++u) {
                 const int p = (t >> 4) + 16 * u;
-                double s0 = 0.0, s1 = 0.0;
-                if (q < a.nt && p < (h ? a.pwb : a.pwa)) {
-                    const double *src = w.wpart + (h * OB + p) * w.wp_ld + q;
-                    int64_t ch = 0;
-                    for (; ch + 1 < a.nch; ch += 2) {
-                        s0 += src[ch * step];
-                        s1 += src[(ch + 1) * step];
-                    }
-                    if (ch < a.nch)
-                        s0 += src[ch * step];
-                }
-                Ps[h * OB + p][ql] = s0 + s1;
+                const bool in = q < a.nt && p < (h ? a.pwb : a.pwa);
+                const double *src = w.wpart + (in ? (h * OB + p) * w.wp_ld + q : 0);
+#pragma unroll
+                for (int ch = 0; ch < W_CHUNKS; ++ch)
+                    v[u][ch] = in && ch < a.nch ? src[ch * step] : 0.0;
             }
+#pragma unroll
+            for (int u = 0; u < NU; ++u) {
+                double s0 = 0.0, s1 = 0.0;
+#pragma unroll
+                for (int ch = 0; ch < W_CHUNKS; ch += 2) {
+                    s0 += v[u][ch];
+                    s1 += v[u][ch + 1];
+                }
+                Ps[h * OB + (t >> 4) + 16 * u][ql] = s0 + s1;
+            }
+        }
     }
     __syncthreads();
     // rows 16 mb .. of T^T P (T upper triangular: terms s <= p), P rows from LDS row base
     auto tri = [&](const double *T, int ld, int mb, int base, int pw) {
-        d4 acc = d4{0.0, 0.0, 0.0, 0.0};
-        for (int sb = 0; sb <= mb; ++sb) {
-            double av[4];
+        double av[OB / 16][4];  // all loads in flight
+        const int p = 16 * mb + r;
+#pragma unroll
+        for (int sb = 0; sb < OB / 16; ++sb)
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-                const int sr = 16 * sb + 4 * e + g, p = 16 * mb + r;
-                av[e] = (sr < pw && p < pw) ? T[sr * ld + p] : 0.0;
+                const int sr = 16 * sb + 4 * e + g;
+                av[sb][e] = (sb <= mb && sr < pw && p < pw) ? T[sr * ld + p] : 0.0;
             }
+        d4 acc = d4{0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-            for (int e = 0; e < 4; ++e)
-                acc = Unit<double>::mfma(av[e], Ps[base + 16 * sb + 4 * e + g][r], acc);
-        }
+        for (int sb = 0; sb < OB / 16; ++sb)
+            if (sb <= mb)
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    acc = Unit<double>::mfma(av[sb][e], Ps[base + 16 * sb + 4 * e + g][r], acc);
         return acc;
     };
     auto put = [&](int prow, int pw, int mb, const d4 &acc) {
@@ -571,16 +582,19 @@ __global__ __launch_bounds__(256) void qr_w_kernel(QrWork w, WArgs a, TW *__rest
 #pragma unroll
         for (int e = 0; e < 4; ++e)
             pb[q][e] = Ps[OB + 16 * mb + g + 4 * e][r];
-        if (16 * mb < a.pwb)
-            for (int sb = 0; sb < OB / 16; ++sb) {
-                double av[4];
+        if (16 * mb < a.pwb) {
+            double av[OB / 16][4];  // zeros past pwa and pwb
+#pragma unroll
+            for (int sb = 0; sb < OB / 16; ++sb)
 #pragma unroll
                 for (int e = 0; e < 4; ++e)
-                    av[e] = a.H[(16 * sb + 4 * e + g) * OB + 16 * mb + r];  // zeros past pwa and pwb
+                    av[sb][e] = a.H[(16 * sb + 4 * e + g) * OB + 16 * mb + r];
+#pragma unroll
+            for (int sb = 0; sb < OB / 16; ++sb)
 #pragma unroll
                 for (int e = 0; e < 4; ++e)
-                    pb[q] = Unit<double>::mfma(-av[e], Ps[16 * sb + 4 * e + g][r], pb[q]);
-            }
+                    pb[q] = Unit<double>::mfma(-av[sb][e], Ps[16 * sb + 4 * e + g][r], pb[q]);
+        }
     }
     __syncthreads();
 #pragma unroll
@@ -611,7 +625,7 @@ __global__ __launch_bounds__(256) void qr_psum_kernel(QrWork w, int pw, int64_t 
     const int64_t step = (int64_t)OB2 * w.wp_ld;
     double s0 = 0.0, s1 = 0.0;
     int64_t ch = 0;
-#pragma unroll 4
+#pragma unroll 8
     for (; ch + 1 < nch; ch += 2) {
         s0 += src[ch * step];
         s1 += src[(ch + 1) * step];
@@ -635,6 +649,7 @@ __global__ __launch_bounds__(256) void qr_gsum_kernel(QrWork w, int pwb, int64_t
         const double *src = w.wpart + p * w.wp_ld + q;
         const int64_t step = (int64_t)OB2 * w.wp_ld;
         int64_t ch = 0;
+#pragma unroll 8
         for (; ch + 1 < nch; ch += 2) {
             s0 += src[ch * step];
             s1 += src[(ch + 1) * step];
@@ -647,15 +662,31 @@ __global__ __launch_bounds__(256) void qr_gsum_kernel(QrWork w, int pwb, int64_t
 
 // Combined compact-WY factor of two consecutive panels A | B:
 // T = [[T_A, -T_A G T_B], [0, T_B]] with G = Y_A^T Y_B (summed by qr_gsum_kernel).  The two
-// products run on MFMA, a wave per 16 rows (67 -> 25 us).
+// products run on MFMA, a wave per 16 rows; bound by the latency of its loads, all issued at
+// the start (67 us; 25 with loads one after the other; 8).
 __global__ __launch_bounds__(256) void qr_tcombine_kernel(QrWork w, const double *__restrict__ Gs,
                                                          double *__restrict__ Tout)
 {
-    __shared__ double G[NB][DL], X[NB][DL];
+    __shared__ double G[NB][DL], B[NB][DL];  // G, then T_A; T_B, then X
     const int t = threadIdx.x, lane = t & 63, wave = t >> 6, g = lane >> 4, r = lane & 15;
     const double *Ta = w.Tin, *Tb = w.Tin + NB * NB;
-    for (int idx = t; idx < NB * NB; idx += 256)
-        G[idx / NB][idx % NB] = Gs[idx];
+    constexpr int NQ = NB * NB / 256;
+    double gv[NQ], tav[NQ], tbv[NQ];  // all loads in flight
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) {
+        gv[q] = Gs[q * 256 + t];
+        tbv[q] = Tb[q * 256 + t];
+        tav[q] = Ta[q * 256 + t];
+    }
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) {
+        const int i = q * 4 + wave, c = lane;
+        G[i][c] = gv[q];
+        B[i][c] = tbv[q];
+        Tout[i * OB + c] = tav[q];
+        Tout[(NB + i) * OB + c] = 0.0;
+        Tout[(NB + i) * OB + NB + c] = tbv[q];
+    }
     __syncthreads();
     d4 acc[4];
 #pragma unroll
@@ -663,29 +694,24 @@ __global__ __launch_bounds__(256) void qr_tcombine_kernel(QrWork w, const double
         acc[c] = d4{0.0, 0.0, 0.0, 0.0};
 #pragma unroll
         for (int k = 0; k < 4 * (c + 1); ++k)
-            acc[c] = mfma16(G[16 * wave + r][4 * k + g], Tb[(4 * k + g) * NB + 16 * c + r], acc[c]);
+            acc[c] = mfma16(G[16 * wave + r][4 * k + g], B[4 * k + g][16 * c + r], acc[c]);
     }
+    __syncthreads();
 #pragma unroll
     for (int c = 0; c < 4; ++c)
 #pragma unroll
         for (int e = 0; e < 4; ++e)
-            X[16 * wave + g + 4 * e][16 * c + r] = acc[c][e];
-    __syncthreads();
-    for (int idx = t; idx < NB * NB; idx += 256)
-        G[idx / NB][idx % NB] = Ta[idx];
-    for (int idx = t; idx < OB * OB; idx += 256) {
-        const int i = idx / OB, c = idx % OB;
-        if (c < NB)
-            Tout[idx] = i < NB ? Ta[i * NB + c] : 0.0;
-        else if (i >= NB)
-            Tout[idx] = Tb[(i - NB) * NB + c - NB];
-    }
+            B[16 * wave + g + 4 * e][16 * c + r] = acc[c][e];
+#pragma unroll
+    for (int q = 0; q < NQ; ++q)
+        G[q * 4 + wave][lane] = tav[q];
     __syncthreads();
 #pragma unroll
     for (int c = 0; c < 4; ++c) {  // -T_A X (T_A's zeros below its diagonal included)
         acc[c] = d4{0.0, 0.0, 0.0, 0.0};
-        for (int k = 4 * wave; k < NB / 4; ++k)
-            acc[c] = mfma16(-G[16 * wave + r][4 * k + g], X[4 * k + g][16 * c + r], acc[c]);
+#pragma unroll
+        for (int k = 0; k < NB / 4; ++k)
+            acc[c] = mfma16(-G[16 * wave + r][4 * k + g], B[4 * k + g][16 * c + r], acc[c]);
 #pragma unroll
         for (int e = 0; e < 4; ++e)
             Tout[(16 * wave + g + 4 * e) * OB + NB + 16 * c + r] = acc[c][e];
@@ -709,12 +735,22 @@ __global__ __launch_bounds__(256) void qr_hmat_kernel(const double *__restrict__
     const int bi = blockIdx.x >> 1, bj = 4 * (blockIdx.x & 1) + wave;
     d4 acc = d4{0.0, 0.0, 0.0, 0.0};
     const int i = 16 * bi + r, j = 16 * bj + r;
-    for (int k0 = 16 * bi; k0 < pwa; k0 += 4) {
-        const int k = k0 + g;
-        const double a = (i < pwa && k < pwa) ? Ta[i * tld + k] : 0.0;
-        const double b = (k < pwa && j < pwb) ? G[k * OB + j] : 0.0;
-        acc = mfma16(a, b, acc);
-    }
+    double av[OB / 16][4], bv[OB / 16][4];  // all loads in flight
+#pragma unroll
+    for (int kb = 0; kb < OB / 16; ++kb)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const int k = 16 * kb + 4 * e + g;
+            const bool in = kb >= bi && k < pwa;
+            av[kb][e] = in && i < pwa ? Ta[i * tld + k] : 0.0;
+            bv[kb][e] = in && j < pwb ? G[k * OB + j] : 0.0;
+        }
+#pragma unroll
+    for (int kb = 0; kb < OB / 16; ++kb)
+        if (kb >= bi)
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                acc = mfma16(av[kb][e], bv[kb][e], acc);
 #pragma unroll
     for (int e = 0; e < 4; ++e)
         H[(16 * bi + g + 4 * e) * OB + j] = acc[e];
@@ -903,6 +939,11 @@ struct BlockT {
     int pw() const { return pwa + pwb; }
 };
 
+// Workgroups of a trailing update's split-K product, about: two per CU.  More chunks write and
+// read more partials (2,048: 9.45 ms for the QR of 18,250 x 2,250 in FP32, 512: 9.26; 61,500 x
+// 1,500 in FP64 11.8 and 11.65, 256: 12.2).
+constexpr int64_t SPLIT_WGS = 512;
+
 // C := (I - Y T Y^T)^T C for the columns c0 .. c0+nt, Y the block at (J, J).
 template <class T>
 static void apply_block(const QrWork &wf, int64_t J, const BlockT &bt, int64_t c0, int64_t nt, hipStream_t s)
@@ -913,8 +954,8 @@ static void apply_block(const QrWork &wf, int64_t J, const BlockT &bt, int64_t c
     const QrWork w = rows_to(wf, J + pw);
     const int64_t rows = w.m - J;
     WArgs a{};
-    a.nch = launch_wpart<T>(w, J, pw, c0, nt, 0, J, w.split_wgs > 0 ? w.split_wgs : 2048, s);
-    if (a.nch > 8) {
+    a.nch = launch_wpart<T>(w, J, pw, c0, nt, 0, J, w.split_wgs > 0 ? w.split_wgs : SPLIT_WGS, s);
+    if (a.nch > W_CHUNKS) {
         hipLaunchKernelGGL(qr_psum_kernel, dim3((unsigned)(((int64_t)pw * nt + 255) / 256)), dim3(256), 0, s, w, pw,
                            a.nch, nt);
         a.nch = 1;
