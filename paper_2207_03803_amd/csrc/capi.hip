@@ -32,7 +32,7 @@ struct Layout {
            off_T2 = 0, off_wpart_s = 0, off_W_s = 0, off_W32_s = 0, off_plan = 0, total = 0;
     // mixed precision only
     bool mixed = false;
-    size_t off_A32 = 0, off_W32 = 0, off_r = 0, off_s = 0, off_z = 0, off_dc = 0, off_p = 0, off_q = 0, off_part = 0,
+    size_t off_A32 = 0, off_W32 = 0, off_r = 0, off_s = 0, off_z = 0, off_dc = 0, off_p = 0, off_q = 0,
            off_rnorm = 0, off_flags = 0, off_stats = 0;
     size_t off_diag = 0;  // diagnostics of the solution (eta, error estimate)
     // low-precision K_NM (GAP_MIXED_BF16 / GAP_MIXED_FP16) only: rounded descriptors
@@ -118,7 +118,7 @@ Layout make_layout(int64_t NE, int64_t n_atoms, int64_t M, int32_t precision, in
     L.off_counters = take(sizeof(unsigned) * N_COUNTERS);
     L.off_status = take(sizeof(int32_t) * 4);
     L.off_tflags = take(sizeof(int32_t) * 2);
-    L.off_tx = take(sizeof(unsigned long long) * (size_t)M);
+    L.off_tx = take(sizeof(unsigned long long) * 2 * (size_t)M);
     L.off_cq_part = takep(sizeof(double) * (size_t)CQ_PART);
     L.off_cq_G = takep(sizeof(double) * 4 * QR_NB * QR_NB);
     L.off_cq_R = takep(sizeof(double) * 4 * QR_NB * QR_NB);
@@ -136,8 +136,7 @@ Layout make_layout(int64_t NE, int64_t n_atoms, int64_t M, int32_t precision, in
         L.off_dc = takep(sizeof(double) * (size_t)M);
         L.off_p = takep(sizeof(double) * (size_t)M);
         L.off_q = takep(sizeof(double) * (size_t)L.m);
-        L.off_part = takep(sizeof(double) * 8 * (size_t)L.m);
-        L.off_rnorm = takep(sizeof(double) * (size_t)((L.m + 255) / 256 + 1));
+        L.off_rnorm = takep(sizeof(double) * (size_t)((L.m + 63) / 64));
         L.off_flags = take(sizeof(int32_t) * 4);
         L.off_stats = takep(sizeof(double) * 4);
     }
@@ -213,7 +212,7 @@ struct gap_handle_s {
         d.sc = base + 14 * M;
         d.sum_part = d.sc + 4;
         d.counter = counters() + 9;
-        d.tail2 = misc();
+        d.r2 = misc();
         d.iters = (p.flags & GAP_FLAG_ERROR_ESTIMATE) ? 16 : 0;
         d.sync = tsync();
         return d;
@@ -254,13 +253,6 @@ __global__ void poison_kernel(uint32_t *p, int64_t n)
 {
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
         p[i] = 0xFFFFFFFFu;
-}
-
-__global__ void copy_kernel(const double *src, double *dst, int64_t n)
-{
-    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (i < n)
-        dst[i] = src[i];
 }
 
 // Where gap_predict reports malformed offsets: the fit's status word, or, on a
@@ -937,15 +929,13 @@ gap_status gap_solve(gap_handle h, const double *y, double *c_out, gap_solve_inf
     w.cq_R = h->at<double>(L.off_cq_R);
     w.cq_counters = h->counters() + 16;
     w.status = h->status();
-    double *rhs = h->at<double>(L.off_rhs);
     if (!L.mixed) {
         h->mark(4, false);
         GAP_TRY(dev(launch_geqrf(w, s, (use_lookahead(h) && h->la.join) ? &h->la : nullptr)));
         h->mark(4, true);
         const double *qtb = A + L.M * L.lda;
         h->mark(5, false);
-        hipLaunchKernelGGL(copy_kernel, dim3((unsigned)((L.M + 255) / 256)), dim3(256), 0, s, qtb, rhs, L.M);
-        GAP_TRY(dev(launch_trsv_upper(A, L.lda, L.M, rhs, c_out, h->tsync(), s)));
+        GAP_TRY(dev(launch_trsv_upper(A, L.lda, L.M, qtb, c_out, h->tsync(), s)));
         h->mark(5, true);
         GAP_TRY(dev(launch_sumsq(qtb + L.M, L.N, h->misc(), h->misc() + 1, h->counters() + 8, s)));
         h->mark(8, false);
@@ -968,8 +958,9 @@ gap_status gap_solve(gap_handle h, const double *y, double *c_out, gap_solve_inf
         GAP_TRY(dev(launch_geqrf(w, s, (use_lookahead(h) && h->la.join) ? &h->la : nullptr)));
         h->mark(4, true);
         h->mark(5, false);
+        double *rhs = h->at<double>(L.off_rhs);
         GAP_TRY(dev(launch_copy_f32_f64(A32 + L.M * L.lda, rhs, L.M, s)));
-        GAP_TRY(dev(launch_trsv_upper_f32(A32, L.lda, L.M, rhs, c_out, h->tsync(), nullptr, s)));
+        GAP_TRY(dev(launch_trsv_upper_f32(A32, L.lda, L.M, rhs, c_out, h->tsync(), s)));
         h->mark(5, true);
         RefineWork rw{};
         rw.A = A;
@@ -984,7 +975,6 @@ gap_status gap_solve(gap_handle h, const double *y, double *c_out, gap_solve_inf
         rw.dc = h->at<double>(L.off_dc);
         rw.p = h->at<double>(L.off_p);
         rw.q = h->at<double>(L.off_q);
-        rw.part = h->at<double>(L.off_part);
         rw.rnorm_part = h->at<double>(L.off_rnorm);
         rw.done = h->at<int32_t>(L.off_flags);
         rw.iters = h->at<int32_t>(L.off_flags) + 1;
@@ -996,8 +986,6 @@ gap_status gap_solve(gap_handle h, const double *y, double *c_out, gap_solve_inf
         h->mark(6, false);
         GAP_TRY(dev(launch_refine(rw, h->p.max_refine_iters, s)));
         h->mark(6, true);
-        GAP_TRY(dev(launch_check_finite(c_out, L.M, h->status(), s)));
-        hipLaunchKernelGGL(copy_kernel, dim3(1), dim3(256), 0, s, rw.stats, h->misc(), (int64_t)1);
         // the refinement's last pass left A^T r at the returned c in rw.s
         h->mark(8, false);
         GAP_TRY(dev(launch_diag_mixed(h->diag(rw.s), A32, A + L.M * L.lda, L.m, rw.stats, c_out, h->diag_out(), s)));

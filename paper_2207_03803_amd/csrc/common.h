@@ -51,6 +51,15 @@ DEV bool arrive_last(unsigned *counter, unsigned nblocks, int *flag_lds)
 // Publish this workgroup's global writes before it arrives (all threads call).
 DEV void release_writes() { __atomic_thread_fence(__ATOMIC_RELEASE); }
 
+// Value of v in lane `lane` (uniform) of the wave.
+DEV double readlane_d(double v, int lane)
+{
+    const long long b = __double_as_longlong(v);
+    const int lo = __builtin_amdgcn_readlane((int)(b & 0xffffffffll), lane);
+    const int hi = __builtin_amdgcn_readlane((int)(b >> 32), lane);
+    return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
+}
+
 // Wave-wide sum with a fixed butterfly order (deterministic).
 DEV double wave_sum(double v)
 {

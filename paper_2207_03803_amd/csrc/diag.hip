@@ -127,48 +127,42 @@ __global__ __launch_bounds__(256) void power_normalise_kernel(const double *y, c
 }
 
 // One workgroup: eta and the error estimate from the pieces.
-//   s [n] A^T r;  c [n];  partR [n] column sums of R^2;  sc[0] ||b||^2 (plus
-//   *tail2 when non-null), sc[1] ||r||^2, sc[2] sigma_max^2 and sc[3]
-//   1 / sigma_min^2 (0: no estimate).  out[0] eta, out[1] the error estimate
+//   s [n] A^T r;  c [n] (checked: DST_ENONFINITE);  partR [n] column sums of R^2;  sc[0] ||b||^2
+//   (plus *r2 with tail set), *r2 = ||r||^2 (left in *keep), and with an estimate sc[2]
+//   sigma_max^2 and sc[3] 1 / sigma_min^2.  out[0] eta, out[1] the error estimate
 //   (-1 without one), out[2] kappa.
 __global__ __launch_bounds__(256) void diag_final_kernel(const double *s, const double *c, const double *partR,
-                                                         int64_t n, const double *sc, const double *tail2,
-                                                         double *out)
+                                                         int64_t n, const double *sc, const double *r2, bool tail,
+                                                         bool estimate, double *keep, double *out, int32_t *status)
 {
     __shared__ double red[4];
     double as = 0.0, ac = 0.0, ar = 0.0;
     for (int64_t i = threadIdx.x; i < n; i += 256) {
+        if (!isfinite(c[i]))
+            set_status(status, DST_ENONFINITE);
         as += s[i] * s[i];
         ac += c[i] * c[i];
         ar += partR[i];
     }
     const double s2 = dblock_sum(as, red);
     const double c2 = dblock_sum(ac, red);
-    const double r2 = dblock_sum(ar, red);
+    const double a2 = dblock_sum(ar, red);
     if (threadIdx.x != 0)
         return;
-    const double b2 = sc[0] + (tail2 ? *tail2 : 0.0);
-    const double nA = sqrt(r2), nc = sqrt(c2), nb = sqrt(b2);
+    const double rr = *r2;
+    *keep = rr;
+    const double b2 = sc[0] + (tail ? rr : 0.0);
+    const double nA = sqrt(a2), nc = sqrt(c2), nb = sqrt(b2);
     const double den = nA * (nA * nc + nb);
     out[0] = den > 0.0 ? sqrt(s2) / den : 0.0;
     out[1] = -1.0;
-    if (sc[2] > 0.0 && sc[3] > 0.0 && nc > 0.0) {
+    if (estimate && sc[2] > 0.0 && sc[3] > 0.0 && nc > 0.0) {
         const double smax = sqrt(sc[2]), smin = 1.0 / sqrt(sc[3]);
         const double kappa = smax / smin;
         const double u = 1.1102230246251565e-16;  // 2^-53
-        const double rn = sqrt(sc[1] > 0.0 ? sc[1] : 0.0);
+        const double rn = sqrt(rr > 0.0 ? rr : 0.0);
         out[1] = u * (kappa + kappa * kappa * rn / (smax * nc));
         out[2] = kappa;
-    }
-}
-
-__global__ void diag_scalars_kernel(double *sc, const double *r2)
-{
-    if (threadIdx.x == 0) {
-        sc[0] = 0.0;
-        sc[1] = r2 ? *r2 : 0.0;
-        sc[2] = 0.0;
-        sc[3] = 0.0;
     }
 }
 
@@ -199,11 +193,11 @@ static hipError_t estimate(const DiagWork &d, const TR *R, hipStream_t s)
         if constexpr (sizeof(TR) == 8) {
             e = launch_trsv_upper_t(reinterpret_cast<const double *>(R), d.ld, n, x, y, d.sync, s);
             if (e == hipSuccess)
-                e = launch_trsv_upper_nc(reinterpret_cast<const double *>(R), d.ld, n, y, z, d.sync, s);
+                e = launch_trsv_upper(reinterpret_cast<const double *>(R), d.ld, n, y, z, d.sync, s);
         } else {
-            e = launch_trsv_upper_t_f32(reinterpret_cast<const float *>(R), d.ld, n, x, y, d.sync, nullptr, s);
+            e = launch_trsv_upper_t_f32(reinterpret_cast<const float *>(R), d.ld, n, x, y, d.sync, s);
             if (e == hipSuccess)
-                e = launch_trsv_upper_f32(reinterpret_cast<const float *>(R), d.ld, n, y, z, d.sync, nullptr, s);
+                e = launch_trsv_upper_f32(reinterpret_cast<const float *>(R), d.ld, n, y, z, d.sync, s);
         }
         if (e != hipSuccess)
             return e;
@@ -216,8 +210,7 @@ hipError_t launch_diag_fp64(const DiagWork &d, const double *R, const double *qt
                             hipStream_t s)
 {
     const int64_t n = d.n;
-    // ||r||^2 of the QR solution is the minimum loss ||(Q^T b)[n:]||^2 (*d.tail2)
-    hipLaunchKernelGGL(diag_scalars_kernel, dim3(1), dim3(64), 0, s, d.sc, d.tail2);
+    // ||r||^2 of the QR solution is the minimum loss ||(Q^T b)[n:]||^2 (*d.r2)
     hipLaunchKernelGGL((sumsq_upper_kernel<double>), dim3((unsigned)n), dim3(256), 0, s, R, d.ld, n, d.partR);
     // t = (Q^T b)[0:n] - R c, then A^T r = R^T t
     rx<double>(R, d.ld, n, c, qtb, true, d.part, d.t, s);
@@ -228,7 +221,8 @@ hipError_t launch_diag_fp64(const DiagWork &d, const double *R, const double *qt
         e = estimate<double>(d, R, s);
     if (e != hipSuccess)
         return e;
-    hipLaunchKernelGGL(diag_final_kernel, dim3(1), dim3(256), 0, s, d.g, c, d.partR, n, d.sc, d.tail2, out);
+    hipLaunchKernelGGL(diag_final_kernel, dim3(1), dim3(256), 0, s, d.g, c, d.partR, n,
+                       (const double *)d.sc, d.r2, true, d.iters > 0, d.r2, out, d.sync.status);
     return hipGetLastError();
 }
 
@@ -237,14 +231,14 @@ hipError_t launch_diag_mixed(const DiagWork &d, const float *R32, const double *
 {
     const int64_t n = d.n;
     // d.g holds A^T r at the returned c (the refinement's last pass); ||r||^2 = *r2
-    hipLaunchKernelGGL(diag_scalars_kernel, dim3(1), dim3(64), 0, s, d.sc, r2);
     hipLaunchKernelGGL((sumsq_upper_kernel<float>), dim3((unsigned)n), dim3(256), 0, s, R32, d.ld, n, d.partR);
     hipError_t e = launch_sumsq(bcol, m, d.sc, d.sum_part, d.counter, s);
     if (e == hipSuccess && d.iters > 0)
         e = estimate<float>(d, R32, s);
     if (e != hipSuccess)
         return e;
-    hipLaunchKernelGGL(diag_final_kernel, dim3(1), dim3(256), 0, s, d.g, c, d.partR, n, d.sc, nullptr, out);
+    hipLaunchKernelGGL(diag_final_kernel, dim3(1), dim3(256), 0, s, d.g, c, d.partR, n,
+                       (const double *)d.sc, r2, false, d.iters > 0, d.r2, out, d.sync.status);
     return hipGetLastError();
 }
 

@@ -117,21 +117,18 @@ struct TrsvSync {
     int32_t *status;
 };
 hipError_t launch_trsv_clear(const TrsvSync &sync, int64_t n, hipStream_t s);
-// Solve R c = rhs for the n x n upper triangle of R (column-major, ld); then
-// check c is finite (DST_ENONFINITE otherwise).
-hipError_t launch_trsv_upper(const double *R, int64_t ld, int64_t n, const double *rhs, double *c,
-                             const TrsvSync &sync, hipStream_t s);
-// Same with R stored in FP32 (FP64 arithmetic).
+// Solve R x = rhs for the n x n upper triangle of R (column-major, ld), stored in FP32 (FP64
+// arithmetic).
 hipError_t launch_trsv_upper_f32(const float *R, int64_t ld, int64_t n, const double *rhs, double *x,
-                                 const TrsvSync &sync, const int32_t *skip, hipStream_t s);
-// FP64 R without the finiteness check, and R^T x = rhs with the FP64 R.
-hipError_t launch_trsv_upper_nc(const double *R, int64_t ld, int64_t n, const double *rhs, double *x,
-                                const TrsvSync &sync, hipStream_t s);
+                                 const TrsvSync &sync, hipStream_t s);
+// The same with the FP64 R, and R^T x = rhs.
+hipError_t launch_trsv_upper(const double *R, int64_t ld, int64_t n, const double *rhs, double *x,
+                             const TrsvSync &sync, hipStream_t s);
 hipError_t launch_trsv_upper_t(const double *R, int64_t ld, int64_t n, const double *rhs, double *x,
                                const TrsvSync &sync, hipStream_t s);
 // Solve R^T x = rhs (forward substitution) for the FP32-stored upper R.
 hipError_t launch_trsv_upper_t_f32(const float *R, int64_t ld, int64_t n, const double *rhs, double *x,
-                                   const TrsvSync &sync, const int32_t *skip, hipStream_t s);
+                                   const TrsvSync &sync, hipStream_t s);
 hipError_t launch_copy_f32_f64(const float *src, double *dst, int64_t n, hipStream_t s);
 hipError_t launch_sumsq(const double *x, int64_t n, double *out, double *part, unsigned *counter,
                         hipStream_t s);
@@ -146,8 +143,7 @@ struct RefineWork {
     double *s, *z, *dc;  // [n] work
     double *p;           // [n] CGLS search direction
     double *q;           // [m] A p
-    double *part;        // [8 * m] column-chunk partials of A c (A p)
-    double *rnorm_part;  // [ceil(m / 256)] partial ||r||^2 (||q||^2)
+    double *rnorm_part;  // [ceil(m / 64)] partial ||r||^2 (||q||^2)
     int32_t *done;       // convergence flag
     int32_t *iters;      // [0] iterations done, [1] of them CGLS steps
     int32_t *mode;       // refinement stage: CSNE, CGLS start, CGLS step
@@ -176,14 +172,15 @@ struct DiagWork {
     double *sc;          // [4] scalars
     double *sum_part;    // [256] partials of launch_sumsq
     unsigned *counter;   // its arrival counter (zero)
-    const double *tail2; // FP64: minimum loss ||(Q^T b)[n:]||^2 (device scalar)
+    double *r2;          // ||r||^2 (device scalar; FP64: the minimum loss ||(Q^T b)[n:]||^2, given)
     int iters;           // steps of each iteration (0: no estimate)
     TrsvSync sync;
 };
 hipError_t launch_diag_fp64(const DiagWork &d, const double *R, const double *qtb, const double *c, double *out,
                             hipStream_t s);
 // Mixed precision: d.g already holds A^T r at c (FP64 A); r2 = device ||r||^2;
-// bcol = the FP64 b (m entries); R32 = the FP32 factor.
+// bcol = the FP64 b (m entries); R32 = the FP32 factor.  Both check that c is finite
+// (DST_ENONFINITE otherwise).
 hipError_t launch_diag_mixed(const DiagWork &d, const float *R32, const double *bcol, int64_t m, const double *r2,
                              const double *c, double *out, hipStream_t s);
 
@@ -195,6 +192,5 @@ hipError_t launch_fill(double *p, int64_t n, double v, hipStream_t s);
 // Zero rows [r0, r1) of columns [c0, c1) of a column-major matrix.
 hipError_t launch_zero_block(double *A, int64_t lda, int64_t r0, int64_t r1, int64_t c0, int64_t c1,
                              hipStream_t s);
-hipError_t launch_check_finite(const double *x, int64_t n, int32_t *status, hipStream_t s);
 
 }  // namespace gap

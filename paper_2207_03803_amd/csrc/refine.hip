@@ -19,17 +19,22 @@
 // Its rate is set by the spread of the singular values of A R^-1, so it needs
 // no bound on u_32 kappa(A).
 //
-// Both stages run the same kernel sequence per iteration, steered by a mode
-// word on the device.  Iterations stop on the device once the step is
+// Both stages run the same three kernels per iteration, steered by a mode
+// word on the device: the product with A, the product with A^T, and the two triangular solves
+// with the end of the step.  A CGLS step's r -= alpha q is taken where r is next read: on the
+// way in the product with A^T, and by the rows' own workgroups when they form the next q.
+// Iterations stop on the device once the step is
 // <= tol ||c|| (or once it stops halving at a level <= 1e-9 ||c||, the FP64
 // rounding floor): later iterations' kernels see the flag and return at once,
-// so the loop needs no host synchronisation.
-#include "kernels.h"
+// so the loop needs no host synchronisation.  (With seven launches per
+// iteration, four of them for vectors, an iteration after the last cost 20 us instead of 10, and
+// one at 2,500 x 500 71 us instead of 53.)
+#include "trsv.h"
 
 namespace gap {
 
-constexpr int RB = 256;   // rows per workgroup in the residual
-constexpr int RCH = 8;    // column chunks of the residual product
+constexpr int RB = 64;    // rows per workgroup in the residual
+constexpr int RCH = 16;   // its column chunks, one per wave
 constexpr double STALL_OK = 1e-9;  // a stalled correction this small counts as converged
 constexpr int MODE_CSNE = 0, MODE_CG_START = 1, MODE_CG = 2;
 
@@ -83,93 +88,100 @@ __device__ __forceinline__ double block_sum(double v, double *red)
     return (red[0] + red[1]) + (red[2] + red[3]);
 }
 
-// Column-chunk partials of A v for rows [blockIdx.x*256, +256); v is c, or p
-// in the CGLS steps.
-__global__ __launch_bounds__(256) void resid_part_kernel(RefineWork w)
+// r = b - A c, or q = A p in the CGLS steps (after the last step's r -= alpha q), for rows
+// [64 blockIdx.x, +64): one column chunk per wave, added in order; partial ||r||^2 (||q||^2) per
+// workgroup.  FINAL: after the loop, the residual at the returned c; whether the loop converged
+// (status ENOCONV otherwise).  Bound by the read of A (18,250 x 2,250: 70 us, 4.7 TB/s;
+// 82 us in two launches).
+template <bool FINAL>
+__global__ __launch_bounds__(RCH * 64) void resid_kernel(RefineWork w)
 {
-    if (*w.done)
+    __shared__ double red[RCH][RB];
+    const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
+    if (FINAL) {
+        if (blockIdx.x == 0 && t == 0 && !*w.done)
+            set_status(w.status, DST_ENOCONV);
+    } else if (*w.done) {
         return;
-    const double *v = (*w.mode == MODE_CG) ? w.p : w.c;
-    const int64_t r = (int64_t)blockIdx.x * RB + threadIdx.x;
-    const int64_t ch = blockIdx.y;
+    }
+    const bool cg = !FINAL && *w.mode == MODE_CG;
+    const double *v = cg ? w.p : w.c;
+    const int64_t r = (int64_t)blockIdx.x * RB + lane;
     const int64_t per = (w.n + RCH - 1) / RCH;
-    const int64_t j0 = ch * per;
+    const int64_t j0 = wave * per;
     const int64_t j1 = (j0 + per) < w.n ? (j0 + per) : w.n;
-    double acc0 = 0.0, acc1 = 0.0;
-    if (r < w.m) {
-        int64_t j = j0;
-        for (; j + 1 < j1; j += 2) {
-            acc0 += w.A[j * w.lda + r] * v[j];
-            acc1 += w.A[(j + 1) * w.lda + r] * v[j + 1];
-        }
-        if (j < j1)
-            acc0 += w.A[j * w.lda + r] * v[j];
-        w.part[ch * w.m + r] = acc0 + acc1;
+    const double *col = w.A + (r < w.m ? r : w.m - 1);
+    double acc[4] = {0.0, 0.0, 0.0, 0.0};
+    int64_t j = j0;
+    for (; j + 8 <= j1; j += 8) {
+        double x[8];
+#pragma unroll
+        for (int k = 0; k < 8; ++k)
+            x[k] = col[(j + k) * w.lda];
+#pragma unroll
+        for (int k = 0; k < 8; ++k)
+            acc[k & 3] += x[k] * v[j + k];
     }
-}
-
-// Sum of the partials (chunks in order): r = b - A c, or q = A p in the CGLS
-// steps; partial ||r||^2 (||q||^2) per workgroup.
-__global__ __launch_bounds__(256) void resid_sum_kernel(RefineWork w)
-{
-    __shared__ double red[4];
-    if (*w.done)
+    for (; j < j1; ++j)
+        acc[0] += col[j * w.lda] * v[j];
+    red[wave][lane] = (acc[0] + acc[1]) + (acc[2] + acc[3]);
+    __syncthreads();
+    if (wave != 0)
         return;
-    const bool cg = *w.mode == MODE_CG;
-    const int64_t r = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    double v = 0.0;
+    double ac = 0.0;
+#pragma unroll
+    for (int ch = 0; ch < RCH; ++ch)
+        ac += red[ch][lane];
+    double o = 0.0;
     if (r < w.m) {
-        double ac = 0.0;
-        for (int ch = 0; ch < RCH; ++ch)
-            ac += w.part[ch * w.m + r];
         if (cg) {
-            v = ac;
-            w.q[r] = v;
+            o = ac;
+            const double alpha = w.stats[2];
+            if (alpha != 0.0)  // zero: no step yet, and no q
+                w.r[r] = fma(-alpha, w.q[r], w.r[r]);
+            w.q[r] = o;
         } else {
-            v = w.A[w.n * w.lda + r] - ac;  // b is column n of [A | b]
-            w.r[r] = v;
+            o = w.A[w.n * w.lda + r] - ac;  // b is column n of [A | b]
+            w.r[r] = o;
         }
     }
-    const double sq = block_sum(v * v, red);
-    if (threadIdx.x == 0)
+    const double sq = wave_sum(o * o);
+    if (lane == 0)
         w.rnorm_part[blockIdx.x] = sq;
 }
 
-// CGLS step, rows: alpha = gamma / ||q||^2 (every workgroup sums the same
-// partials in the same order), r -= alpha q.
-__global__ __launch_bounds__(256) void cg_step_kernel(RefineWork w, int64_t nparts)
+// s_j = sum_i A[i][j] r[i], one column per workgroup (fixed-order reduction); in the CGLS steps
+// r is r - alpha q, alpha = gamma / ||q||^2 (every workgroup sums the same partials in the same
+// order).  Otherwise the first workgroup keeps ||r||^2.
+template <bool FINAL>
+__global__ __launch_bounds__(256) void atr_kernel(RefineWork w, int64_t nparts)
 {
-    __shared__ double red[4];
-    if (*w.done || *w.mode != MODE_CG)
+    __shared__ double red[4], red2[4];
+    if (!FINAL && *w.done)
         return;
-    double a = 0.0;
-    for (int64_t b = threadIdx.x; b < nparts; b += 256)
-        a += w.rnorm_part[b];
-    const double qq = block_sum(a, red);
-    const double alpha = qq > 0.0 ? w.stats[3] / qq : 0.0;
-    const int64_t r = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (r < w.m)
-        w.r[r] -= alpha * w.q[r];
-    if (blockIdx.x == 0 && threadIdx.x == 0)
-        w.stats[2] = alpha;
-}
-
-// s_j = sum_i A[i][j] r[i], one column per workgroup (fixed-order reduction).
-__global__ __launch_bounds__(256) void atr_kernel(RefineWork w)
-{
-    __shared__ double red[4];
-    if (*w.done)
-        return;
+    const bool cg = !FINAL && *w.mode == MODE_CG;
     const int64_t j = blockIdx.x;
+    double alpha = 0.0;
+    if (cg || j == 0) {
+        double a = 0.0;
+        for (int64_t b = threadIdx.x; b < nparts; b += 256)
+            a += w.rnorm_part[b];
+        const double qq = block_sum(a, red2);
+        if (cg)
+            alpha = qq > 0.0 ? w.stats[3] / qq : 0.0;
+        if (j == 0 && threadIdx.x == 0)
+            w.stats[cg ? 2 : 0] = cg ? alpha : qq;
+    }
     const double *col = w.A + j * w.lda;
+    auto at = [&](int64_t i) { return cg ? fma(-alpha, w.q[i], w.r[i]) : w.r[i]; };
     double a0 = 0.0, a1 = 0.0;
     int64_t i = threadIdx.x;
     for (; i + 256 < w.m; i += 512) {
-        a0 += col[i] * w.r[i];
-        a1 += col[i + 256] * w.r[i + 256];
+        a0 += col[i] * at(i);
+        a1 += col[i + 256] * at(i + 256);
     }
     if (i < w.m)
-        a0 += col[i] * w.r[i];
+        a0 += col[i] * at(i);
     const double v = block_sum(a0 + a1, red);
     if (threadIdx.x == 0)
         w.s[j] = v;
@@ -180,15 +192,13 @@ __global__ __launch_bounds__(256) void atr_kernel(RefineWork w)
 //   CSNE:       c += dc unless the switch to CGLS drops a grown correction;
 //               convergence test on ||dc|| / ||c + dc||.
 //   CGLS start: p = dc, gamma = ||z||^2.
-//   CGLS step:  c += alpha p (alpha from cg_step_kernel), convergence test on
+//   CGLS step:  c += alpha p (alpha from atr_kernel), convergence test on
 //               ||alpha p|| / ||c||, then p = dc + (||z||^2 / gamma) p.
-__global__ __launch_bounds__(256) void refine_update_kernel(RefineWork w, int64_t nparts)
+DEV void refine_update(const RefineWork &w)
 {
     __shared__ double red[3][4];
     __shared__ int act;
     __shared__ double beta;
-    if (*w.done)
-        return;
     const int mode = *w.mode;
     const double alpha = w.stats[2];
     double a0 = 0.0, a1 = 0.0, a2 = 0.0;
@@ -230,10 +240,6 @@ __global__ __launch_bounds__(256) void refine_update_kernel(RefineWork w, int64_
         w.iters[0] += 1;
         int a = 0;  // 0: nothing, 1: c += dc, 2: p = dc, 3: p = dc + beta p
         if (mode == MODE_CSNE) {
-            double rn = 0.0;
-            for (int64_t b = 0; b < nparts; ++b)
-                rn += w.rnorm_part[b];
-            w.stats[0] = rn;  // ||r||^2 before this correction
             const bool halving = ratio <= 0.5 * prev;
             // converged: the correction is below tol; or it has reached the FP64
             // rounding floor (stopped halving) at a level already below STALL_OK
@@ -246,6 +252,7 @@ __global__ __launch_bounds__(256) void refine_update_kernel(RefineWork w, int64_
                 *w.done = 1;
             w.stats[1] = ratio;
         } else if (mode == MODE_CG_START) {
+            w.stats[2] = 0.0;  // no step of r outstanding
             w.stats[3] = g2;
             *w.mode = MODE_CG;
             a = 2;
@@ -277,27 +284,26 @@ __global__ __launch_bounds__(256) void refine_update_kernel(RefineWork w, int64_
     }
 }
 
-// ||r||^2 at the final c (after the loop): sum of the residual kernel's partials.
-__global__ void refine_final_kernel(RefineWork w, int64_t nparts)
+// z = R^-T s and dc = R^-1 z (R from the FP32 factorisation, FP64 arithmetic) in one launch, the
+// second solve's block rows behind the first's in ticket order; then the end of the iteration
+// on the last workgroup.
+__global__ __launch_bounds__(256, 1) void refine_step_kernel(RefineWork w, TrsvArgs a)
 {
-    if (threadIdx.x != 0)
+    __shared__ TrsvLds L;
+    if (*w.done)
         return;
-    double rn = 0.0;
-    for (int64_t b = 0; b < nparts; ++b)
-        rn += w.rnorm_part[b];
-    w.stats[0] = rn;
-}
-
-// After the loop: remember whether it converged (status ENOCONV otherwise) and
-// re-arm the residual kernels for the final residual r = b - A c.
-__global__ void refine_reset_done_kernel(RefineWork w)
-{
-    if (threadIdx.x == 0) {
-        if (!*w.done)
-            set_status(w.status, DST_ENOCONV);
-        *w.done = 0;
-        *w.mode = MODE_CSNE;
+    if (threadIdx.x == 0)
+        L.dead = 0;
+    unsigned long long *xbuf2 = a.xbuf + a.n;
+    for (int64_t q = take_item(a, L); q < 2 * a.nb; q = take_item(a, L)) {
+        const bool ok = q < a.nb
+                            ? trsv_item<float, true>(w.R32, a, L, q, w.s, nullptr, a.xbuf, w.z)
+                            : trsv_item<float, false>(w.R32, a, L, q - a.nb, nullptr, a.xbuf, xbuf2, w.dc);
+        if (!ok)
+            break;
     }
+    if (trsv_finish(a, L, 2 * a.n))
+        refine_update(w);
 }
 
 __global__ void refine_reset_kernel(RefineWork w)
@@ -312,35 +318,20 @@ __global__ void refine_reset_kernel(RefineWork w)
     }
 }
 
-static void residual(const RefineWork &w, hipStream_t s)
-{
-    const unsigned gr = (unsigned)((w.m + RB - 1) / RB);
-    hipLaunchKernelGGL(resid_part_kernel, dim3(gr, RCH), dim3(256), 0, s, w);
-    hipLaunchKernelGGL(resid_sum_kernel, dim3((unsigned)((w.m + 255) / 256)), dim3(256), 0, s, w);
-}
-
 hipError_t launch_refine(const RefineWork &w, int max_iters, hipStream_t s)
 {
     hipLaunchKernelGGL(refine_reset_kernel, dim3(1), dim3(64), 0, s, w);
-    const int64_t nparts = (w.m + 255) / 256;
+    const int64_t nparts = (w.m + RB - 1) / RB;
+    const TrsvArgs a = trsv_args(w.lda, w.n, nullptr, nullptr, w.sync);
+    const unsigned g = (unsigned)(2 * a.nb < TS_GRID ? 2 * a.nb : TS_GRID);
     for (int it = 0; it < max_iters; ++it) {
-        residual(w, s);
-        hipLaunchKernelGGL(cg_step_kernel, dim3((unsigned)nparts), dim3(256), 0, s, w, nparts);
-        hipLaunchKernelGGL(atr_kernel, dim3((unsigned)w.n), dim3(256), 0, s, w);
-        // z = R^-T s, dc = R^-1 z (R from the FP32 factorisation, FP64 arithmetic)
-        hipError_t e = launch_trsv_upper_t_f32(w.R32, w.lda, w.n, w.s, w.z, w.sync, w.done, s);
-        if (e != hipSuccess)
-            return e;
-        e = launch_trsv_upper_f32(w.R32, w.lda, w.n, w.z, w.dc, w.sync, w.done, s);
-        if (e != hipSuccess)
-            return e;
-        hipLaunchKernelGGL(refine_update_kernel, dim3(1), dim3(256), 0, s, w, nparts);
+        hipLaunchKernelGGL(resid_kernel<false>, dim3((unsigned)nparts), dim3(RCH * 64), 0, s, w);
+        hipLaunchKernelGGL(atr_kernel<false>, dim3((unsigned)w.n), dim3(256), 0, s, w, nparts);
+        hipLaunchKernelGGL(refine_step_kernel, dim3(g), dim3(256), 0, s, w, a);
     }
     // final residual r = b - A c at the returned c, ||r||^2, and s = A^T r
-    hipLaunchKernelGGL(refine_reset_done_kernel, dim3(1), dim3(64), 0, s, w);
-    residual(w, s);
-    hipLaunchKernelGGL(refine_final_kernel, dim3(1), dim3(64), 0, s, w, nparts);
-    hipLaunchKernelGGL(atr_kernel, dim3((unsigned)w.n), dim3(256), 0, s, w);
+    hipLaunchKernelGGL(resid_kernel<true>, dim3((unsigned)nparts), dim3(RCH * 64), 0, s, w);
+    hipLaunchKernelGGL(atr_kernel<true>, dim3((unsigned)w.n), dim3(256), 0, s, w, nparts);
     return hipGetLastError();
 }
 

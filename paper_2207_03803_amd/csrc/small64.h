@@ -23,15 +23,6 @@ DEV int blk_at(int b, int c) { return c * (c + 1) / 2 + b; }
 
 DEV d4 mfma16(double a, double b, d4 c) { return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0); }
 
-// Value of v in lane `lane` (uniform) of the wave.
-DEV double readlane_d(double v, int lane)
-{
-    const long long b = __double_as_longlong(v);
-    const int lo = __builtin_amdgcn_readlane((int)(b & 0xffffffffll), lane);
-    const int hi = __builtin_amdgcn_readlane((int)(b >> 32), lane);
-    return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
-}
-
 // Lane N of each row of 16 lanes, to the whole row: one instruction, and no scalar register
 // for the next one to wait on.
 template <int N>
