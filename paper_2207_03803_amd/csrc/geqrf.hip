@@ -19,6 +19,8 @@
 // Reflector convention inside the tiles: H = I - tau v v^T, v(0) = 1,
 // beta = -sign(alpha) ||(alpha, x)||, tau = (beta - alpha)/beta,
 // v(1:) = x / (alpha - beta); tau = 0 when x is exactly zero.
+#include <algorithm>
+
 #include "kernels.h"
 #include "small64.h"
 
@@ -392,21 +394,26 @@ DEV bool update_tile(int64_t n_rb, int64_t n_cb, int64_t &rb, int64_t &cb)
 constexpr int OB = 2 * NB;                 // a TSQR panel pair (one factor_block)
 constexpr int OB2 = 2 * OB;                // outer block of the trailing update: two panel pairs
 
-// Tiles of the two products.  The large ones run at 4 waves per SIMD; the small ones spread
-// the narrow products of the panel chain (64 or 128 columns) and short matrices over more
-// workgroups (see wpart_small, update_small).
+// Tiles of the two products, four waves each.  The small ones spread the narrow products of the
+// panel chain (64 or 128 columns) and short matrices over more workgroups.  Bound by the matrix
+// cores and, at the tiles' ends, by what the CU's other workgroups leave to do: in FP64, waves of
+// 64 x 32 with two or three workgroups per CU against 128 x 128 tiles of eight waves, 70,000 x
+// 10,000: Y^T C 127 -> 124 ms, C - Y W 111 -> 107 ms (60 and 62 TFLOP/s); 128 x 128 tiles of four
+// waves 124 and 113, 256 x 64 124 and 109 with spills.
 template <class T>
 struct QrTiles;
 template <>
 struct QrTiles<double> {
-    using WL = KTile<double, OB, 128, 4, 2, 4>;  // P = Y^T C over a row chunk
+    using WL = KTile<double, OB, 64, 8, 2, 2>;  // P = Y^T C over a row chunk
+    static constexpr int WL_WAVES = 2;          // per SIMD
     using WS = KTile<double, 64, 64, 8, 2, 2>;
-    using UL = MTile<double, 128, 128, 8, 2, 4>;  // C^T -= W^T Y^T (rows of C along the MFMA N axis)
+    using UL = MTile<double, 64, 128, 8, 2, 2>;  // C^T -= W^T Y^T (rows of C along the MFMA N axis)
     using US = MTile<double, 64, 64, 8, 2, 2>;
 };
 template <>
 struct QrTiles<float> {
     using WL = KTile<float, OB, 128, 4, 2, 2>;
+    static constexpr int WL_WAVES = 3;
     using WS = KTile<float, 64, 64, 4, 2, 2>;
     using UL = MTile<float, 128, 128, 8, 2, 2>;
     using US = MTile<float, 64, 64, 8, 1, 1>;
@@ -427,8 +434,8 @@ DEV T unit_lower(T v, int64_t r, int64_t diag)
 // (ymode = 1, used for Y_A^T Y_B with rows below Y_A's triangle).  Rows r0 .. m.  Both operands
 // are contiguous along the summed rows and go straight to LDS, except in the stages that
 // meet a unit triangle and a ragged last one.
-template <class S>
-__global__ __launch_bounds__(S::NT, sizeof(typename S::elem) == 8 && S::NT == 512 ? 4 : 3) void qr_wpart_kernel(
+template <class S, int WAVES>
+__global__ __launch_bounds__(S::NT, WAVES) void qr_wpart_kernel(
     QrWork w, int64_t j0, int pw, int64_t c0, int64_t nt, int ymode, int64_t r0, int64_t chunk)
 {
     using T = typename S::elem;
@@ -762,7 +769,7 @@ __global__ __launch_bounds__(256) void qr_hmat_kernel(const double *__restrict__
 // operand slices), so the epilogue is a plain store.  Y and W go straight to LDS, except
 // where a row block meets Y's unit triangle and in a ragged last slice.
 template <class S>
-__global__ __launch_bounds__(S::NT, sizeof(typename S::elem) == 8 && S::NT == 512 ? 4 : 3) void qr_update_kernel(
+__global__ __launch_bounds__(S::NT, 3) void qr_update_kernel(
     QrWork w, int64_t j0, int pw, int64_t c0, int64_t nt)
 {
     using T = typename S::elem;
@@ -846,10 +853,15 @@ __global__ __launch_bounds__(S::NT, sizeof(typename S::elem) == 8 && S::NT == 51
             }
 }
 
-// Split of rows [r0, m) into chunks for the split-K products (whole tiles of 64 rows).
+// Split of rows [r0, m) into chunks for the split-K products (whole tiles of 64 rows): ncb tiles
+// per chunk, about `target` workgroups.  0: chunks of 1,024 rows, but at least 512 workgroups (two
+// per CU) and at most 2,048.  More chunks write and read more partial sums (2,048 workgroups: 9.45
+// ms for the QR of 18,250 x 2,250 in FP32, 512: 9.26), fewer leave the last round of
+// workgroups half empty (110,000 x 10,000 in FP64, 512 workgroups: 45 ms more than 2,048).
 static void chunking(int64_t rows, int64_t ncb, int64_t &chunk, int64_t &nch, int64_t cap, int64_t target = 2048)
 {
-    nch = (target + ncb - 1) / ncb;
+    auto count = [&](int64_t wgs) { return (wgs + ncb - 1) / ncb; };
+    nch = target > 0 ? count(target) : std::max(count(512), std::min(count(2048), rows / 1024));
     if (nch > cap)
         nch = cap;
     chunk = (rows + nch - 1) / nch;
@@ -913,12 +925,12 @@ static int64_t launch_wpart(const QrWork &w, int64_t j0, int pw, int64_t c0, int
     if (narrow) {
         const int64_t nq = tiles(nt, M::BN), np = tiles(pw, M::BM);
         chunking(rows, nq * np, chunk, nch, w.max_chunks, target);
-        hipLaunchKernelGGL(qr_wpart_kernel<M>, dim3((unsigned)nq, (unsigned)nch, (unsigned)np), dim3(M::NT), 0, s, w,
+        hipLaunchKernelGGL((qr_wpart_kernel<M, 3>), dim3((unsigned)nq, (unsigned)nch, (unsigned)np), dim3(M::NT), 0, s, w,
                            j0, pw, c0, nt, ymode, r0, chunk);
     } else {
         const int64_t nq = tiles(nt, L::BN), np = tiles(pw, L::BM);
         chunking(rows, nq * np, chunk, nch, w.max_chunks, target);
-        hipLaunchKernelGGL(qr_wpart_kernel<L>, dim3((unsigned)nq, (unsigned)nch, (unsigned)np), dim3(L::NT), 0, s, w,
+        hipLaunchKernelGGL((qr_wpart_kernel<L, QrTiles<T>::WL_WAVES>), dim3((unsigned)nq, (unsigned)nch, (unsigned)np), dim3(L::NT), 0, s, w,
                            j0, pw, c0, nt, ymode, r0, chunk);
     }
     return nch;
@@ -939,11 +951,6 @@ struct BlockT {
     int pw() const { return pwa + pwb; }
 };
 
-// Workgroups of a trailing update's split-K product, about: two per CU.  More chunks write and
-// read more partials (2,048: 9.45 ms for the QR of 18,250 x 2,250 in FP32, 512: 9.26; 61,500 x
-// 1,500 in FP64 11.8 and 11.65, 256: 12.2).
-constexpr int64_t SPLIT_WGS = 512;
-
 // C := (I - Y T Y^T)^T C for the columns c0 .. c0+nt, Y the block at (J, J).
 template <class T>
 static void apply_block(const QrWork &wf, int64_t J, const BlockT &bt, int64_t c0, int64_t nt, hipStream_t s)
@@ -954,7 +961,7 @@ static void apply_block(const QrWork &wf, int64_t J, const BlockT &bt, int64_t c
     const QrWork w = rows_to(wf, J + pw);
     const int64_t rows = w.m - J;
     WArgs a{};
-    a.nch = launch_wpart<T>(w, J, pw, c0, nt, 0, J, w.split_wgs > 0 ? w.split_wgs : SPLIT_WGS, s);
+    a.nch = launch_wpart<T>(w, J, pw, c0, nt, 0, J, w.split_wgs, s);
     if (a.nch > W_CHUNKS) {
         hipLaunchKernelGGL(qr_psum_kernel, dim3((unsigned)(((int64_t)pw * nt + 255) / 256)), dim3(256), 0, s, w, pw,
                            a.nch, nt);
