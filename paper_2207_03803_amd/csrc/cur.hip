@@ -24,6 +24,8 @@ namespace gap {
 // projection tiles of 128 rows x 64 columns.
 using CG = MTile<double, 64, 64, 16, 2, 2>;
 using CP = KTile<double, 128, 64, 4, 2, 2>;
+template <int BN>
+using CPW = KTile<double, 128, BN, 4, 4, 1>;  // a last tile of 80 or 96 columns
 constexpr int CUR_GB = 64;                 // block of G
 constexpr int CUR_NB = 128;                // columns of Y whose squares one workgroup sums
 constexpr int64_t CUR_MAX_CHUNKS = 64;     // row chunks the partials' space is sized for (128-wide blocks)
@@ -51,6 +53,13 @@ int64_t cur_chunks(int64_t n, int d)
     return nch < 1 ? 1 : nch;
 }
 int64_t cur_sel_blocks(int64_t n) { return (n + CUR_SEL_PER - 1) / CUR_SEL_PER; }
+
+// Column tiles of the projection: of 64, the last one with up to 32 columns more.
+__host__ __device__ inline int64_t cur_proj_tiles(int d)
+{
+    const int full = d / CP::BN, rest = d % CP::BN;
+    return full + (rest > 0 && (full == 0 || rest > 32) ? 1 : 0);
+}
 
 // Byte offsets of the workspace parts (each 256-aligned).
 struct CurLayout {
@@ -211,31 +220,21 @@ __global__ __launch_bounds__(256) void cur_trinv_kernel(const double *__restrict
     }
 }
 
-// Y = X W for 128 rows and the 64 columns of tile 2 ct + odd; rowpart[ct][r] = the sum of
-// Y[r][q]^2 over the tile's columns (a fixed order), added to the even tile's by the odd one's
-// launch.  A row tile's column tiles start together on one XCD and walk its rows of X in step,
-// so that they are read from HBM once per launch; both halves in one workgroup, one after
-// the other, read them at their own pace (1e6 x 400: 5.4 ms against 4.7; 6.0 on K-major
-// 128 x 128 tiles).
-__global__ __launch_bounds__(CP::NT, 3) void cur_proj_kernel(const double *__restrict__ X, int64_t n, int d,
-                                                             const double *__restrict__ W, int64_t nct, int odd,
-                                                             double *__restrict__ rowpart)
+// Y = X W for 128 rows and the columns of tile 2 ct + odd (64, up to 96 in the last one);
+// rowpart[ct][r] = the sum of Y[r][q]^2 over the tile's columns (a fixed order), added to the
+// even tile's by the odd one's launch.
+template <class S>
+DEV void cur_proj_tile(const double *__restrict__ X, int64_t n, int d, const double *__restrict__ W, int64_t r0,
+                       int64_t q0, double *out, int odd, d2 *lds, double (*rsum)[CP::BM])
 {
-    using S = CP;
-    __shared__ __align__(16) d2 lds[2 * S::UNITS];
-    __shared__ double rsum[S::WN][S::BM];
-    const int64_t total = (n + S::BM - 1) / S::BM * nct;
-    const int64_t lw = xcd_remap(blockIdx.x, (total + 7) & ~int64_t(7));
-    if (lw >= total)
-        return;
-    const int64_t r0 = lw / nct * S::BM, ct = lw % nct, q0 = (2 * ct + odd) * S::BN;
+    static_assert(S::BM == CP::BM && S::NT == CP::NT && S::UNITS <= CPW<96>::UNITS && S::WN <= CP::WN, "LDS");
     const int t = threadIdx.x, lane = t & 63, wave = t >> 6, g = lane >> 4, rl = lane & 15;
     const int wm = wave / S::WN, wn = wave % S::WN;
     const int K = (int)((q0 + S::BN) < d ? (q0 + S::BN) : d);  // W[k][q] = 0 for k > q
     const double *src[S::LPT];
 #pragma unroll
     for (int i = 0; i < S::LPT; ++i) {
-        const int r = S::unit_row(i);
+        const int r = S::has(i) ? S::unit_row(i) : 0;
         // rows past n and columns past d repeat the last one; the columns count as zero below
         const int64_t row = r < S::BM ? (r0 + r < n ? r0 + r : n - 1) : (q0 + r - S::BM < d ? q0 + r - S::BM : d - 1);
         src[i] = (r < S::BM ? X : W) + row * (int64_t)d + S::unit_k(i);
@@ -262,10 +261,38 @@ __global__ __launch_bounds__(CP::NT, 3) void cur_proj_kernel(const double *__res
         }
     __syncthreads();
     if (t < S::BM && r0 + t < n) {
-        double *out = rowpart + ct * n + r0 + t;
-        const double rs = rsum[0][t] + rsum[1][t];
-        *out = odd ? *out + rs : rs;
+        double rs = rsum[0][t];
+        if constexpr (S::WN == 2)
+            rs += rsum[1][t];
+        out[r0 + t] = odd ? out[r0 + t] + rs : rs;
     }
+}
+
+// A row tile's column tiles start together on one XCD and walk its rows of X in step,
+// so that they are read from HBM once per launch; both halves in one workgroup, one after
+// the other, read them at their own pace (1e6 x 400: 5.4 ms against 4.7; 6.0 on K-major
+// 128 x 128 tiles).  Up to 32 columns past the last full tile go with it (cur_proj_tiles): they
+// take all of K, and a tile of their own costs as much as a full one (d = 400: 4.7 ms; on a 16
+// wide tile, bound by its stages' latency, 4.3; 3.3 with the last 80 columns together).
+__global__ __launch_bounds__(CP::NT, 3) void cur_proj_kernel(const double *__restrict__ X, int64_t n, int d,
+                                                             const double *__restrict__ W, int64_t nct, int odd,
+                                                             double *__restrict__ rowpart)
+{
+    __shared__ __align__(16) d2 lds[2 * CPW<96>::UNITS];
+    __shared__ double rsum[CP::WN][CP::BM];
+    const int64_t total = (n + CP::BM - 1) / CP::BM * nct;
+    const int64_t lw = xcd_remap(blockIdx.x, (total + 7) & ~int64_t(7));
+    if (lw >= total)
+        return;
+    const int64_t r0 = lw / nct * CP::BM, ct = lw % nct, tile = 2 * ct + odd, q0 = tile * CP::BN;
+    const int64_t width = tile == cur_proj_tiles(d) - 1 ? d - q0 : CP::BN;
+    double *out = rowpart + ct * n;
+    if (width <= CP::BN)
+        cur_proj_tile<CP>(X, n, d, W, r0, q0, out, odd, lds, rsum);
+    else if (width <= 80)
+        cur_proj_tile<CPW<80>>(X, n, d, W, r0, q0, out, odd, lds, rsum);
+    else
+        cur_proj_tile<CPW<96>>(X, n, d, W, r0, q0, out, odd, lds, rsum);
 }
 
 // lev = sum of the column tiles' parts in order; key = draw / lev (1 / lev
@@ -481,7 +508,7 @@ hipError_t launch_cur_select(const CurLaunch &c, hipStream_t s)
     unsigned *hist = reinterpret_cast<unsigned *>(ws + L.hist);
     long long *cnt = reinterpret_cast<long long *>(ws + L.cnt);
     long long *base = reinterpret_cast<long long *>(ws + L.base);
-    const int64_t nb = cur_nb(d), gb = (d + CUR_GB - 1) / CUR_GB, pairs = gb * (gb + 1) / 2;
+    const int64_t gb = (d + CUR_GB - 1) / CUR_GB, pairs = gb * (gb + 1) / 2;
     const int64_t nch = cur_gram_chunks(n, d);
     int64_t chunk = (n + nch - 1) / nch;
     chunk = (chunk + 15) / 16 * 16;
@@ -495,12 +522,13 @@ hipError_t launch_cur_select(const CurLaunch &c, hipStream_t s)
         return e;
     hipLaunchKernelGGL(cur_trinv_kernel, dim3((unsigned)d), dim3(256), 0, s, G, d, W);
     for (int odd = 0; odd < 2; ++odd) {
-        const int64_t nct = (gb + 1 - odd) / 2, ptiles = (n + CP::BM - 1) / CP::BM * nct;
+        const int64_t nct = (cur_proj_tiles(d) + 1 - odd) / 2, ptiles = (n + CP::BM - 1) / CP::BM * nct;
         if (ptiles > 0)
             hipLaunchKernelGGL(cur_proj_kernel, dim3((unsigned)((ptiles + 7) & ~int64_t(7))), dim3(CP::NT), 0, s, c.x, n,
                                d, W, nct, odd, rowpart);
     }
-    hipLaunchKernelGGL(cur_keys_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, rowpart, n, nb, c.draws,
+    hipLaunchKernelGGL(cur_keys_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, rowpart, n,
+                       (cur_proj_tiles(d) + 1) / 2, c.draws,
                        c.lev_out, keys);
     int64_t hg = (n + 255) / 256;
     if (hg > 2048)
