@@ -978,7 +978,7 @@ static void apply_block(const QrWork &wf, int64_t J, const BlockT &bt, int64_t c
         hipLaunchKernelGGL(qr_w_kernel<double>, dim3((unsigned)((nt + 15) / 16)), dim3(256), 0, s, w, a, w.W);
     else
         hipLaunchKernelGGL(qr_w_kernel<float>, dim3((unsigned)((nt + 15) / 16)), dim3(256), 0, s, w, a, w.W32);
-    // the large tiles where they fill the chip at least twice
+    // the large tiles from two per CU on (from 256, 1,024 or 2,048 tiles on: within 1 %)
     using L = typename QrTiles<T>::UL;
     using M = typename QrTiles<T>::US;
     auto tiles = [](int64_t x, int64_t b) { return (x + b - 1) / b; };

@@ -41,7 +41,7 @@ def source_hash():
 
 
 def _short(name):
-    return name.split("(")[0].replace("void ", "").strip()
+    return name.replace("(gap::KnmRows)", "").split("(")[0].replace("void ", "").strip()
 
 
 def trace_table(db, top=40):
