@@ -866,8 +866,9 @@ static void chunking(int64_t rows, int64_t ncb, int64_t &chunk, int64_t &nch, in
         nch = cap;
     chunk = (rows + nch - 1) / nch;
     chunk = (chunk + 63) & ~int64_t(63);
-    if (chunk < 128)
-        chunk = 128;
+    const int64_t least = rows <= 4096 ? 64 : 128;  // 64: 2,500 x 500 in FP32 2 % of the fit, 7,100 x 1,111 0.5 % slower
+    if (chunk < least)
+        chunk = least;
     nch = (rows + chunk - 1) / chunk;
 }
 

@@ -116,8 +116,9 @@ __global__ __launch_bounds__(256) void chol_step_kernel(double *U, int64_t ld, i
     if (blockIdx.x == 0) {
         if (t == 0 && !L.ok)
             set_status(status, DST_ENOTPD);
-        for (int e = t; e < CNB * CNB; e += 256) {
-            const int i = e & 63, l = e >> 6;
+#pragma unroll
+        for (int q = 0; q < CNB * CNB / 256; ++q) {
+            const int e = q * 256 + t, i = e & 63, l = e >> 6;
             if (right)
                 diag[e] = L.D[i][l];
             else if (i < kb && l < kb)
@@ -145,16 +146,41 @@ __global__ __launch_bounds__(256) void chol_step_kernel(double *U, int64_t ld, i
 // Trailing update of the upper triangle: A[r][c] -= sum_{p < kb} U[k0+p][r] U[k0+p][c]
 // for k1 <= r <= c < n, one tile per workgroup (enumerated column by column), both operands
 // contiguous along p.  The tile is computed transposed, acc(c, r), so that
-// consecutive lanes update consecutive rows of the column-major matrix.  The first workgroup
-// also stores the nd diagonal blocks that the steps left in diag.
+// consecutive lanes update consecutive rows of the column-major matrix; in the small tiles the
+// accumulators start from -A, so that its loads run beside the first stages (the large ones would
+// spill: n = 10,000 13.4 -> 17.0 ms).  The last workgroup stores the two diagonal blocks that the
+// steps left in diag.  Bound by latency at a few tiles: 12 us (15 with A read at the end and
+// the blocks stored by the first tile's workgroup).
+
+// The 64 x 64 block dg ([column][row]) into U at k0, by NT threads: all loads in flight.
+template <int NT>
+DEV void chol_store_block(double *U, int64_t ld, int64_t k0, const double *dg)
+{
+    constexpr int N = CNB * CNB / NT;
+    double v[N];
+#pragma unroll
+    for (int q = 0; q < N; ++q)
+        v[q] = dg[q * NT + threadIdx.x];
+#pragma unroll
+    for (int q = 0; q < N; ++q) {
+        const int e = q * NT + threadIdx.x;
+        U[(k0 + (e >> 6)) * ld + k0 + (e & 63)] = v[q];
+    }
+}
+
 template <class S>
 __global__ __launch_bounds__(S::NT, S::NT == 512 ? 4 : 2) void chol_syrk_kernel(double *U, int64_t ld, int64_t k0,
                                                                                 int kb, int64_t k1, int64_t n,
-                                                                                const double *__restrict__ diag, int nd)
+                                                                                const double *__restrict__ diag)
 {
     __shared__ __align__(16) d2 lds[2 * S::UNITS];
     static_assert(S::BM == S::BN, "square tiles");
     const int64_t L = blockIdx.x;
+    if (L == (int64_t)gridDim.x - 1) {
+        chol_store_block<S::NT>(U, ld, k0, diag);
+        chol_store_block<S::NT>(U, ld, k0 + CNB, diag + CNB * CNB);
+        return;
+    }
     int64_t tj = (int64_t)((sqrt(8.0 * (double)L + 1.0) - 1.0) * 0.5);
     while ((tj + 1) * (tj + 2) / 2 <= L)
         ++tj;
@@ -162,11 +188,6 @@ __global__ __launch_bounds__(S::NT, S::NT == 512 ? 4 : 2) void chol_syrk_kernel(
         --tj;
     const int64_t ti = L - tj * (tj + 1) / 2;
     const int64_t r0 = k1 + ti * S::BM, c0 = k1 + tj * S::BN;
-    if (L == 0)
-        for (int e = threadIdx.x; e < nd * CNB * CNB; e += S::NT) {
-            const int b = e / (CNB * CNB), i = e & 63, l = (e >> 6) & 63;
-            U[(k0 + b * CNB + l) * ld + k0 + b * CNB + i] = diag[e];
-        }
     const double *src[S::LPT];
 #pragma unroll
     for (int i = 0; i < S::LPT; ++i) {
@@ -175,11 +196,24 @@ __global__ __launch_bounds__(S::NT, S::NT == 512 ? 4 : 2) void chol_syrk_kernel(
         col = col < n ? col : n - 1;  // computed, not stored
         src[i] = U + col * ld + k0 + S::unit_k(i);
     }
-    d4 acc[S::FM][S::FN];
-    ktile_zero<S>(acc);
-    ktile_product<S>(acc, lds, src, kb, rows_aligned16(U + k0, ld));
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int wm = wave / S::WN, wn = wave % S::WN;
+    constexpr bool FROM_A = S::NT == 256;
+    d4 acc[S::FM][S::FN];
+    ktile_zero<S>(acc);
+    if constexpr (FROM_A)
+#pragma unroll
+        for (int i = 0; i < S::FM; ++i)
+#pragma unroll
+            for (int j = 0; j < S::FN; ++j)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const int64_t c = c0 + acc_row<S>(wm, i, lane, e);
+                    const int64_t r = r0 + acc_col<S>(wn, j, lane, e);
+                    if (r <= c && c < n)
+                        acc[i][j][e] = -U[c * ld + r];
+                }
+    ktile_product<S>(acc, lds, src, kb, rows_aligned16(U + k0, ld));
 #pragma unroll
     for (int i = 0; i < S::FM; ++i)
 #pragma unroll
@@ -189,15 +223,14 @@ __global__ __launch_bounds__(S::NT, S::NT == 512 ? 4 : 2) void chol_syrk_kernel(
                 const int64_t c = c0 + acc_row<S>(wm, i, lane, e);
                 const int64_t r = r0 + acc_col<S>(wn, j, lane, e);
                 if (r <= c && c < n)
-                    U[c * ld + r] -= acc[i][j][e];
+                    U[c * ld + r] = FROM_A ? -acc[i][j][e] : U[c * ld + r] - acc[i][j][e];
             }
 }
 
 // The diagonal block that a step with no trailing update after it left in diag.
 __global__ __launch_bounds__(256) void chol_store_kernel(double *U, int64_t ld, int64_t k0, const double *diag)
 {
-    for (int e = threadIdx.x; e < CNB * CNB; e += 256)
-        U[(k0 + (e >> 6)) * ld + k0 + (e & 63)] = diag[e];
+    chol_store_block<256>(U, ld, k0, diag);
 }
 
 // diag: 2 x 64 x 64 doubles of scratch.
@@ -229,11 +262,11 @@ hipError_t launch_potrf_upper(double *U, int64_t ld, int64_t n, double *diag, in
         // 64 x 64 tiles where large ones would leave CUs without one
         const int64_t nl = blocks(rest, SL::BM), ns = blocks(rest, SS::BM);
         if (nl * (nl + 1) / 2 >= 256)
-            hipLaunchKernelGGL(chol_syrk_kernel<SL>, dim3((unsigned)(nl * (nl + 1) / 2)), dim3(SL::NT), 0, s, U, ld, k0,
-                               2 * CNB, k1 + CNB, n, (const double *)diag, 2);
+            hipLaunchKernelGGL(chol_syrk_kernel<SL>, dim3((unsigned)(nl * (nl + 1) / 2 + 1)), dim3(SL::NT), 0, s, U, ld, k0,
+                               2 * CNB, k1 + CNB, n, (const double *)diag);
         else
-            hipLaunchKernelGGL(chol_syrk_kernel<SS>, dim3((unsigned)(ns * (ns + 1) / 2)), dim3(SS::NT), 0, s, U, ld, k0,
-                               2 * CNB, k1 + CNB, n, (const double *)diag, 2);
+            hipLaunchKernelGGL(chol_syrk_kernel<SS>, dim3((unsigned)(ns * (ns + 1) / 2 + 1)), dim3(SS::NT), 0, s, U, ld, k0,
+                               2 * CNB, k1 + CNB, n, (const double *)diag);
     }
     return hipGetLastError();
 }
