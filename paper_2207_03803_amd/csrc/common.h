@@ -27,15 +27,20 @@ DEV void set_status(int32_t *status, int32_t code)
 }
 
 // ---------------------------------------------------------------------------
-// "Last workgroup" completion pattern: every workgroup publishes its partial
-// results, then one arrival counter tells the last one that all partials are
-// visible.  The counter is reset by that last workgroup, ready for the next
-// launch that uses it.  Returns true in every thread of the last workgroup.  Thread 0's
-// arrival releases the whole workgroup's writes (ordered before it by the barrier) and
-// acquires the others' for it (the second barrier).
+// "Last workgroup" completion pattern: every workgroup stores its partial results, then one
+// arrival counter tells the last one that all partials are visible.  The counter is reset by
+// that last workgroup, ready for the next launch that uses it.  Returns true in every thread of
+// the last workgroup.  Callers need no fence of their own, on either side:
+//   * each wave first waits until its own stores have reached the L2 (a barrier alone does not
+//     wait for them, and thread 0's wait counts the stores of its own wave only);
+//   * thread 0's release then writes the XCD's L2 back before the counter is raised, for the
+//     workgroups of other XCDs;
+//   * each wave of the last workgroup drops what its caches may hold of the partials.
 // ---------------------------------------------------------------------------
 DEV bool arrive_last(unsigned *counter, unsigned nblocks, int *flag_lds)
 {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+    __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0)
     __syncthreads();
     if (threadIdx.x == 0) {
         unsigned prev = __hip_atomic_fetch_add(counter, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
@@ -45,11 +50,11 @@ DEV bool arrive_last(unsigned *counter, unsigned nblocks, int *flag_lds)
         *flag_lds = last;
     }
     __syncthreads();
-    return *flag_lds != 0;
+    const bool last = *flag_lds != 0;
+    if (last)
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+    return last;
 }
-
-// Publish this workgroup's global writes before it arrives (all threads call).
-DEV void release_writes() { __atomic_thread_fence(__ATOMIC_RELEASE); }
 
 // Value of v in lane `lane` (uniform) of the wave.
 DEV double readlane_d(double v, int lane)

@@ -79,7 +79,6 @@ __global__ __launch_bounds__(256) void sumsq_kernel(const double *x, int64_t n, 
     __syncthreads();
     if (threadIdx.x == 0)
         part[blockIdx.x] = (red[0] + red[1]) + (red[2] + red[3]);
-    release_writes();
     if (!arrive_last(counter, gridDim.x, &flag))
         return;
     if (threadIdx.x == 0) {
