@@ -17,8 +17,9 @@
  *  - Pointers named x_*, config_offsets, sigma, y, c, c_out, y_out and the
  *    workspace are DEVICE pointers (HBM of the GPU current when the handle was
  *    created), owned by the caller; the library never allocates device memory
- *    and never frees what it is given.  gap_params, gap_solve_info and
- *    gap_layout_info are host structs.
+ *    and never frees what it is given.  (Two arrays of its own are part of the loaded
+ *    library on each GPU: gap_fit_static's scratch and gap_predict's pool.)
+ *    gap_params, gap_solve_info and gap_layout_info are host structs.
  *  - Work is enqueued asynchronously on the handle's HIP stream (a hipStream_t
  *    passed as void*; NULL = the default stream).  Inputs must stay valid and
  *    unmodified until that work completes; sigma given to gap_build_knm is
@@ -288,7 +289,12 @@ gap_status gap_solve(gap_handle h, const double *y, double *c_out, gap_solve_inf
  * sparse set bound by the last gap_build_knm (or gap_set_model):
  *   y_out[A] = sum_{i in A} sum_j c_j sigma_w^2 (x_i . x_j)^zeta.
  * x_atoms/offsets as in gap_build_knm; c [M] and y_out [n_configs] device FP64.
- * Uses no workspace.  The offsets are checked on the device before any
+ * Uses no workspace: the partial sums lie in a pool of device memory that the
+ * library holds on each GPU, of which a call takes a part while it runs.  Calls
+ * of any handles, streams and threads may run at the same time, each with its own
+ * y_out; one that finds no part free computes without it, with the same result.  A captured
+ * call counts as one call: its replays follow one another.
+ * The offsets are checked on the device before any
  * descriptor is read: a configuration whose range is not inside [0, n_atoms),
  * or offsets[0] != 0, or offsets[n_configs] != n_atoms, gives NaN energies for
  * the configurations of its workgroup and GAP_EINVAL in the device status

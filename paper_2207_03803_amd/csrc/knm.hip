@@ -6,6 +6,7 @@
 #include "knm.h"
 #include "small64.h"
 
+#include <atomic>
 #include <type_traits>
 
 namespace gap {
@@ -732,11 +733,12 @@ __global__ __launch_bounds__(KNM_NT, 2) void knm_group_kernel(KnmGroup g)
 // CUs a third idle in the last round.
 //
 // The pieces live in a static pool of PRED_SLOTS slots per GPU (a predict call has
-// no workspace).  The call's first kernel claims a free slot and writes its
-// number into the call's own output (the first entry of each group of
-// configurations, which is written last); the last workgroup of the second
-// kernel frees it.  Claiming on the device works for any streams, threads and
-// captured graphs, and never waits: with no slot free (more than PRED_SLOTS
+// no workspace).  Every call has a number of its own; its first kernel claims a free slot by
+// writing that number into the slot's owner word, the other kernels look for it there, and the
+// last workgroup of the second one frees the slot.  Nothing of a call's state lies in memory
+// that another call may write, the caller's output included.  Claiming on the device works for any
+// streams, threads and captured graphs (whose replays, one after the other, keep their number),
+// and never waits: with no slot free (more than PRED_SLOTS
 // calls in flight), with malformed offsets, or when one request's pieces exceed a
 // slot, the second kernel computes its groups' tiles itself, with the same sums in
 // the same order.
@@ -748,8 +750,9 @@ __global__ __launch_bounds__(KNM_NT, 2) void knm_group_kernel(KnmGroup g)
 constexpr int PRED_SLOTS = 32;
 constexpr int64_t PRED_CAP = 131072;  // doubles of a slot (1 MiB)
 static __device__ double g_pred_pool[PRED_SLOTS * PRED_CAP];
-static __device__ unsigned g_pred_busy[PRED_SLOTS];
+static __device__ unsigned long long g_pred_owner[PRED_SLOTS];  // the call's number; 0: free
 static __device__ unsigned g_pred_done[PRED_SLOTS];
+static_assert(PRED_SLOTS <= 64, "one lane per owner word");
 
 // Both tile heights give waves of 64 columns and the same order of every sum.
 using PSL = KTile<double, KNM_BM, KNM_BN, 4, 4, 1>;  // 256 atoms
@@ -771,6 +774,7 @@ struct PredArgs {
     int64_t tiles, n_ct;    // atom tiles, column tiles
     int split;              // runs of column tiles
     int small;              // 64-atom tiles
+    unsigned long long id;  // the call's number (positive)
 };
 
 // Energies of the tile's atoms over column tiles [ct0, ct1), into eps[0 .. S::BM).
@@ -865,18 +869,30 @@ DEV int64_t configs_before(const int64_t *offsets, int64_t N, int64_t r)
     return lo;
 }
 
-// The call's slot, and the claim kernel that finds one.
-DEV int64_t pred_slot(const double *y, int64_t at)
+// The call's slot (-1: none), the same in every lane.
+DEV int pred_slot(unsigned long long id)
 {
-    return __double_as_longlong(y[at]);
+    const int lane = threadIdx.x & 63;
+    const unsigned long long o =
+        lane < PRED_SLOTS ? __hip_atomic_load(&g_pred_owner[lane], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0ull;
+    const uint64_t mine = __ballot(o == id);
+    return mine ? (int)__builtin_ctzll(mine) : -1;
 }
 
+// Gives back what a call holds whose second kernel could not be launched.
+__global__ void predict_release_kernel(unsigned long long id)
+{
+    if (threadIdx.x < PRED_SLOTS && atomicCAS(&g_pred_owner[threadIdx.x], id, 0ull) == id)
+        g_pred_done[threadIdx.x] = 0u;
+}
+
+// Claims a slot.
 // Also checks every offset: with a malformed one no slot is taken, and each group computes
 // its own tiles (a good group's energies do not depend on the others' offsets).
 constexpr int CLAIM_NT = 1024;
-__global__ __launch_bounds__(CLAIM_NT) void predict_claim_kernel(PredArgs a, int64_t n_groups)
+__global__ __launch_bounds__(CLAIM_NT) void predict_claim_kernel(PredArgs a)
 {
-    __shared__ int slot_s, bad_s;
+    __shared__ int bad_s;
     if (threadIdx.x == 0)
         bad_s = 0;
     __syncthreads();
@@ -886,17 +902,10 @@ __global__ __launch_bounds__(CLAIM_NT) void predict_claim_kernel(PredArgs a, int
     if (bad)
         bad_s = 1;
     __syncthreads();
-    if (threadIdx.x == 0) {
-        int slot = -1;
-        if (!bad_s)
-            for (int k = 0; k < PRED_SLOTS && slot < 0; ++k)
-                if (atomicCAS(&g_pred_busy[k], 0u, 1u) == 0u)
-                    slot = k;
-        slot_s = slot;
-    }
-    __syncthreads();
-    for (int64_t w = threadIdx.x; w < n_groups; w += CLAIM_NT)
-        a.y[w * a.C] = __longlong_as_double((long long)slot_s);
+    if (threadIdx.x == 0 && !bad_s)
+        for (int k = 0; k < PRED_SLOTS; ++k)
+            if (atomicCAS(&g_pred_owner[k], 0ull, a.id) == 0ull)
+                break;
 }
 
 template <class S>
@@ -909,7 +918,7 @@ __global__ __launch_bounds__(S::NT, S::BM == 64 ? 3 : 2) void predict_tile_kerne
     const int64_t lw = xcd_remap(blockIdx.x, (total + 7) & ~int64_t(7));
     if (lw >= total)
         return;
-    const int64_t slot = pred_slot(a.y, 0);
+    const int64_t slot = pred_slot(a.id);
     if (slot < 0)
         return;
     const int64_t t = lw / a.split, s = lw % a.split;
@@ -946,7 +955,7 @@ __global__ __launch_bounds__(KNM_NT) void predict_sum_kernel(PredArgs a)
     // Every configuration must be a range inside [0, n_atoms); offsets[0] = 0 and offsets[N] =
     // n_atoms are checked by the first and last group.  A violation gives NaN energies for the
     // group and GAP_EINVAL in the status word (when there is one).
-    const int64_t slot = a.split > 0 ? pred_slot(a.y, cfg_lo) : -1;
+    const int64_t slot = a.split > 0 ? pred_slot(a.id) : -1;
     if (tid == 0)
         bad_s = 0;
     __syncthreads();
@@ -1013,7 +1022,7 @@ __global__ __launch_bounds__(KNM_NT) void predict_sum_kernel(PredArgs a)
         a.y[cfg_lo + tid] = ysum;
     // the last workgroup to have read the pieces frees the slot
     if (slot >= 0 && arrive_last(&g_pred_done[slot], gridDim.x, &last_s) && tid == 0)
-        __hip_atomic_store(&g_pred_busy[slot], 0u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(&g_pred_owner[slot], 0ull, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 hipError_t launch_predict(const double *X, int64_t n_atoms, const int64_t *offsets, int64_t N,
@@ -1035,6 +1044,8 @@ hipError_t launch_predict(const double *X, int64_t n_atoms, const int64_t *offse
     a.c = c;
     a.y = y;
     a.status = status;
+    static std::atomic<unsigned long long> calls{0};
+    a.id = ++calls;
     a.C = n_atoms > 0 ? (224 * N) / n_atoms : N;
     a.C = a.C < 1 ? 1 : (a.C > 256 ? 256 : a.C);
     const int64_t groups = (N + a.C - 1) / a.C;
@@ -1051,7 +1062,7 @@ hipError_t launch_predict(const double *X, int64_t n_atoms, const int64_t *offse
         split = PRED_CAP / (N + a.tiles);
     a.split = (int)split;  // 0: no atoms, or too many pieces for a slot
     if (a.split > 0) {
-        hipLaunchKernelGGL(predict_claim_kernel, dim3(1), dim3(CLAIM_NT), 0, s, a, groups);
+        hipLaunchKernelGGL(predict_claim_kernel, dim3(1), dim3(CLAIM_NT), 0, s, a);
         const unsigned grid = (unsigned)((a.tiles * a.split + 7) & ~int64_t(7));
         if (a.small)
             hipLaunchKernelGGL(predict_tile_kernel<PSS>, dim3(grid), dim3(PSS::NT), 0, s, a);
@@ -1059,7 +1070,12 @@ hipError_t launch_predict(const double *X, int64_t n_atoms, const int64_t *offse
             hipLaunchKernelGGL(predict_tile_kernel<PSL>, dim3(grid), dim3(PSL::NT), 0, s, a);
     }
     hipLaunchKernelGGL(predict_sum_kernel, dim3((unsigned)groups), dim3(KNM_NT), 0, s, a);
-    return hipGetLastError();
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess && a.split > 0) {
+        hipLaunchKernelGGL(predict_release_kernel, dim3(1), dim3(64), 0, s, a.id);
+        (void)hipGetLastError();
+    }
+    return e;
 }
 
 hipError_t launch_plan_tiles(const int64_t *offsets, int64_t N, int64_t n_atoms, int chunk, const KnmPlan &p,
