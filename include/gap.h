@@ -294,6 +294,8 @@ gap_status gap_solve(gap_handle h, const double *y, double *c_out, gap_solve_inf
  * of any handles, streams and threads may run at the same time, each with its own
  * y_out; one that finds no part free computes without it, with the same result.  A captured
  * call counts as one call: its replays follow one another.
+ * A configuration's energy does not depend, to the bit, on the request that it is
+ * part of: every sum has the same order whatever the other configurations are.
  * The offsets are checked on the device before any
  * descriptor is read: a configuration whose range is not inside [0, n_atoms),
  * or offsets[0] != 0, or offsets[n_configs] != n_atoms, gives NaN energies for

@@ -722,42 +722,49 @@ __global__ __launch_bounds__(KNM_NT, 2) void knm_group_kernel(KnmGroup g)
 // ---------------------------------------------------------------------------
 // Prediction (Eqs. 1-2): y_A = sum_{i in A} sum_j c_j sigma_w^2 (x_i . x_j)^zeta.
 //
-// The atoms are cut into tiles of BM consecutive rows and the sparse points into
-// `split` runs of column tiles; workgroup (tile, run) forms its atoms' energies
-// over its run (the atom-by-sparse covariances stay in registers) and adds them
-// up, in atom order, over the piece of each configuration that lies in the tile.
-// A second kernel adds a configuration's pieces: tile by tile, run by run.  One
-// request's column runs thus spread over the chip: with one workgroup per
-// few configurations and all columns, a single configuration against 4,000
-// points took 4.2 ms on one CU, and 4,096 configurations 21 ms with the
-// CUs a third idle in the last round.
+// The order of the sums is the same whatever the request: within a column tile of KNM_BN
+// sparse points as the wave adds them up, the tiles of a group of PRED_G in order, the groups in
+// order, then the configuration's atoms in order.  So a configuration's energy does not depend,
+// to the bit, on the configurations beside it or on how the work is split.
 //
-// The pieces live in a static pool of PRED_SLOTS slots per GPU (a predict call has
-// no workspace).  Every call has a number of its own; its first kernel claims a free slot by
-// writing that number into the slot's owner word, the other kernels look for it there, and the
-// last workgroup of the second one frees the slot.  Nothing of a call's state lies in memory
-// that another call may write, the caller's output included.  Claiming on the device works for any
+// The atoms are cut into tiles of consecutive rows, the sparse points into runs of one column
+// tile or of a whole group; workgroup (tile, run) forms its atoms' energies over its run (the
+// atom-by-sparse covariances stay in registers).  A second kernel adds up an atom's runs and a
+// configuration's atoms.  One request's column runs thus spread over the chip: with one
+// workgroup per few configurations and all columns, a single configuration against 4,000
+// points took 4.2 ms on one CU, and 4,096 configurations 21 ms with the
+// CUs a third idle in the last round.  A request whose energies exceed what a call may claim is
+// taken in ranges of atoms, one after the other.
+//
+// The atoms' energies lie in a static pool of PRED_CHUNKS chunks of 1 MiB per GPU (a predict
+// call has no workspace).  Every call has a number of its own; its first kernel claims the
+// consecutive chunks it needs by writing that number into their owner words, the other kernels look
+// for it there, and the last workgroup of the last one frees them.  Nothing of a call's state lies in
+// memory that another call may write, the caller's output included.  Claiming on the device works for any
 // streams, threads and captured graphs (whose replays, one after the other, keep their number),
-// and never waits: with no slot free (more than PRED_SLOTS
-// calls in flight), with malformed offsets, or when one request's pieces exceed a
-// slot, the second kernel computes its groups' tiles itself, with the same sums in
-// the same order.
+// and never waits: with no room free, the
+// second kernel computes its groups' atoms itself, with the same sums in the same order.
 //
 // Bound by the matrix cores from a few hundred configurations on (d = 400, M = 4,000:
-// 4,096 configurations 21.3 -> 7.6 ms, 62 TFLOP/s; d = 256, M = 2,250: 333
-// configurations 3.2 -> 0.26 ms), by the latency of the column tile's k loop below
-// (one configuration 4,230 -> 29 us, three launches). ---------------------------------------------------------------------------
-constexpr int PRED_SLOTS = 32;
-constexpr int64_t PRED_CAP = 131072;  // doubles of a slot (1 MiB)
-static __device__ double g_pred_pool[PRED_SLOTS * PRED_CAP];
-static __device__ unsigned long long g_pred_owner[PRED_SLOTS];  // the call's number; 0: free
-static __device__ unsigned g_pred_done[PRED_SLOTS];
-static_assert(PRED_SLOTS <= 64, "one lane per owner word");
+// 4,096 configurations 21.5 -> 7.3 ms, 64 TFLOP/s; d = 256, M = 2,250: 333
+// configurations 3.2 -> 0.26 ms; d = 128, M = 1,000: 150,000 configurations in nine ranges 39.8 ->
+// 25.4 ms), by the latency of the column tile's k loop below (one configuration 4,230 -> 30 us,
+// three launches).  Without room in the pool a request takes about the time on the left.
+// ---------------------------------------------------------------------------
+constexpr int PRED_G = 4;               // column tiles of a group
+constexpr int PRED_CHUNKS = 128;
+constexpr int64_t PRED_CHUNK = 131072;  // doubles of a chunk
+constexpr int PRED_MAX = 20;            // chunks of one call, at most
+static __device__ double g_pred_pool[PRED_CHUNKS * PRED_CHUNK];
+static __device__ unsigned long long g_pred_owner[PRED_CHUNKS];  // the call's number; 0: free
+static __device__ unsigned g_pred_done[PRED_CHUNKS];             // arrivals, at the call's first chunk
+static_assert(PRED_CHUNKS == 128 && PRED_MAX <= 64, "two owner words per lane; one lane per claimed chunk");
 
 // Both tile heights give waves of 64 columns and the same order of every sum.
 using PSL = KTile<double, KNM_BM, KNM_BN, 4, 4, 1>;  // 256 atoms
 using PSS = KTile<double, 64, KNM_BN, 8, 4, 1>;     // 64 atoms
-static_assert(PSL::TN == PSS::TN && PSL::WN == PSS::WN && PSL::NT == KNM_NT, "one summation order");
+static_assert(PSL::TN == PSS::TN && PSL::WN == 1 && PSS::WN == 1 && PSL::NT == KNM_NT, "one summation order");
+static_assert(PSS::NT == KNM_NT && PSL::BM == KNM_NT, "a thread per atom");
 
 struct PredArgs {
     const double *X;
@@ -771,19 +778,20 @@ struct PredArgs {
     double *y;
     int32_t *status;
     int64_t C;              // configurations per group (checked together; a bad one makes the group NaN)
-    int64_t tiles, n_ct;    // atom tiles, column tiles
-    int split;              // runs of column tiles
-    int small;              // 64-atom tiles
+    int64_t n_ct;           // column tiles
+    int run;                // column tiles per run: 1 or PRED_G (0: the atoms' energies are not kept)
+    int64_t n_runs;
+    int64_t a0, a1;         // the atoms of this range
+    int64_t tiles, ld;      // atom tiles, and atoms they cover: a run's energies lie ld apart
+    int chunks;             // claimed
     unsigned long long id;  // the call's number (positive)
 };
 
-// Energies of the tile's atoms over column tiles [ct0, ct1), into eps[0 .. S::BM).
+// Energy of atom row0 + threadIdx.x (the first S::BM threads) over column tiles [ct0, ct1).
 template <class S>
-DEV void predict_tile_energies(const PredArgs &a, int64_t t, int64_t ct0, int64_t ct1, d2 *lds,
-                               double (&part)[S::WN][S::BM], double *eps)
+DEV double predict_tile_energy(const PredArgs &a, int64_t row0, int64_t ct0, int64_t ct1, d2 *lds, double *part)
 {
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int wm = wave / S::WN, wn = wave % S::WN;
+    const int tid = threadIdx.x, lane = tid & 63, wm = tid >> 6;
     const bool direct = rows_aligned16(a.X, a.d) && rows_aligned16(a.XM, a.d);
     double e_sum = 0.0;
     for (int64_t ct = ct0; ct < ct1; ++ct) {
@@ -794,25 +802,21 @@ DEV void predict_tile_energies(const PredArgs &a, int64_t t, int64_t ct0, int64_
             const int r = S::unit_row(i);
             const double *p = a.XM;  // a missing row reads the first sparse row, unused below
             if (r < S::BM) {
-                if (t * S::BM + r < a.n_atoms)
-                    p = a.X + (t * S::BM + r) * (int64_t)a.d;
+                if (row0 + r < a.n_atoms)
+                    p = a.X + (row0 + r) * (int64_t)a.d;
             } else if (col0 + r - S::BM < a.M) {
                 p = a.XM + (col0 + r - S::BM) * (int64_t)a.d;
             }
             src[i] = p + S::unit_k(i);
         }
         d4 acc[S::FM][S::FN];
-#pragma unroll
-        for (int i = 0; i < S::FM; ++i)
-#pragma unroll
-            for (int j = 0; j < S::FN; ++j)
-                acc[i][j] = d4{0.0, 0.0, 0.0, 0.0};
+        ktile_zero<S>(acc);
         ktile_product<S>(acc, lds, src, a.d, direct);
         double cw[S::FN];
         bool in[S::FN];
 #pragma unroll
         for (int j = 0; j < S::FN; ++j) {
-            const int64_t col = col0 + acc_col<S>(wn, j, lane, 0);
+            const int64_t col = col0 + acc_col<S>(0, j, lane, 0);
             in[j] = col < a.M;
             cw[j] = in[j] ? a.c[col] : 0.0;
         }
@@ -830,199 +834,186 @@ DEV void predict_tile_energies(const PredArgs &a, int64_t t, int64_t ct0, int64_
                 s += __shfl_xor(s, 4, 64);
                 s += __shfl_xor(s, 8, 64);
                 if ((lane & 15) == 0)
-                    part[wn][acc_row<S>(wm, i, lane, e)] = s;
+                    part[acc_row<S>(wm, i, lane, e)] = s;
             }
         __syncthreads();
-        if (tid < S::BM) {
-            double add = part[0][tid];
-#pragma unroll
-            for (int q = 1; q < S::WN; ++q)
-                add += part[q][tid];
-            e_sum += add;
-        }
+        if (tid < S::BM)
+            e_sum += part[tid];
     }
-    if (tid < S::BM)
-        eps[tid] = e_sum;
-    __syncthreads();
+    return e_sum;
 }
 
-// First and last column tile of run s.
-DEV int64_t run_lo(const PredArgs &a, int64_t s) { return s * a.n_ct / a.split; }
-
-// Number of configurations whose atoms end at or before row r (every lane probes one
-// point of the remaining range; uniform).
-DEV int64_t configs_before(const int64_t *offsets, int64_t N, int64_t r)
+// Where the call's part of the pool starts (-1: it has none), the same in every lane.
+DEV int64_t pred_base(unsigned long long id)
 {
     const int lane = threadIdx.x & 63;
-    int64_t lo = 0, hi = N;  // offsets[c + 1] <= r for c < lo, > r for c >= hi
-    while (lo < hi) {
-        const int64_t step = (hi - lo + 63) / 64;
-        const int64_t c = lo + lane * step;
-        const uint64_t le = __ballot(c < hi && offsets[c + 1] <= r);
-        const int k = __builtin_ctzll(~le);  // leading run of probes at or before r (64: all of them)
-        const int64_t first_gt = lo + (int64_t)(le == ~0ull ? 64 : k) * step;
-        if (k > 0 || le == ~0ull)
-            lo = first_gt - step + 1;
-        if (first_gt < hi)
-            hi = first_gt;
-    }
-    return lo;
+    const auto owner = [](int k) {
+        return __hip_atomic_load(&g_pred_owner[k], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    };
+    const uint64_t lo = __ballot(owner(lane) == id), hi = __ballot(owner(64 + lane) == id);
+    const int k = lo ? __builtin_ctzll(lo) : (hi ? 64 + __builtin_ctzll(hi) : -1);
+    return k < 0 ? -1 : k * PRED_CHUNK;
 }
 
-// The call's slot (-1: none), the same in every lane.
-DEV int pred_slot(unsigned long long id)
+// Gives back what a call holds whose last kernel could not be launched.
+__global__ __launch_bounds__(PRED_CHUNKS) void predict_release_kernel(unsigned long long id)
 {
-    const int lane = threadIdx.x & 63;
-    const unsigned long long o =
-        lane < PRED_SLOTS ? __hip_atomic_load(&g_pred_owner[lane], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0ull;
-    const uint64_t mine = __ballot(o == id);
-    return mine ? (int)__builtin_ctzll(mine) : -1;
-}
-
-// Gives back what a call holds whose second kernel could not be launched.
-__global__ void predict_release_kernel(unsigned long long id)
-{
-    if (threadIdx.x < PRED_SLOTS && atomicCAS(&g_pred_owner[threadIdx.x], id, 0ull) == id)
+    if (atomicCAS(&g_pred_owner[threadIdx.x], id, 0ull) == id)
         g_pred_done[threadIdx.x] = 0u;
 }
 
-// Claims a slot.
-// Also checks every offset: with a malformed one no slot is taken, and each group computes
-// its own tiles (a good group's energies do not depend on the others' offsets).
-constexpr int CLAIM_NT = 1024;
-__global__ __launch_bounds__(CLAIM_NT) void predict_claim_kernel(PredArgs a)
+// One wave claims a.chunks consecutive free chunks, each lane one of them; if another call took one
+// of them meanwhile, it gives the others back and looks again.
+constexpr int CLAIM_TRIES = 16;
+__global__ __launch_bounds__(64) void predict_claim_kernel(PredArgs a)
 {
-    __shared__ int bad_s;
-    if (threadIdx.x == 0)
-        bad_s = 0;
-    __syncthreads();
-    bool bad = threadIdx.x == 0 && (a.offsets[0] != 0 || a.offsets[a.N] != a.n_atoms);
-    for (int64_t c = threadIdx.x; c < a.N; c += CLAIM_NT)
-        bad |= a.offsets[c] > a.offsets[c + 1];
-    if (bad)
-        bad_s = 1;
-    __syncthreads();
-    if (threadIdx.x == 0 && !bad_s)
-        for (int k = 0; k < PRED_SLOTS; ++k)
-            if (atomicCAS(&g_pred_owner[k], 0ull, a.id) == 0ull)
-                break;
+    const int lane = threadIdx.x;
+    const auto owner = [](int k) {
+        return __hip_atomic_load(&g_pred_owner[k], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    };
+    for (int t = 0; t < CLAIM_TRIES; ++t) {
+        const uint64_t lo = __ballot(owner(lane) == 0ull), hi = __ballot(owner(64 + lane) == 0ull);
+        int at = -1;
+        for (int k = 0, run = 0; k < PRED_CHUNKS && at < 0; ++k) {
+            run = ((k < 64 ? lo >> k : hi >> (k - 64)) & 1) ? run + 1 : 0;
+            if (run == a.chunks)
+                at = k + 1 - run;
+        }
+        if (at < 0)
+            return;
+        const bool mine = lane < a.chunks && atomicCAS(&g_pred_owner[at + lane], 0ull, a.id) == 0ull;
+        if (__popcll(__ballot(mine)) == a.chunks)
+            return;
+        if (mine)
+            __hip_atomic_store(&g_pred_owner[at + lane], 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
 }
 
 template <class S>
 __global__ __launch_bounds__(S::NT, S::BM == 64 ? 3 : 2) void predict_tile_kernel(PredArgs a)
 {
     __shared__ __align__(16) d2 lds[2 * S::UNITS];
-    __shared__ double part[S::WN][S::BM];
-    __shared__ double eps[S::BM];
-    const int64_t total = a.tiles * a.split;
+    __shared__ double part[S::BM];
+    const int64_t total = a.tiles * a.n_runs;
     const int64_t lw = xcd_remap(blockIdx.x, (total + 7) & ~int64_t(7));
     if (lw >= total)
         return;
-    const int64_t slot = pred_slot(a.id);
-    if (slot < 0)
+    const int64_t base = pred_base(a.id);
+    if (base < 0)
         return;
-    const int64_t t = lw / a.split, s = lw % a.split;
-    // the configurations that own the tile's first and last row
-    const int64_t r0 = t * S::BM, r1 = (r0 + S::BM < a.n_atoms) ? r0 + S::BM : a.n_atoms;
-    const int64_t c_first = configs_before(a.offsets, a.N, r0), c_end = configs_before(a.offsets, a.N, r1 - 1) + 1;
-    predict_tile_energies<S>(a, t, run_lo(a, s), run_lo(a, s + 1), lds, part, eps);
-    double *out = g_pred_pool + slot * PRED_CAP + s * (a.N + a.tiles) + t;
-    for (int64_t c = c_first + threadIdx.x; c < c_end && c < a.N; c += S::NT) {
-        int64_t lo = a.offsets[c], hi = a.offsets[c + 1];
-        lo = lo > r0 ? lo : r0;
-        hi = hi < r1 ? hi : r1;
-        if (lo >= hi)
-            continue;
-        double sum = 0.0;
-        for (int64_t r = lo; r < hi; ++r)
-            sum += eps[r - r0];
-        out[c] = sum;
-    }
+    const int64_t t = lw / a.n_runs, s = lw % a.n_runs;
+    const int64_t ct0 = s * a.run, ct1 = ct0 + a.run < a.n_ct ? ct0 + a.run : a.n_ct;
+    const double e = predict_tile_energy<S>(a, a.a0 + t * S::BM, ct0, ct1, lds, part);
+    if (threadIdx.x < S::BM)
+        g_pred_pool[base + s * a.ld + t * S::BM + threadIdx.x] = e;
 }
 
-// One group of configurations: checks their offsets, then adds up their pieces.
-__global__ __launch_bounds__(KNM_NT) void predict_sum_kernel(PredArgs a)
+// An atom's energy from its runs' energies at p, p + ld, ...: groups of PRED_G column tiles in
+// order, as a workgroup that takes a whole group adds them.
+DEV double pred_atom_energy(const PredArgs &a, const double *p)
+{
+    constexpr int B = 32;
+    static_assert(B % PRED_G == 0, "whole groups");
+    double e = 0.0;
+    for (int64_t s0 = 0; s0 < a.n_runs; s0 += B) {
+        double v[B];  // all loads in flight
+#pragma unroll
+        for (int k = 0; k < B; ++k)
+            v[k] = s0 + k < a.n_runs ? p[(s0 + k) * a.ld] : 0.0;
+        if (a.run == 1) {
+#pragma unroll
+            for (int k = 0; k < B; k += PRED_G) {
+                double g = 0.0;
+#pragma unroll
+                for (int q = 0; q < PRED_G; ++q)
+                    g += v[k + q];
+                e += g;
+            }
+        } else {
+#pragma unroll
+            for (int k = 0; k < B; ++k)
+                e += v[k];
+        }
+    }
+    return e;
+}
+
+// One group of configurations: checks their offsets, then adds up their atoms' energies, 256 atoms at a
+// time, for the atoms of the range.  LAST: the last range; the group's result if its offsets are bad, and all
+// of its atoms if the call has no part of the pool.  (The ranges before pass most groups by at
+// once; without the code and the LDS of the tiles more of them do so at a time.)
+template <bool LAST>
+__global__ __launch_bounds__(KNM_NT, LAST ? 2 : 4) void predict_sum_kernel(PredArgs a)
 {
     using S = PSL;
-    __shared__ __align__(16) d2 lds[2 * S::UNITS];
-    __shared__ double part[S::WN][S::BM];
+    __shared__ __align__(16) d2 lds[LAST ? 2 * S::UNITS : 1];
+    __shared__ double part[LAST ? S::BM : 1];
     __shared__ double eps[S::BM];
     __shared__ int bad_s, last_s;
     const int tid = threadIdx.x;
     const int64_t cfg_lo = (int64_t)blockIdx.x * a.C;
     const int64_t cfg_hi = (cfg_lo + a.C < a.N) ? cfg_lo + a.C : a.N;
     const int ncfg = (int)(cfg_hi - cfg_lo);
+    const int64_t g0 = a.offsets[cfg_lo], g1 = a.offsets[cfg_hi];
+    if (!LAST && (g1 < a.a0 || g0 >= a.a1))
+        return;
+    const int64_t base = a.run > 0 ? pred_base(a.id) : -1;
+    if (!LAST && base < 0)
+        return;
     // Every configuration must be a range inside [0, n_atoms); offsets[0] = 0 and offsets[N] =
     // n_atoms are checked by the first and last group.  A violation gives NaN energies for the
     // group and GAP_EINVAL in the status word (when there is one).
-    const int64_t slot = a.split > 0 ? pred_slot(a.id) : -1;
     if (tid == 0)
         bad_s = 0;
+    const int64_t my_lo = tid < ncfg ? a.offsets[cfg_lo + tid] : 0, my_hi = tid < ncfg ? a.offsets[cfg_lo + tid + 1] : 0;
     __syncthreads();
-    int64_t my_lo = 0, my_hi = 0;
-    if (tid < ncfg) {
-        my_lo = a.offsets[cfg_lo + tid];
-        my_hi = a.offsets[cfg_lo + tid + 1];
-        if (my_lo < 0 || my_hi < my_lo || my_hi > a.n_atoms)
-            bad_s = 1;
-    }
-    if (tid == 0 && ((cfg_lo == 0 && a.offsets[0] != 0) || (cfg_hi == a.N && a.offsets[a.N] != a.n_atoms)))
+    if (my_lo < 0 || my_hi < my_lo || my_hi > a.n_atoms)
+        bad_s = 1;
+    if (tid == 0 && ((cfg_lo == 0 && g0 != 0) || (cfg_hi == a.N && g1 != a.n_atoms)))
         bad_s = 1;
     __syncthreads();
-    const bool bad = bad_s != 0;
     double ysum = 0.0;
-    if (bad) {
+    bool out = tid < ncfg;
+    if (bad_s != 0) {
+        out = out && LAST;
         ysum = __builtin_nan("");
-        if (tid == 0 && a.status)
+        if (LAST && tid == 0 && a.status)
             set_status(a.status, DST_EINVAL);
-    } else if (slot >= 0) {
-        if (tid < ncfg && my_lo < my_hi) {
-            const int64_t bm = a.small ? PSS::BM : PSL::BM;
-            const double *p = g_pred_pool + slot * PRED_CAP + cfg_lo + tid;
-            for (int64_t t = my_lo / bm; t * bm < my_hi; ++t) {
-                double piece = 0.0;
-#pragma unroll 8
-                for (int s = 0; s < a.split; ++s)
-                    piece += p[s * (a.N + a.tiles) + t];
-                ysum += piece;
-            }
-        }
     } else {
-        // no slot: the tiles that the group meets (of 256 rows, four small tiles at a time),
-        // and in them the pieces of its configurations
-        const int64_t atom_lo = a.offsets[cfg_lo], atom_hi = a.offsets[cfg_hi];
-        const int64_t bm = a.small ? PSS::BM : PSL::BM;
-        const int runs = a.split > 0 ? a.split : 1;
-        PredArgs b = a;
-        b.split = runs;
-        for (int64_t t = atom_lo / S::BM; t * S::BM < atom_hi; ++t) {
-            const int64_t r0 = t * S::BM;
-            constexpr int PIECES = PSL::BM / PSS::BM;
-            double piece[PIECES] = {};
-            for (int s = 0; s < runs; ++s) {
-                predict_tile_energies<S>(b, t, run_lo(b, s), run_lo(b, s + 1), lds, part, eps);
-#pragma unroll
-                for (int q = 0; q < PIECES; ++q) {
-                    const int64_t q0 = r0 + q * bm, q1 = (q + 1) * bm <= S::BM ? q0 + bm : q0;
-                    const int64_t lo = my_lo > q0 ? my_lo : q0, hi = my_hi < q1 ? my_hi : q1;
-                    double sum = 0.0;
-                    if (tid < ncfg)
-                        for (int64_t r = lo; r < hi; ++r)
-                            sum += eps[r - r0];
-                    piece[q] += sum;
-                }
-                __syncthreads();
+        // a configuration starts in the range of its first atom (an empty one at the very end in the
+        // last), and is carried on from one range to the next in y
+        const int64_t a0 = base >= 0 ? a.a0 : 0;
+        const bool begun = my_lo < a0;
+        out = out && (begun ? my_hi > a0 : (LAST || my_lo < a.a1));
+        if (out && begun)
+            ysum = a.y[cfg_lo + tid];
+        const int64_t lo = g0 > a0 ? g0 : a0, hi = g1 < a.a1 ? g1 : a.a1;
+        for (int64_t cs = lo; cs < hi; cs += S::BM) {
+            double e = 0.0;
+            if (base >= 0) {
+                if (cs + tid < hi)
+                    e = pred_atom_energy(a, g_pred_pool + base + (cs - a0) + tid);
+            } else if constexpr (LAST) {
+                for (int64_t ct = 0; ct < a.n_ct; ct += PRED_G)
+                    e += predict_tile_energy<S>(a, cs, ct, ct + PRED_G < a.n_ct ? ct + PRED_G : a.n_ct, lds, part);
             }
-#pragma unroll
-            for (int q = 0; q < PIECES; ++q)
-                ysum += piece[q];
+            __syncthreads();  // the previous atoms' sums have read eps
+            eps[tid] = e;
+            __syncthreads();
+            const int64_t r0 = my_lo > cs ? my_lo : cs;
+            int64_t r1 = my_hi < cs + S::BM ? my_hi : cs + S::BM;
+            r1 = r1 < hi ? r1 : hi;
+            if (tid < ncfg)
+#pragma unroll 8
+                for (int64_t r = r0; r < r1; ++r)
+                    ysum += eps[r - cs];
         }
     }
-    if (tid < ncfg)
+    if (out)
         a.y[cfg_lo + tid] = ysum;
-    // the last workgroup to have read the pieces frees the slot
-    if (slot >= 0 && arrive_last(&g_pred_done[slot], gridDim.x, &last_s) && tid == 0)
-        __hip_atomic_store(&g_pred_owner[slot], 0ull, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
+    // the last workgroup to have read the energies frees them
+    if (LAST && base >= 0 && arrive_last(&g_pred_done[base / PRED_CHUNK], gridDim.x, &last_s) && tid < a.chunks)
+        __hip_atomic_store(&g_pred_owner[base / PRED_CHUNK + tid], 0ull, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 hipError_t launch_predict(const double *X, int64_t n_atoms, const int64_t *offsets, int64_t N,
@@ -1049,30 +1040,48 @@ hipError_t launch_predict(const double *X, int64_t n_atoms, const int64_t *offse
     a.C = n_atoms > 0 ? (224 * N) / n_atoms : N;
     a.C = a.C < 1 ? 1 : (a.C > 256 ? 256 : a.C);
     const int64_t groups = (N + a.C - 1) / a.C;
-    // 64-atom tiles where 256-atom ones would not fill the chip's 512 workgroup places
-    // twice: a workgroup then has a quarter of the work, and the last round costs less
     a.n_ct = (M + KNM_BN - 1) / KNM_BN;
-    const int64_t large = (n_atoms + PSL::BM - 1) / PSL::BM;
-    a.small = large * a.n_ct < 1024;
-    a.tiles = a.small ? (n_atoms + PSS::BM - 1) / PSS::BM : large;
-    // runs: enough workgroups for about twelve rounds, so that the last one costs little
-    int64_t split = a.tiles > 0 ? (6144 + a.tiles - 1) / a.tiles : 0;
-    split = split > a.n_ct ? a.n_ct : split;
-    if (split * (N + a.tiles) > PRED_CAP)
-        split = PRED_CAP / (N + a.tiles);
-    a.split = (int)split;  // 0: no atoms, or too many pieces for a slot
-    if (a.split > 0) {
-        hipLaunchKernelGGL(predict_claim_kernel, dim3(1), dim3(CLAIM_NT), 0, s, a);
-        const unsigned grid = (unsigned)((a.tiles * a.split + 7) & ~int64_t(7));
-        if (a.small)
-            hipLaunchKernelGGL(predict_tile_kernel<PSS>, dim3(grid), dim3(PSS::NT), 0, s, a);
+    auto tiles = [](int64_t n, int64_t b) { return (n + b - 1) / b; };
+    // runs of one column tile where their energies fit what a call may claim, else whole groups
+    constexpr int64_t ROOM = PRED_MAX * PRED_CHUNK;
+    a.run = tiles(n_atoms, PSS::BM) * PSS::BM * a.n_ct <= ROOM ? 1 : PRED_G;
+    a.n_runs = tiles(a.n_ct, a.run);
+    // as many atoms at a time as the claim holds, in ranges of equal length
+    const int64_t most = ROOM / a.n_runs / PSL::BM * PSL::BM;
+    const int64_t n_ranges = n_atoms > 0 && most > 0 ? tiles(n_atoms, most) : 1;
+    const int64_t range = tiles(tiles(n_atoms, n_ranges), PSL::BM) * PSL::BM;
+    // 64-atom tiles where 256-atom ones are fewer than four rounds of the chip's 512 workgroup
+    // places: a workgroup then has a quarter of the work, and the last round costs less (1,692
+    // of the large tiles: 254 us, 275 with them); from there on the large ones are 2 % faster (9,009:
+    // 1,829 us, 1,873 with small ones)
+    const bool small = tiles(range, PSL::BM) * a.n_runs < 2048;
+    const int64_t bm = small ? PSS::BM : PSL::BM;
+    const int64_t ld = tiles(range < n_atoms ? range : n_atoms, bm) * bm;
+    a.chunks = (int)tiles(ld * a.n_runs, PRED_CHUNK);
+    if (n_atoms == 0 || most == 0)  // (then one range)
+        a.run = a.chunks = 0;
+    if (a.run > 0)
+        hipLaunchKernelGGL(predict_claim_kernel, dim3(1), dim3(64), 0, s, a);
+    for (int64_t r = 0; r < n_ranges; ++r) {
+        a.a0 = r * range;
+        a.a1 = a.a0 + range < n_atoms ? a.a0 + range : n_atoms;
+        if (a.run > 0) {
+            a.tiles = tiles(a.a1 - a.a0, bm);
+            a.ld = a.tiles * bm;
+            const unsigned grid = (unsigned)((a.tiles * a.n_runs + 7) & ~int64_t(7));
+            if (small)
+                hipLaunchKernelGGL(predict_tile_kernel<PSS>, dim3(grid), dim3(PSS::NT), 0, s, a);
+            else
+                hipLaunchKernelGGL(predict_tile_kernel<PSL>, dim3(grid), dim3(PSL::NT), 0, s, a);
+        }
+        if (r == n_ranges - 1)
+            hipLaunchKernelGGL(predict_sum_kernel<true>, dim3((unsigned)groups), dim3(KNM_NT), 0, s, a);
         else
-            hipLaunchKernelGGL(predict_tile_kernel<PSL>, dim3(grid), dim3(PSL::NT), 0, s, a);
+            hipLaunchKernelGGL(predict_sum_kernel<false>, dim3((unsigned)groups), dim3(KNM_NT), 0, s, a);
     }
-    hipLaunchKernelGGL(predict_sum_kernel, dim3((unsigned)groups), dim3(KNM_NT), 0, s, a);
     const hipError_t e = hipGetLastError();
-    if (e != hipSuccess && a.split > 0) {
-        hipLaunchKernelGGL(predict_release_kernel, dim3(1), dim3(64), 0, s, a.id);
+    if (e != hipSuccess && a.chunks > 0) {
+        hipLaunchKernelGGL(predict_release_kernel, dim3(1), dim3(PRED_CHUNKS), 0, s, a.id);
         (void)hipGetLastError();
     }
     return e;
