@@ -42,9 +42,10 @@ DEV void static_for(F f)
     }
 }
 
-// 1 / d for a normal d, to about one ulp: the hardware's estimate (error e below 2^-20) and one
-// step of third order, x + x (e + e^2) (a third of a division's latency, which the chains
-// below would wait for at each step).
+// 1 / d to about one ulp: the hardware's estimate (error e below 2^-20) and one step of third
+// order, x + x (e + e^2) (a third of a division's latency, which the chains below would wait for
+// at each step).  For d and 1 / d well inside the normal range (2^-1000 .. 2^1000): a subnormal d
+// gives NaN.  chol64 sees to that; lu64_signs divides by pivots between 1 and 2.
 DEV double fast_rcp(double d)
 {
     const double x = __builtin_amdgcn_rcp(d);
@@ -142,6 +143,35 @@ DEV void pack_upper(F f, double *P, double (*T)[16][17])
     __syncthreads();
 }
 
+// The same as chol64 below, a row at a time with a square root and divisions, for any finite
+// pivots.
+DEV void chol64_plain(double (*S)[DL], double *P, int *ok)
+{
+    const int t = threadIdx.x, wave = t >> 6;
+#pragma unroll 1
+    for (int k = 0; k < S64; ++k) {
+        const double d = S[k][k];
+        const bool good = d > 0.0 && d < INFINITY;
+        const double u = sqrt(good ? d : 1.0);
+        __syncthreads();
+        if (t < S64)
+            S[k][t] = t > k ? S[k][t] / u : (t == k ? u : 0.0);
+        if (t == k && !good)
+            *ok = 0;
+        __syncthreads();
+#pragma unroll 1
+        for (int e = t; e < S64 * S64; e += 256) {
+            const int i = e >> 6, j = e & 63;
+            if (i > k && j >= i)
+                S[i][j] -= S[k][i] * S[k][j];
+        }
+        __syncthreads();
+    }
+    invert_upper16(&S[16 * wave][16 * wave], DL, P + (NBLK + wave) * BLK);
+    pack_blocks([&](int i, int j) { return S[i][j]; }, P);
+    __syncthreads();
+}
+
 // Cholesky S = U^T U of the 64 x 64 matrix in LDS (upper triangle read), in place: U above,
 // zeros below, and U as a PACK in P (LDS or global).  A pivot that is not positive and finite
 // counts as 1 and clears *ok (LDS, set to 1 by the caller).
@@ -153,9 +183,18 @@ DEV void pack_upper(F f, double *P, double (*T)[16][17])
 // after the chain.  The wave whose columns are done inverts the diagonal block before.
 // 9.3 us where one wave with all 64 columns and scalar broadcasts took 13, and 2 us more for the
 // pack.
+//
+// A pivot is a diagonal entry less what the rows above take off it: at least 2^-53 of the entry,
+// unless it is none at all.  With all entries in 2^-900 .. 2^900 fast_rcp can take every pivot; other
+// blocks (descriptors or sigma_w of extreme size) go row by row.
 DEV void chol64(double (*S)[DL], double *P, int *ok)
 {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, g = lane >> 4, r = lane & 15;
+    const double sd = S[lane][lane];
+    if (__builtin_expect(__any((sd > 0.0 && sd < 0x1p-900) || (sd > 0x1p900 && sd < INFINITY)), 0)) {
+        chol64_plain(S, P, ok);
+        return;
+    }
 #pragma unroll 1
     for (int kb = 0; kb < 4; ++kb) {
         const int k0 = 16 * kb, c0 = 16 * wave;
