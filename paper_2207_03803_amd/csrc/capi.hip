@@ -105,14 +105,14 @@ Layout make_layout(int64_t NE, int64_t n_atoms, int64_t M, int32_t precision, in
     L.off_U = takep(sizeof(double) * QR_NB * QR_NB);
     L.off_rhs = takep(sizeof(double) * (size_t)M);
     L.off_misc = takep(sizeof(double) * 512);
-    L.off_tiles = take(sizeof(int32_t) * (size_t)(L.max_tiles + 2));
-    L.off_plan = take(sizeof(int32_t) * (size_t)knm_plan_ints(NE, L.plan_chunk));
+    L.off_tiles = take(sizeof(int32_t) * (size_t)(knm_tiles_room(NE, n_atoms) + 2));
+    L.off_plan = take(sizeof(int32_t) * (size_t)knm_plan_room(NE));
     if (n_obs > 0) {
         // derivative observations: their tile plan over the positions, and D = (X X_M^T)^(zeta - 1)
         L.plan_chunk_d = knm_plan_chunk(n_pos, M, d);
         L.max_tiles_d = knm_max_tiles(n_obs, n_pos, L.plan_chunk_d);
-        L.off_tiles_d = take(sizeof(int32_t) * (size_t)(L.max_tiles_d + 2));
-        L.off_plan_d = take(sizeof(int32_t) * (size_t)knm_plan_ints(n_obs, L.plan_chunk_d));
+        L.off_tiles_d = take(sizeof(int32_t) * (size_t)(knm_tiles_room(n_obs, n_pos) + 2));
+        L.off_plan_d = take(sizeof(int32_t) * (size_t)knm_plan_room(n_obs));
         L.off_D = takep(sizeof(double) * (size_t)n_atoms * (size_t)M);
     }
     L.off_counters = take(sizeof(unsigned) * N_COUNTERS);

@@ -49,6 +49,10 @@ int64_t knm_max_tiles(int64_t N, int64_t n_atoms, int chunk);
 // Plan arrays (device): tile_start [max_tiles + 1], n_tiles [1], cfg_list [N] followed by
 // the chunks' tile lists (knm_plan_ints(N, chunk) int32 together).
 int64_t knm_plan_ints(int64_t N, int chunk);
+// The same for the chunk that needs the most, whatever the sizes: a workspace's room (its size then
+// never falls where a larger problem takes longer chunks).
+int64_t knm_tiles_room(int64_t N, int64_t n_atoms);
+int64_t knm_plan_room(int64_t N);
 struct KnmPlan {
     int32_t *tile_start, *n_tiles, *cfg_list;
     uint16_t *lists;

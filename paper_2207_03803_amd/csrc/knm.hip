@@ -28,13 +28,14 @@ namespace gap {
 // configurations are 99.1 % full with chunks of 512, about 3.5 / chunk short of full.
 // ---------------------------------------------------------------------------
 constexpr int PLAN_C = 512;                // configurations per chunk, at most (a power of two)
+constexpr int PLAN_C_LEAST = 128;          // and at least
 
 // Configurations per chunk: a chunk costs 0.15 us per configuration, and a K_NM of T us loses
 // 3.5 T / chunk to its chunks' last tiles; 128 up to 1.3 ms, 256 up to 4.5 ms (at 63 TFLOP/s).
 int knm_plan_chunk(int64_t n_atoms, int64_t M, int64_t d)
 {
     const double flops = 2.0 * (double)n_atoms * (double)M * (double)d;
-    return flops < 8.2e10 ? 128 : (flops < 2.8e11 ? 256 : PLAN_C);
+    return flops < 8.2e10 ? PLAN_C_LEAST : (flops < 2.8e11 ? 256 : PLAN_C);
 }
 constexpr int PLAN_LARGE = KNM_CAP + 1;    // bucket of the configurations above KNM_CAP atoms
 constexpr int PLAN_WORDS = (KNM_CAP + 64) / 64;
@@ -42,6 +43,7 @@ constexpr int PLAN_WORDS = (KNM_CAP + 64) / 64;
 static int64_t plan_chunks(int64_t N, int chunk) { return (N + chunk - 1) / chunk; }
 // cfg_list [N] and, per chunk, its tile count and first positions (16 bits each)
 int64_t knm_plan_ints(int64_t N, int chunk) { return N + plan_chunks(N, chunk) * (chunk / 2); }
+int64_t knm_plan_room(int64_t N) { return knm_plan_ints(N, PLAN_C); }
 
 // lists: chunk c's tile starts at [c * chunk]; entry 0, always position 0, holds the tile
 // count instead.
@@ -234,6 +236,7 @@ int64_t knm_max_tiles(int64_t N, int64_t n_atoms, int chunk)
                     plan_chunks(N, chunk) + 1;
     return bound < N ? bound : N;
 }
+int64_t knm_tiles_room(int64_t N, int64_t n_atoms) { return knm_max_tiles(N, n_atoms, PLAN_C_LEAST); }
 
 // 256 threads, 4 waves of 64 x BN (BN = 64 by default, 32 as a tuning choice), BK = 8.
 // Bound by the FP64 matrix cores; two workgroups share a CU and one's tile set-up and
