@@ -22,6 +22,7 @@
 #include <algorithm>
 
 #include "kernels.h"
+#include "qr_split.h"
 #include "small64.h"
 
 namespace gap {
@@ -853,25 +854,6 @@ __global__ __launch_bounds__(S::NT, 3) void qr_update_kernel(
             }
 }
 
-// Split of rows [r0, m) into chunks for the split-K products (whole tiles of 64 rows): ncb tiles
-// per chunk, about `target` workgroups.  0: chunks of 1,024 rows, but at least 512 workgroups (two
-// per CU) and at most 2,048.  More chunks write and read more partial sums (2,048 workgroups: 9.45
-// ms for the QR of 18,250 x 2,250 in FP32, 512: 9.26), fewer leave the last round of
-// workgroups half empty (110,000 x 10,000 in FP64, 512 workgroups: 45 ms more than 2,048).
-static void chunking(int64_t rows, int64_t ncb, int64_t &chunk, int64_t &nch, int64_t cap, int64_t target = 2048)
-{
-    auto count = [&](int64_t wgs) { return (wgs + ncb - 1) / ncb; };
-    nch = target > 0 ? count(target) : std::max(count(512), std::min(count(2048), rows / 1024));
-    if (nch > cap)
-        nch = cap;
-    chunk = (rows + nch - 1) / nch;
-    chunk = (chunk + 63) & ~int64_t(63);
-    const int64_t least = rows <= 4096 ? 64 : 128;  // 64: 2,500 x 500 in FP32 2 % of the fit, 7,100 x 1,111 0.5 % slower
-    if (chunk < least)
-        chunk = least;
-    nch = (rows + chunk - 1) / chunk;
-}
-
 // w with its rows cut to those that can be nonzero in columns [0, j_end): below a
 // trailing upper-triangular block's row tri0 + j_end, every column before j_end
 // is still zero, so the reflectors of those columns are zero there and leave
@@ -911,30 +893,21 @@ static void factor_panel(const QrWork &wf, int64_t j0, int pw, double *Tout, hip
 }
 
 // P = Y^T C for the block at (j0, j0) of width pw, split over row chunks; returns their number.
-// The 64 x 64 tiles where either side is at most 64 wide, and where the large tiles would be
-// fewer than one per CU even with chunks of 512 rows.
 template <class T>
 static int64_t launch_wpart(const QrWork &w, int64_t j0, int pw, int64_t c0, int64_t nt, int ymode, int64_t r0,
                             int64_t target, hipStream_t s)
 {
     using L = typename QrTiles<T>::WL;
     using M = typename QrTiles<T>::WS;
-    const int64_t rows = w.m - r0;
-    auto tiles = [](int64_t x, int64_t b) { return (x + b - 1) / b; };
-    int64_t chunk, nch;
-    const bool narrow = pw <= 64 || nt <= 64 || tiles(nt, L::BN) * tiles(pw, L::BM) * tiles(rows, 512) < 256;
-    if (narrow) {
-        const int64_t nq = tiles(nt, M::BN), np = tiles(pw, M::BM);
-        chunking(rows, nq * np, chunk, nch, w.max_chunks, target);
-        hipLaunchKernelGGL((qr_wpart_kernel<M, 3>), dim3((unsigned)nq, (unsigned)nch, (unsigned)np), dim3(M::NT), 0, s, w,
-                           j0, pw, c0, nt, ymode, r0, chunk);
-    } else {
-        const int64_t nq = tiles(nt, L::BN), np = tiles(pw, L::BM);
-        chunking(rows, nq * np, chunk, nch, w.max_chunks, target);
-        hipLaunchKernelGGL((qr_wpart_kernel<L, QrTiles<T>::WL_WAVES>), dim3((unsigned)nq, (unsigned)nch, (unsigned)np), dim3(L::NT), 0, s, w,
-                           j0, pw, c0, nt, ymode, r0, chunk);
-    }
-    return nch;
+    const QrSplit q = qr_split(w.m - r0, pw, nt, L::BM, L::BN, sizeof(T) == 4, target, w.max_chunks);
+    const dim3 grid((unsigned)q.nq, (unsigned)q.nch, (unsigned)q.np);
+    static_assert(M::BM == QR_SMALL_TILE && M::BN == QR_SMALL_TILE, "small tiles");
+    if (q.small)
+        hipLaunchKernelGGL((qr_wpart_kernel<M, 3>), grid, dim3(M::NT), 0, s, w, j0, pw, c0, nt, ymode, r0, q.chunk);
+    else
+        hipLaunchKernelGGL((qr_wpart_kernel<L, QrTiles<T>::WL_WAVES>), grid, dim3(L::NT), 0, s, w, j0, pw, c0, nt,
+                           ymode, r0, q.chunk);
+    return q.nch;
 }
 
 // The compact-WY data of a trailing-update block at column J: panel pair a
