@@ -11,6 +11,14 @@
 // the diagonal, exactly as the TSQR panel does.  The intermediate Q's are kept in an FP64
 // scratch panel; the factored matrix may be stored in FP32 (arithmetic stays FP64).
 //
+// The rows are solved with explicit inverses of the factors' 16 x 16 diagonal blocks (solve_rows). Such a
+// solve loses the block's condition number times u. The blocks of R1 may be as ill-conditioned as P,
+// and those of R2 up to about u^-1/2 (beyond, its Cholesky fails and the panel is refused), so there
+// each block's solution is refined once. R3 is the identity up to what R2's pass leaves, the
+// pivots of U lie between 1 and 2, and Y1 is unit lower with entries of at most 1. Orthogonality and
+// backward error of panels of condition 1 to 1e13, Kahan's matrices among them, are those of row
+// substitution (464 x 64: 31 to 43 u and 3 to 5 u; with R2's solves unrefined up to 8 u).
+//
 // Four launches per panel, each one pass over its rows: the Gram matrix of P; then twice
 // a triangular solve of the rows together with the Gram matrix of the result; then the
 // last solve, with R, T and tau formed on a workgroup beside it.  The Gram partials of the
@@ -346,7 +354,7 @@ __global__ __launch_bounds__(CQ_NT) void cqr_step_kernel(CqArgs a, const TS *src
             load_rows(nxt, src, lds_, row + CQ_ROWS, hi, pw);
         const int nr = (int)((hi - r0) < CQ_ROWS ? (hi - r0) : CQ_ROWS);
         if (STEP != CQ_GRAM && 16 * wave < nr) {
-            solve_rows<STEP == CQ_PASS1>(y, P);
+            solve_rows<STEP != CQ_PASS3>(y, P);
             // the last pass leaves the top block (rows below pw) to the reconstruction
             store_rows(y, dst, ldd, row, STEP == CQ_PASS3 ? (int64_t)pw : (int64_t)0, hi, pw);
         }
