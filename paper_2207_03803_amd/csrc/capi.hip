@@ -594,9 +594,7 @@ static gap_status launch_knm_int8(gap_handle h, hipStream_t s)
     return dev(launch_knm_oz(l, s));
 }
 
-// On the handle's stream, after the K_NM: the low-precision K_NM (mixed BF16 /
-// FP16), K_MM + jitter (upper triangle) into rows N..N+M-1, then U = L^T in place.
-// K_MM + jitter and its Cholesky into the bottom block of A, on stream s.
+// K_MM + jitter (upper triangle) into rows N .. N + M - 1 of A, then U = L^T in place, on stream s.
 static gap_status launch_kmm_chol(gap_handle h, hipStream_t s)
 {
     const Layout &L = h->L;
@@ -648,6 +646,8 @@ static gap_status launch_knm_and_kmm(gap_handle h, const KnmArgs &a, bool &forke
     return st != GAP_OK ? st : sk;
 }
 
+// After the K_NM on the handle's stream: the low-precision K_NM (mixed BF16 / FP16), and K_MM with its
+// Cholesky, or the wait for them.
 static gap_status build_rest(gap_handle h, bool kmm_forked = false)
 {
     const Layout &L = h->L;

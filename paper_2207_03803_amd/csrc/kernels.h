@@ -107,8 +107,8 @@ struct QrAsync {
 hipError_t launch_geqrf(const QrWork &w, hipStream_t s, const QrAsync *la);
 
 // -------------------------------------------------------- triangular solve
-// State of the one-launch blocked substitution: xbuf [n] and flags [2], set by
-// launch_trsv_clear before the first solve (each solve leaves them as it found them), one
+// State of the one-launch blocked substitution: xbuf [2 n] (a second solve in the same launch has its
+// own half) and flags [2], set by launch_trsv_clear before the first solve (each solve leaves them as it found them), one
 // counter (zero), the device status word.
 struct TrsvSync {
     int32_t *flags;
@@ -188,9 +188,5 @@ hipError_t launch_diag_mixed(const DiagWork &d, const float *R32, const double *
 // b = [y / sigma ; 0] into column `col` of the column-major A (lda rows).
 hipError_t launch_assemble_b(const double *y, const double *sigma, int64_t N, double *bcol,
                              int64_t lda, hipStream_t s);
-hipError_t launch_fill(double *p, int64_t n, double v, hipStream_t s);
-// Zero rows [r0, r1) of columns [c0, c1) of a column-major matrix.
-hipError_t launch_zero_block(double *A, int64_t lda, int64_t r0, int64_t r1, int64_t c0, int64_t c1,
-                             hipStream_t s);
 
 }  // namespace gap

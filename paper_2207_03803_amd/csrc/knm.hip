@@ -258,8 +258,6 @@ constexpr int knm_lds_units()
     return (2 * KSB<BN>::UNITS > KNM_BM * EPLD / 2) ? 2 * KSB<BN>::UNITS : KNM_BM * EPLD / 2;
 }
 
-// One workgroup's tile; bid = the workgroup's index within this K_NM's own grid
-// (a multiple-of-8 offset into a grouped grid keeps bid's XCD the hardware's).
 // A derivative position whose gradient row and atom are in range.
 DEV bool kdm_valid(const KnmArgs &a, int64_t pos)
 {
@@ -271,6 +269,8 @@ DEV bool kdm_valid(const KnmArgs &a, int64_t pos)
 // positions.
 enum KnmRows { CONFIGS, POINTS, POSITIONS };
 
+// One workgroup's tile; bid = the workgroup's index within this K_NM's own grid
+// (a multiple-of-8 offset into a grouped grid keeps bid's XCD the hardware's).
 template <int BN, KnmRows ROWS = CONFIGS>
 DEV void knm_body(const KnmArgs &a, int64_t bid)
 {

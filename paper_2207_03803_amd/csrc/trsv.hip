@@ -134,43 +134,4 @@ hipError_t launch_copy_f32_f64(const float *src, double *dst, int64_t n, hipStre
     return hipGetLastError();
 }
 
-__global__ void fill_kernel(double *p, int64_t n, double v)
-{
-    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256)
-        p[i] = v;
-}
-
-hipError_t launch_fill(double *p, int64_t n, double v, hipStream_t s)
-{
-    if (n <= 0)
-        return hipSuccess;
-    int64_t g = (n + 255) / 256;
-    if (g > 65536)
-        g = 65536;
-    hipLaunchKernelGGL(fill_kernel, dim3((unsigned)g), dim3(256), 0, s, p, n, v);
-    return hipGetLastError();
-}
-
-__global__ void zero_block_kernel(double *A, int64_t lda, int64_t r0, int64_t r1, int64_t c0, int64_t c1)
-{
-    const int64_t rows = r1 - r0;
-    const int64_t total = rows * (c1 - c0);
-    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < total; i += (int64_t)gridDim.x * 256) {
-        const int64_t c = c0 + i / rows, r = r0 + i % rows;
-        A[c * lda + r] = 0.0;
-    }
-}
-
-hipError_t launch_zero_block(double *A, int64_t lda, int64_t r0, int64_t r1, int64_t c0, int64_t c1,
-                             hipStream_t s)
-{
-    if (r1 <= r0 || c1 <= c0)
-        return hipSuccess;
-    int64_t g = ((r1 - r0) * (c1 - c0) + 255) / 256;
-    if (g > 65536)
-        g = 65536;
-    hipLaunchKernelGGL(zero_block_kernel, dim3((unsigned)g), dim3(256), 0, s, A, lda, r0, r1, c0, c1);
-    return hipGetLastError();
-}
-
 }  // namespace gap
