@@ -739,7 +739,7 @@ def serve_sweep_md(out, args):
         lines.append(f"| {name} | {st} | {r.get('fp64_fallbacks', 0)} |")
     ok = all(r.get("all_fits_ok") for _, r in runs)
     lines += ["", "p99 of the fits is set by the realistic-size fits (5 % of the requests), each of which needs "
-              f"the whole GPU for about 1.3 s on its own. Every fit ended GAP_OK in every run: {ok}.", ""]
+              f"the whole GPU for about 0.8 s on its own. Every fit ended GAP_OK in every run: {ok}.", ""]
     return "\n".join(lines)
 
 

@@ -24,11 +24,11 @@
 // last solve, with R, T and tau formed on a workgroup beside it.  The Gram partials of the
 // workgroups are summed by the last one of them to arrive (in a fixed order, in two levels
 // above 16 workgroups), which then factors the 64 x 64 matrix that the next launch needs.
-// Bound by the latency of this chain: at 456 rows 20 + 25 + 44 + 12 us (of the first three, 9
+// Bound by the latency of this chain: at 456 rows 20 + 24 + 44 + 12 us (of the first three, 9
 // us each for the Cholesky factorisation, 13 for the LU, 4 for an arrival and the sum), 387
-// us with twelve launches and chains of 64 steps on one wave; at 16,000 rows 36 + 43 + 58 +
-// 13 (8 us more for the rows' loads, 10 for the second level of sums).  Workgroups of 256
-// threads and 64-row steps took 41 + 47 + 70 + 12 there.
+// us with twelve launches and chains of 64 steps on one wave; at 16,000 rows in FP32 storage 37 + 44 +
+// 62 + 13 (8 us more for the rows' loads, 10 for the second level of sums).  Workgroups of 256
+// threads and 64-row steps took 41 + 47 + 70 + 12 there, without the second pass's refinement (4 us).
 #include "kernels.h"
 #include "small64.h"
 
@@ -38,7 +38,7 @@ constexpr int CB = QR_NB;        // panel width bound (64)
 static_assert(CB == S64, "panel blocks");
 constexpr int CQ_NT = 512;       // threads of a workgroup; the 64 x 64 factorisations take the first 256
 constexpr int CQ_ROWS = CQ_NT / 4;  // rows per workgroup and step (16 per wave)
-constexpr int DT = CQ_ROWS + 2;  // LDS row stride of the transposed tile (free of bank conflicts like DL)
+constexpr int DT = CQ_ROWS + 2;  // LDS row stride of the transposed tile (its reads are free of bank conflicts)
 constexpr int CQ_GRP = 16;       // workgroups of one first-level sum
 constexpr int NENT = NBLK * BLK / CQ_NT;  // entries of a partial Gram matrix per thread
 static_assert(CQ_WGS * NBLK * BLK == CQ_PART && CQ_WGS / CQ_GRP < CQ_COUNTERS, "partials and counters");
