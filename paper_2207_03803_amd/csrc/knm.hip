@@ -911,34 +911,43 @@ __global__ __launch_bounds__(S::NT, S::BM == 64 ? 3 : 2) void predict_tile_kerne
         g_pred_pool[base + s * a.ld + t * S::BM + threadIdx.x] = e;
 }
 
-// An atom's energy from its runs' energies at p, p + ld, ...: groups of PRED_G column tiles in
-// order, as a workgroup that takes a whole group adds them.
-DEV double pred_atom_energy(const PredArgs &a, const double *p)
+// Adds up to B of an atom's run energies, at p, p + ld, ... (p the same in every lane, t the atom; n of
+// them) to e: groups of PRED_G column tiles in order, as a workgroup that takes a whole group adds
+// them. All loads in flight, those past the last run repeated (a branch around each costs more).
+template <int B>
+DEV void pred_add_runs(const PredArgs &a, const double *&p, int n, int t, double &e)
 {
-    constexpr int B = 32;
     static_assert(B % PRED_G == 0, "whole groups");
-    double e = 0.0;
-    for (int64_t s0 = 0; s0 < a.n_runs; s0 += B) {
-        double v[B];  // all loads in flight
+    double v[B];
+#pragma unroll
+    for (int k = 0; k < B; ++k) {
+        v[k] = p[t];
+        p += k + 1 < n || k + 1 == B ? a.ld : 0;
+    }
+#pragma unroll
+    for (int k = 0; k < B; ++k)
+        v[k] = k < n ? v[k] : 0.0;
+    if (a.run == 1) {
+#pragma unroll
+        for (int k = 0; k < B; k += PRED_G) {
+            double g = 0.0;
+#pragma unroll
+            for (int q = 0; q < PRED_G; ++q)
+                g += v[k + q];
+            e += g;
+        }
+    } else {
 #pragma unroll
         for (int k = 0; k < B; ++k)
-            v[k] = s0 + k < a.n_runs ? p[(s0 + k) * a.ld] : 0.0;
-        if (a.run == 1) {
-#pragma unroll
-            for (int k = 0; k < B; k += PRED_G) {
-                double g = 0.0;
-#pragma unroll
-                for (int q = 0; q < PRED_G; ++q)
-                    g += v[k + q];
-                e += g;
-            }
-        } else {
-#pragma unroll
-            for (int k = 0; k < B; ++k)
-                e += v[k];
-        }
+            e += v[k];
     }
-    return e;
+}
+
+// v, known to be the same in every lane.
+DEV int64_t uniform(int64_t v)
+{
+    const unsigned lo = __builtin_amdgcn_readfirstlane((unsigned)v), hi = __builtin_amdgcn_readfirstlane((unsigned)(v >> 32));
+    return (int64_t)((uint64_t)hi << 32 | lo);
 }
 
 // One group of configurations: checks their offsets, then adds up their atoms' energies, 256 atoms at a
@@ -994,8 +1003,20 @@ __global__ __launch_bounds__(KNM_NT, LAST ? 2 : 4) void predict_sum_kernel(PredA
         for (int64_t cs = lo; cs < hi; cs += S::BM) {
             double e = 0.0;
             if (base >= 0) {
-                if (cs + tid < hi)
-                    e = pred_atom_energy(a, g_pred_pool + base + (cs - a0) + tid);
+                const double *p = g_pred_pool + uniform(base + (cs - a0));
+                const int t = cs + tid < hi ? tid : (int)(hi - cs) - 1;  // past the end: the last atom, unused
+                for (int n = (int)a.n_runs; n > 0;) {
+                    if (n <= 8) {
+                        pred_add_runs<8>(a, p, n, t, e);
+                        n -= 8;
+                    } else if (n <= 16) {
+                        pred_add_runs<16>(a, p, n, t, e);
+                        n -= 16;
+                    } else {
+                        pred_add_runs<32>(a, p, n, t, e);
+                        n -= 32;
+                    }
+                }
             } else if constexpr (LAST) {
                 for (int64_t ct = 0; ct < a.n_ct; ct += PRED_G)
                     e += predict_tile_energy<S>(a, cs, ct, ct + PRED_G < a.n_ct ? ct + PRED_G : a.n_ct, lds, part);
@@ -1012,11 +1033,12 @@ __global__ __launch_bounds__(KNM_NT, LAST ? 2 : 4) void predict_sum_kernel(PredA
                     ysum += eps[r - cs];
         }
     }
+    // the last workgroup to have read the energies (before the barriers above) frees them
+    if (LAST && base >= 0 && (gridDim.x == 1 || arrive_last(&g_pred_done[base / PRED_CHUNK], gridDim.x, &last_s)) &&
+        tid < a.chunks)
+        __hip_atomic_store(&g_pred_owner[base / PRED_CHUNK + tid], 0ull, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
     if (out)
         a.y[cfg_lo + tid] = ysum;
-    // the last workgroup to have read the energies frees them
-    if (LAST && base >= 0 && arrive_last(&g_pred_done[base / PRED_CHUNK], gridDim.x, &last_s) && tid < a.chunks)
-        __hip_atomic_store(&g_pred_owner[base / PRED_CHUNK + tid], 0ull, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 hipError_t launch_predict(const double *X, int64_t n_atoms, const int64_t *offsets, int64_t N,
@@ -1053,11 +1075,11 @@ hipError_t launch_predict(const double *X, int64_t n_atoms, const int64_t *offse
     const int64_t most = ROOM / a.n_runs / PSL::BM * PSL::BM;
     const int64_t n_ranges = n_atoms > 0 && most > 0 ? tiles(n_atoms, most) : 1;
     const int64_t range = tiles(tiles(n_atoms, n_ranges), PSL::BM) * PSL::BM;
-    // 64-atom tiles where 256-atom ones are fewer than four rounds of the chip's 512 workgroup
-    // places: a workgroup then has a quarter of the work, and the last round costs less (1,692
-    // of the large tiles: 254 us, 275 with them); from there on the large ones are 2 % faster (9,009:
-    // 1,829 us, 1,873 with small ones)
-    const bool small = tiles(range, PSL::BM) * a.n_runs < 2048;
+    // The tile height whose whole rounds of workgroups take less: 512 places of 256 atoms, or 768 of 64,
+    // 3.5 % slower per atom (9,009 runs of large tiles, 18 rounds: 1,829 us, 1,873 on small ones, 47 rounds;
+    // 1,692, 4 rounds: 275 us, 254 in 9 rounds of small ones; 3,336, 7 rounds: 1,053 us, 1,016 in 18)
+    auto rounds = [&](int64_t rows, int64_t places) { return tiles(tiles(range, rows) * a.n_runs, places); };
+    const bool small = 1.035 * (double)(rounds(PSS::BM, 768) * 768 * PSS::BM) < (double)(rounds(PSL::BM, 512) * 512 * PSL::BM);
     const int64_t bm = small ? PSS::BM : PSL::BM;
     const int64_t ld = tiles(range < n_atoms ? range : n_atoms, bm) * bm;
     a.chunks = (int)tiles(ld * a.n_runs, PRED_CHUNK);
